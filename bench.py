@@ -26,26 +26,54 @@ def progress(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
-def kernel_words_per_node(N, curved=False, fp32=False):
-    """Algorithmic words per volume node for each kernel of one stage: every
+def stage_kernel_words(N, curved=False, fp32=False):
+    """Algorithmic words per volume node of each kernel of one stage: every
     array the kernel reads or writes, each element counted once (a face trace
     that an element and its neighbour both read counts once); F = 6/(N+1)
     face points per node. Wall face points also carry grad c in the T2 trace
     (3 words written by lift1, read by lift2 on Navier-slip walls), not
     counted: under 0.1 % of a stage on the wall workloads.  Curved meshes:
-    each stage kernel also reads the node metrics (9 Ja + J) and the face
-    points' normal and surface element (4 per face point).  FP32 instances
-    carry the face temperature's rounding error as a third T2 field (written
-    by lift1, read by lift2 on the own face)."""
+    lift1 and lift2 also read the node metrics (9 Ja + J) and the face
+    points' normal and surface element (4 per face point), the update J.
+    FP32 instances carry the rounding error of |grad c|^2 as a third T2 field
+    (written by lift1, read by lift2)."""
+    F = 6.0 / (N + 1)
+    k = {
+        "prolong": 6 + 6 * F,             # U in; conserved traces out
+        "lift1": 1 + 3 * F,               # c, neighbour c traces in; grad c . n and |grad c|^2 traces (2) out
+        "lift2": 16.8 + 14 * F,           # U, R, conserved traces (own and neighbour: 6), T2 traces (2) in; R with
+                                          # the volume part, flux traces (6) out; R is read by stages 2-5: 4/5 of 6
+        "update": 22.8 + 12 * F,          # U, R, flux traces (6) in; U, R, conserved traces (6) out; R is written
+                                          # by stages 1-4: 4/5 of 6
+    }
+    if fp32:
+        k["lift1"] += F
+        k["lift2"] += F
+    if curved:
+        k["lift1"] += 10 + 4 * F
+        k["lift2"] += 10 + 4 * F
+        k["update"] += 1
+    return k
+
+
+def stage_words(N, curved=False, fp32=False):
+    k = stage_kernel_words(N, curved, fp32)
+    return k["lift1"] + k["lift2"] + k["update"]
+
+
+def kernel_words_per_node(N, curved=False, fp32=False):
+    """The same count for a stage whose update kernel lifts the gradients
+    again and forms the volume integral itself (grad T, lap c and seven flux
+    fields go through memory, the partly updated register does not): the
+    yardstick `relift_bytes_per_node_stage` of the stage model."""
     F = 6.0 / (N + 1)
     k = {
         "prolong": 6 + 6 * F,             # U in; conserved traces out
         "lift1": 6 + 3 * F,               # U, neighbour c traces in; grad c . n + T traces (2) out
-        "lift2": 10 + 15 * F,             # U, conserved traces (own and neighbour: 6), grad c . n + T traces (2)
-                                          # in; grad T + lap c (4), flux + wave-speed traces (7) out
+        "lift2": 10 + 15 * F,             # U, conserved traces (6), grad c . n + T traces (2) in; grad T + lap c
+                                          # (4), flux + wave-speed traces (7) out
         "update": 25.6 + 19 * F,          # U, R, grad T + lap c, neighbour conserved traces (6), flux traces (7)
-                                          # in; U, R, conserved traces (6) out; R (6) is read by stages 2-5 and
-                                          # written by stages 1-4, so 4/5 of its 12 words per launch of a step
+                                          # in; U, R, conserved traces (6) out
     }
     if fp32:
         k["lift1"] += F
@@ -598,7 +626,7 @@ def main():
         prof = s.profile(stream)
         s.set_profiling(False)
         word = 8 if precision == "fp64" else 4
-        words = kernel_words_per_node(wk.N, wk.curve_amp != 0.0, precision == "fp32_mixed")
+        words = stage_kernel_words(wk.N, wk.curve_amp != 0.0, precision == "fp32_mixed")
         if precision == "fp32_mixed" and s.kahan:
             words["update"] += 12  # compensation of the state update, read and written
         kern = {}
@@ -629,8 +657,9 @@ def main():
     dom = max(kern, key=lambda k: kern[k]["avg_us"] * kern[k]["launches"])
     ach = kern[dom]["achieved_GBs"]
     floor_b, b3 = three_phase_bytes_model(w.N, word)
-    stage_b = (stage_words_per_node(w.N, w.curve_amp != 0.0, args.precision == "fp32_mixed") +
-               (12 if args.precision == "fp32_mixed" else 0)) * word
+    extra = 12 if args.precision == "fp32_mixed" else 0  # compensation of the state update
+    stage_b = (stage_words(w.N, w.curve_amp != 0.0, args.precision == "fp32_mixed") + extra) * word
+    relift_b = (stage_words_per_node(w.N, w.curve_amp != 0.0, args.precision == "fp32_mixed") + extra) * word
     out = {
         "metric": METRIC,
         "value": value,
@@ -655,6 +684,7 @@ def main():
                          "stream) over a second pass of the same K steps right after the timed pass",
         "stage_model": {"design_bytes_per_node_stage": stage_b,
                         "design_GBs": value * stage_b / 1e9,
+                        "relift_bytes_per_node_stage": relift_b,
                         "B_3phase_bytes": b3, "B_3phase_GBs": value * b3 / 1e9,
                         "B_floor_bytes": floor_b, "B_floor_GBs": value * floor_b / 1e9},
         "gpu_event_ms": r["gpu_ms"],

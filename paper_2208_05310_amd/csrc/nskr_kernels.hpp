@@ -15,22 +15,24 @@
 //
 // Data flow of one stage (BR1 needs three neighbour exchanges).  Only what a
 // later kernel cannot rebuild from the state goes through memory: the lifted
-// gradients of the primitives are recomputed where they are needed from the
-// state and the neighbours' conserved face traces, which costs a few hundred
-// flops per node and saves their storage round trip.
-//   k_lift1  : U + neighbour c traces -> lifted grad c; own-face traces of
-//              (grad c) . n, of the face temperature and, on walls, of grad c
-//              (T2).
-//   k_lift2  : U + neighbour conserved traces -> lifted grad u, grad c, nodal
-//              T; with the T2 traces of both sides -> grad T, lap c (G2);
-//              then the own-face flux traces (normal flux, wave speed), or the
-//              complete wall flux on wall faces (TF).
-//   k_update : U + neighbour conserved traces -> all lifted gradients again;
-//              volume integral of the contravariant fluxes, surface integral
-//              of the Rusanov (model 2: HLLC) + central viscous face flux,
-//              point-wise source,
-//              Jacobian scaling, RK stage update, and the conserved face
-//              traces of the new state for the next stage.
+// gradients never do.
+//   k_lift1  : c + neighbour c traces -> lifted grad c; own-face traces of
+//              (grad c) . n, of |grad c|^2 and, on walls, of grad c (T2).
+//   k_lift2  : U + both sides' conserved and T2 traces -> all lifted
+//              gradients, nodal and face temperatures, grad T, lap c; the
+//              volume integral of the contravariant fluxes and the point-wise
+//              source, into the RK register; the own-face flux traces:
+//              convective flux with the own half of the Rusanov dissipation
+//              (model 2: the HLLC flux) and viscous flux, or the complete wall
+//              flux on wall faces (TF).
+//   k_update : TF of both sides -> surface integral, RK stage update, and the
+//              conserved face traces of the new state for the next stage.
+// Everything that needs the gradients is done in the one kernel that lifts
+// them.  Where the update kernel lifted them again for the volume integral,
+// the three kernels took 132, 412 and 570 us on 32^3 elements of N = 5 in
+// FP64 (71, 232 and 317 us on 48x48x24 of N = 3); this split takes 105, 475
+// and 402 us (55, 291 and 212), moves 11 % fewer bytes and evaluates half as
+// many sweeps.
 // The conserved traces rotate over three buffers: stage s reads buffer b(s)
 // and writes b(s+1), b = 0 1 0 1 2 (0), so no kernel overwrites traces that
 // a neighbouring workgroup may still read.
@@ -133,24 +135,64 @@ struct MeshDev {
     const int *bcid;     // [E][6] 0 interior, else 1-based wall index
     // affine elements (the kernels' CV = false instances)
     const double *emet;  // [E][10] Ja[d*3+m], J
-    const double *fmet;  // [E][6][4] outward unit normal, surface element
+    const void *em;      // [E][kEm] what the stage kernels read of an element, in the element type of
+                         // the precision: [6][4] outward unit normal and surface element of its
+                         // faces, Ja[d*3+m], 1/J
     const double *egeo;  // [E][12] corner 0 and the three edge vectors
     // curved elements (CV = true), in the element type of the precision
     const void *nmet;    // [10][nodes] Ja[d*3+m] and J at every node
     const void *fnrm;    // [E][6][P^2][4] outward unit normal and surface element at every face point
     const double *xnode; // [3][nodes] node coordinates (initial state)
     const BcDev *bcs;
+    int wall;            // some face is a wall
     int dyn;             // some Navier-slip wall has gamma_1 != 0 (g needs div u at the wall)
     const double *stab;  // [kTabN][3] wall-temperature table (walls with a temperature gradient)
     int var;             // some wall has a temperature gradient or rate
 };
 
-template <int P, int BS = kBlock> struct Tile {
+// Values of a record of MeshDev::em, and where Ja and 1/J stand in it.
+constexpr int kEm = 36, kEmJa = 24, kEmIJ = 33;
+
+template <int P, int BS = kBlock, int EPB_ = BS / (P * P * P)> struct Tile {
     static constexpr int n2 = P * P, n3 = P * P * P;
-    static constexpr int EPB = BS / n3;         // elements per block
-    static constexpr int NV = EPB * n3;         // active node threads
+    static constexpr int EPB = EPB_;            // elements per block
+    static constexpr int NV = EPB * n3;         // nodes per block
     static constexpr int NF = EPB * 6 * n2;     // face points per block
+    // Threads per element of the node phases: whole waves where the block has
+    // room for it, so that a wave's element (and with it everything read per
+    // element) is uniform.
+    static constexpr int kWaves = (n3 + 63) / 64 * 64;
+    static constexpr bool kUni = EPB * kWaves <= BS;
+    static constexpr int TPE = kUni ? kWaves : n3;
 };
+
+// Node thread of a workgroup: local element, node of the element, and the
+// node's place in the workgroup's tile.
+template <typename G> struct NodeTask {
+    int le, nd, q;
+    bool in;
+    __device__ __forceinline__ NodeTask(int t)
+    {
+        le = t / G::TPE;
+        nd = t - le * G::TPE;
+        in = le < G::EPB && nd < G::n3;
+        q = le * G::n3 + nd;
+    }
+};
+
+// Value r of element e's record; UNI: e is the same for all lanes of the wave
+// and the load a scalar one, whatever the kernel has stored before it (the
+// records do not change while a kernel runs).
+template <bool UNI, typename T> __device__ __forceinline__ T em_at(const MeshDev &m, int e, int r)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (UNI) {
+        const uint32_t u = __builtin_amdgcn_readfirstlane(e);
+        return ((const __attribute__((address_space(4))) T *)m.em)[(size_t)u * kEm + r];
+    }
+#endif
+    return gld((const T *)m.em, (uint32_t)e * kEm + r);
+}
 
 template <int P> __device__ __forceinline__ int line_node(int d, int l, int p, int q)
 {
@@ -193,17 +235,18 @@ __device__ __forceinline__ void face_normal(const MeshDev &m, size_t face, int f
         n[2] = gld(fn, q + 2);
         dS = gld(fn, q + 3);
     } else {
-        const uint32_t q = (uint32_t)face * 4;
-        n[0] = T(gld(m.fmet, q));
-        n[1] = T(gld(m.fmet, q + 1));
-        n[2] = T(gld(m.fmet, q + 2));
-        dS = T(gld(m.fmet, q + 3));
+        const T *em = (const T *)m.em;
+        const uint32_t q = (uint32_t)face / 6 * (kEm - 24) + (uint32_t)face * 4;
+        n[0] = gld(em, q);
+        n[1] = gld(em, q + 1);
+        n[2] = gld(em, q + 2);
+        dS = gld(em, q + 3);
     }
 }
 template <int P, typename T, bool CV> __device__ __forceinline__ T face_dS(const MeshDev &m, size_t face, int fp)
 {
     if (CV) return gld((const T *)m.fnrm, ((uint32_t)face * (P * P) + fp) * 4 + 3);
-    return T(gld(m.fmet, (uint32_t)face * 4 + 3));
+    return gld((const T *)m.em, (uint32_t)face / 6 * (kEm - 24) + (uint32_t)face * 4 + 3);
 }
 
 // ---------------------------------------------------------------- physics
@@ -223,14 +266,20 @@ template <bool FAST> __device__ __forceinline__ double recip(double x)
 // Temperature recovery of eq. totalenergyalpha with eps = R c_v T - a rho
 // (always FP64 arithmetic: it cancels large terms near the spinodal).
 template <bool FAST = false>
-__device__ __forceinline__ double temperature(const Phys &ph, double rho, double m0, double m1, double m2,
-                                              double E, double c, double q0, double q1, double q2)
+__device__ __forceinline__ double temperature_g2(const Phys &ph, double rho, double m0, double m1, double m2,
+                                                 double E, double c, double g2)
 {
     const double ir = recip<FAST>(rho);
     double kin = 0.5 * (m0 * m0 + m1 * m1 + m2 * m2) * ir;
     double rel = 0.5 * ph.alpha * (rho - c) * (rho - c);
-    double grd = 0.5 * ph.gam * (q0 * q0 + q1 * q1 + q2 * q2);
+    double grd = 0.5 * ph.gam * g2;
     return ((E - kin - rel - grd) * ir + ph.a * rho) * ph.inv_Rcv;
+}
+template <bool FAST = false>
+__device__ __forceinline__ double temperature(const Phys &ph, double rho, double m0, double m1, double m2,
+                                              double E, double c, double q0, double q1, double q2)
+{
+    return temperature_g2<FAST>(ph, rho, m0, m1, m2, E, c, q0 * q0 + q1 * q1 + q2 * q2);
 }
 
 // van der Waals pressure (eq. pressure) and isentropic sound speed squared
@@ -252,45 +301,6 @@ template <typename T> __device__ __forceinline__ T sqrt_to(double x)
 {
     if (sizeof(T) == 4) return T(sqrtf((float)x));
     return T(sqrt(x));
-}
-
-// Local state at a point for the flux evaluation.
-template <typename T> struct Pt {
-    T rho, m[3], E, c;    // conserved
-    T ir;                 // 1 / rho
-    T p;                  // pressure
-    T gu[3][3];           // gu[j][i] = d u_j / d x_i
-    T gT[3], gc[3], lapc; // grad T, grad c, lap c
-};
-
-// Physical flux tensor of relaxation model 1 (eq. navierstokeskorteweg_p),
-// F[v][i] = (F^C - F^V)_v . e_i, so that (F^C - F^V) . w = sum_i F[v][i] w_i
-// for any vector w (the contravariant metric rows in the volume integral):
-// F^V = (0, tau, tau u + j_e, gamma beta grad c), tau = mu (grad u + grad u^T
-// - 2/3 div u I), j_e = k grad T - gamma c grad c div u + gamma grad c zeta,
-// zeta = beta (gamma lap c + alpha (rho - c)).
-template <typename T>
-__device__ __forceinline__ void flux_tensor(const Phys &ph, const Pt<T> &s, T F[6][3])
-{
-    const T ir = s.ir;
-    const T u[3] = {s.m[0] * ir, s.m[1] * ir, s.m[2] * ir};
-    const T div = s.gu[0][0] + s.gu[1][1] + s.gu[2][2];
-    const T mu = T(ph.mu), tdiv = T(2.0 / 3.0) * div;
-    T tau[3][3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-#pragma unroll
-        for (int i = 0; i < 3; ++i) tau[j][i] = mu * (s.gu[j][i] + s.gu[i][j] - (i == j ? tdiv : T(0)));
-    const T zeta = T(ph.beta) * (T(ph.gam) * s.lapc + T(ph.alpha) * (s.rho - s.c));
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const T je = T(ph.kappa) * s.gT[i] - T(ph.gam) * s.c * s.gc[i] * div + T(ph.gam) * s.gc[i] * zeta;
-        F[0][i] = s.m[i];
-#pragma unroll
-        for (int j = 0; j < 3; ++j) F[1 + j][i] = s.m[j] * u[i] + (i == j ? s.p : T(0)) - tau[j][i];
-        F[4][i] = (s.E + s.p) * u[i] - (tau[i][0] * u[0] + tau[i][1] * u[1] + tau[i][2] * u[2]) - je;
-        F[5][i] = s.c * u[i] - T(ph.gam * ph.beta) * s.gc[i];
-    }
 }
 
 // HLLC flux (Toro 2009, Sec. 10.4) of the convective part for relaxation
@@ -338,34 +348,33 @@ __device__ __forceinline__ void hllc(const T uL[6], T pL, T aL, const T uR[6], T
 // Relaxation model 2 (eq. navierstokeskorteweg_palpha) drops the alpha rho
 // grad rho and alpha/2 rho^2 div u parts, which its pressure p_alpha carries.
 template <typename T>
-__device__ __forceinline__ void source(const Phys &ph, const Pt<T> &s, const T grho[3], T S[6])
+__device__ __forceinline__ void source(const Phys &ph, T rho, T c, const T u[3], const T grho[3], const T gu[3][3],
+                                       const T gc[3], T S[6])
 {
-    const T ir = s.ir;
-    const T u[3] = {s.m[0] * ir, s.m[1] * ir, s.m[2] * ir};
-    const T div = s.gu[0][0] + s.gu[1][1] + s.gu[2][2];
+    const T div = gu[0][0] + gu[1][1] + gu[2][2];
     const T al = T(ph.alpha);
     const bool m2 = ph.model == 2;
     T d[3], gg = T(0), cc = T(0), du = T(0);
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        d[i] = m2 ? s.gc[i] : s.gc[i] - grho[i];
-        gg += s.gc[i] * s.gc[i];
+        d[i] = m2 ? gc[i] : gc[i] - grho[i];
+        gg += gc[i] * gc[i];
         du += d[i] * u[i];
     }
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         T r = T(0);
 #pragma unroll
-        for (int j = 0; j < 3; ++j) r += s.gc[j] * s.gu[j][i];
-        cc += s.gc[i] * r;
+        for (int j = 0; j < 3; ++j) r += gc[j] * gu[j][i];
+        cc += gc[i] * r;
     }
     S[0] = T(0);
-    S[1] = al * s.rho * d[0];
-    S[2] = al * s.rho * d[1];
-    S[3] = al * s.rho * d[2];
-    S[4] = al * s.rho * du + T(0.5) * al * (m2 ? s.c * s.c : s.c * s.c - s.rho * s.rho) * div +
+    S[1] = al * rho * d[0];
+    S[2] = al * rho * d[1];
+    S[3] = al * rho * d[2];
+    S[4] = al * rho * du + T(0.5) * al * (m2 ? c * c : c * c - rho * rho) * div +
            T(ph.gam) * (T(0.5) * gg * div - cc);
-    S[5] = al * T(ph.beta) * (s.rho - s.c);
+    S[5] = al * T(ph.beta) * (rho - c);
 }
 
 // ------------------------------------------------------------ kernel args
@@ -375,9 +384,9 @@ template <typename T> struct Inst {
     T *U, *R, *Ut;             // state, RK register, U_t output (rhs)
     T *Ck;                     // compensation of the state update (FP32 Kahan), or null
     T *Q, *TH;                 // grad(rho,u,c) [15] and T, for the API outputs only
-    T *G2;                     // grad T + lap c [4]
-    T *T2, *TF, *TU;           // face traces: grad c . n and T (+ grad c on walls) [kT2<T>()],
-                               // flux + wave speed [7],
+    T *G2;                     // grad T + lap c [4], for the API output only
+    T *T2, *TF, *TU;           // face traces: grad c . n, |grad c|^2 (+ grad c on walls) [kT2<T>()],
+                               // flux [6],
                                // conserved state [3 buffers][6]; within an array
                                // (a buffer) face-major: [face][field][point]
     MeshDev mesh;
@@ -398,7 +407,7 @@ template <typename T> struct Launch {
     const int *blk_inst, *blk_e0;
     const int *blk_map;  // single instance: first element of every block (null: block b, elements b EPB..)
     Basis bas;
-    int mode;        // update: 0 write U_t; 1 RK stage (update U, R, write traces)
+    int mode;        // 0 write U_t; 1 RK stage (update U, R, write traces); 2 write grad T and lap c (k_lift2)
     int first;       // RK: assign R at the first stage
     int last;        // RK: the step's last stage, which does not store R (the next
                      // stage to read it is a first stage, which assigns it)
@@ -424,14 +433,16 @@ __device__ __forceinline__ double stage_time(double t0, int n, double dt, double
 // not K runs of N2 values each that straddle line boundaries, and the field
 // offsets are compile-time constants.
 // Fields of the T2 face trace: (grad c) . n with the element's own outward
-// normal, the face temperature, and on wall faces only the vector grad c
-// (the tangential gradient of a Navier-slip wall). Interior faces need only
-// the first two: the divergence lifting of grad c takes the central normal
-// component, and the neighbour's outward normal is minus the own one.
-// FP32 instances store the FP64 face temperature as two floats, the rounded
-// value (the BR1 face value of the FP32 lifting) and the rounding error in
-// the field after it, so that the pressure and sound speed at the face are
-// formed from the temperature as recovered in FP64 (about 48 bits).
+// normal, |grad c|^2, and on wall faces only the vector grad c (the
+// tangential gradient of a Navier-slip wall). Interior faces need only the
+// first two: the divergence lifting of grad c takes the central normal
+// component, and the neighbour's outward normal is minus the own one; the
+// face temperature of either side follows from its |grad c|^2 and its
+// conserved trace, so the kernel that needs it recovers it there and the one
+// that lifts grad c reads one field of the state instead of six.
+// FP32 instances store |grad c|^2, formed in FP64, as two floats, the
+// rounded value and the rounding error in the field after it, so that the
+// face temperature is the one recovered in FP64 (about 48 bits).
 template <typename T> constexpr int kT2() { return sizeof(T) == 4 ? 6 : 5; }
 template <typename T> constexpr int kT2gc() { return sizeof(T) == 4 ? 3 : 2; }  // first wall grad c field
 
@@ -461,32 +472,58 @@ template <typename P> __device__ __forceinline__ P load_const(const P *p, int i)
 }
 
 template <typename T, bool BATCH>
-__device__ __forceinline__ void instance_of(const Launch<T> &L, Inst<T> &a, int &e0, int epb)
+__device__ __forceinline__ void instance_of(const Launch<T> &L, Inst<T> &a, int &e0, int epb, int b)
 {
     if (BATCH) {
-        const int k = load_const(L.blk_inst, blockIdx.x);
-        e0 = load_const(L.blk_e0, blockIdx.x);
+        const int k = load_const(L.blk_inst, b);
+        e0 = load_const(L.blk_e0, b);
         a = load_const(L.tab, k);
     } else {
         a = L.one;
-        e0 = L.blk_map ? load_const(L.blk_map, blockIdx.x) : blockIdx.x * epb;
+        e0 = L.blk_map ? load_const(L.blk_map, b) : b * epb;
     }
 }
 
-// Copy the basis into LDS (the rows each thread needs differ per lane), in
-// the element type of the kernel: FP32 instances then read and multiply
-// floats (the values are the FP64 host basis rounded once, as a conversion
-// at every use would round them).
-template <int P, typename B_>
-__device__ __forceinline__ void load_basis(const Basis &b, B_ *sDh, B_ *sL, B_ *sLh)
-{
-    const int t = threadIdx.x;
-    if (t < P * P) sDh[t] = B_(b.Dh[t]);
-    if (t < 2 * P) {
-        sL[t] = B_(b.L[t / P][t % P]);
-        sLh[t] = B_(b.Lh[t / P][t % P]);
+// Pairs of fields.  The LDS delivers 128-bit reads at the same rate per
+// instruction as 64-bit ones (measured: 4.5 against 4.4 cycles per wave
+// instruction, 137 against 71 TB/s over the chip; 5.4 and 5.3 along the lines
+// of an N = 5 element), and the stage kernels read every node value once per
+// node of its three lines, so fields that are swept together lie together.
+template <typename T> using V2 = T __attribute__((ext_vector_type(2)));
+
+// 1D operators in LDS (the rows each thread needs differ per lane), in the
+// element type of the kernel: FP32 instances then read and multiply floats
+// (the values are the FP64 host basis rounded once, as a conversion at every
+// use would round them).  Rows are padded to whole pairs.
+template <int P, typename T> struct alignas(16) BasisS {
+    static constexpr int PS = (P + 1) / 2 * 2;
+    T Dh[P * PS];     // Dhat, row i at i PS
+    T Lf[2 * PS];     // l_j(-1), l_j(+1)
+    V2<T> L[P];       // (l_j(-1), l_j(+1))
+    V2<T> Lh[P];      // (l_j(-1), l_j(+1)) / w_j
+    __device__ __forceinline__ void load(const Basis &b)
+    {
+        const int t = threadIdx.x;
+        if (t < P * P) Dh[t / P * PS + t % P] = T(b.Dh[t]);
+        if (t < 2 * P) Lf[t / P * PS + t % P] = T(b.L[t / P][t % P]);
+        if (t < P) {
+            L[t] = V2<T>{T(b.L[0][t]), T(b.L[1][t])};
+            Lh[t] = V2<T>{T(b.Lh[0][t]), T(b.Lh[1][t])};
+        }
     }
-}
+    // a padded row of P values
+    static __device__ __forceinline__ void row(const T *r, T out[P])
+    {
+        const V2<T> *v = (const V2<T> *)r;
+#pragma unroll
+        for (int l = 0; l < P / 2; ++l) {
+            const V2<T> q = v[l];
+            out[2 * l] = q.x;
+            out[2 * l + 1] = q.y;
+        }
+        if constexpr (P % 2) out[P - 1] = r[P - 1];
+    }
+};
 
 // Line task: the line of P nodes through face point (p,q) along direction d
 // of local element le; it carries the two face points of faces 2d (xi^d = -1)
@@ -508,9 +545,10 @@ template <int P> struct LineTask {
     }
 };
 
-// Prolongation of one LDS field of an element to both faces of a line.
-template <int P, typename T, typename B_>
-__device__ __forceinline__ void prolong2(const T *s, int base, const B_ *sL, const LineTask<P> &lt, T &vm,
+// Prolongation of one LDS field of an element, or of a pair of fields, to
+// both faces of a line.
+template <int P, typename T>
+__device__ __forceinline__ void prolong2(const T *s, int base, const BasisS<P, T> &B, const LineTask<P> &lt, T &vm,
                                          T &vp)
 {
     T am = T(0), ap = T(0);
@@ -518,11 +556,31 @@ __device__ __forceinline__ void prolong2(const T *s, int base, const B_ *sL, con
 #pragma unroll
     for (int l = 0; l < P; ++l) {
         const T v = ln[l * lt.str];
-        am += T(sL[l]) * v;
-        ap += T(sL[P + l]) * v;
+        const V2<T> w = B.L[l];
+        am += w.x * v;
+        ap += w.y * v;
     }
     vm = am;
     vp = ap;
+}
+template <int P, typename T>
+__device__ __forceinline__ void prolong2(const V2<T> *s, int base, const BasisS<P, T> &B, const LineTask<P> &lt,
+                                         T *vm, T *vp)
+{
+    T am0 = T(0), ap0 = T(0), am1 = T(0), ap1 = T(0);
+    const V2<T> *ln = s + base + lt.off;
+#pragma unroll
+    for (int l = 0; l < P; ++l) {
+        const V2<T> v = ln[l * lt.str], w = B.L[l];
+        am0 += w.x * v.x;
+        ap0 += w.y * v.x;
+        am1 += w.x * v.y;
+        ap1 += w.y * v.y;
+    }
+    vm[0] = am0;
+    vm[1] = am1;
+    vp[0] = ap0;
+    vp[1] = ap1;
 }
 
 // Face task: face point fp of face f of local element le, with the line of
@@ -634,9 +692,9 @@ __device__ __forceinline__ WallPt wall_point(const MeshDev &m, const Basis &bas,
 // J q_m = sum_d Ja^d_m (Dhat w + lhat(+1) w*_+ - lhat(-1) w*_-), from the node
 // values fw (element starting at base) and face values fs (element's face
 // points starting at fbase) in LDS.
-template <int P, typename T, typename B_>
+template <int P, typename T>
 __device__ __forceinline__ void lifted_grad(const T *fw, const T *fs, int base, int fbase, int i, int j, int k,
-                                            const B_ *sDh, const B_ *sLh, const T Ja[9], T iJ, T q[3])
+                                            const BasisS<P, T> &B, const T Ja[9], T iJ, T q[3])
 {
     constexpr int n2 = P * P;
     const int idx[3] = {i, j, k};
@@ -644,60 +702,90 @@ __device__ __forceinline__ void lifted_grad(const T *fw, const T *fs, int base, 
     T gd[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        T acc = T(0);
-        const int id = idx[d];
+        T acc = T(0), D[P];
         const int p = d == 0 ? j : i, r = d == 2 ? j : k;
+        B.row(B.Dh + idx[d] * B.PS, D);
 #pragma unroll
-        for (int l = 0; l < P; ++l) acc += T(sDh[id * P + l]) * fw[base + line_node<P>(d, l, p, r)];
-        acc += T(sLh[P + id]) * fs[fbase + (2 * d + 1) * n2 + fpd[d]];
-        acc -= T(sLh[id]) * fs[fbase + (2 * d) * n2 + fpd[d]];
+        for (int l = 0; l < P; ++l) acc += D[l] * fw[base + line_node<P>(d, l, p, r)];
+        const V2<T> lh = B.Lh[idx[d]];
+        acc += lh.y * fs[fbase + (2 * d + 1) * n2 + fpd[d]];
+        acc -= lh.x * fs[fbase + (2 * d) * n2 + fpd[d]];
         gd[d] = acc;
     }
 #pragma unroll
     for (int m = 0; m < 3; ++m) q[m] = iJ * (Ja[m] * gd[0] + Ja[3 + m] * gd[1] + Ja[6 + m] * gd[2]);
 }
 
-// The same lifted gradient for NFLD consecutive LDS fields at once, sweeping
-// direction by direction so that only one row of Dhat is live: the reference
-// derivatives gd[f][d] first, then the metric transform.  Each (field,
-// direction) sum is formed exactly as in lifted_grad.
-template <int P, int NFLD, int NVS, int NFS, typename T, typename B_>
-__device__ __forceinline__ void lifted_grads(const T (*fw)[NVS], const T (*fs)[NFS], int base, int fbase, int i, int j,
-                                             int k, const B_ *sDh, const B_ *sLh, T gd[NFLD][3])
+// Bounds the loads that a sweep keeps in flight: what has been loaded is
+// summed into a[0..n) before anything that follows is loaded.  Without it the
+// compiler requests a whole line of every field at once and needs the
+// registers of one or two waves per SIMD for it.
+template <typename T> __device__ __forceinline__ void bound(T *a, int n)
+{
+#pragma unroll
+    for (int k = 0; k < n; ++k) asm volatile("" : "+v"(a[k]));
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Five fields of a tile: two rows of pairs and one single row.
+template <typename T> struct Five {
+    const V2<T> *a, *b;
+    const T *c;
+    __device__ __forceinline__ void at(int n, T v[5]) const
+    {
+        const V2<T> x = a[n], y = b[n];
+        v[0] = x.x;
+        v[1] = x.y;
+        v[2] = y.x;
+        v[3] = y.y;
+        v[4] = c[n];
+    }
+};
+
+// The same lifted gradient for five fields at once, sweeping direction by
+// direction so that only one row of Dhat is live: the reference derivatives
+// gd[f][d], before the metric transform.
+template <int P, typename T>
+__device__ __forceinline__ void lifted_grads(const Five<T> &w, const Five<T> &s, int base, int fbase, int i, int j,
+                                             int k, const BasisS<P, T> &B, T gd[5][3])
 {
     constexpr int n2 = P * P;
     const int idx[3] = {i, j, k};
     const int fpd[3] = {j + P * k, i + P * k, i + P * j};
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        const int id = idx[d];
         const int p = d == 0 ? j : i, r = d == 2 ? j : k;
-        T Dl[P];
+        T D[P], acc[5] = {T(0), T(0), T(0), T(0), T(0)}, v[5];
+        B.row(B.Dh + idx[d] * B.PS, D);
 #pragma unroll
-        for (int l = 0; l < P; ++l) Dl[l] = T(sDh[id * P + l]);
-        const T lp = T(sLh[P + id]), lm = T(sLh[id]);
+        for (int l = 0; l < P; ++l) {
+            w.at(base + line_node<P>(d, l, p, r), v);
 #pragma unroll
-        for (int f = 0; f < NFLD; ++f) {
-            T acc = T(0);
-#pragma unroll
-            for (int l = 0; l < P; ++l) acc += Dl[l] * fw[f][base + line_node<P>(d, l, p, r)];
-            acc += lp * fs[f][fbase + (2 * d + 1) * n2 + fpd[d]];
-            acc -= lm * fs[f][fbase + (2 * d) * n2 + fpd[d]];
-            gd[f][d] = acc;
+            for (int f = 0; f < 5; ++f) acc[f] += D[l] * v[f];
+            if (l % 2 == 1) bound(acc, 5);
         }
+        bound(acc, 5);
+        const V2<T> lh = B.Lh[idx[d]];
+        s.at(fbase + (2 * d + 1) * n2 + fpd[d], v);
+#pragma unroll
+        for (int f = 0; f < 5; ++f) acc[f] += lh.y * v[f];
+        s.at(fbase + (2 * d) * n2 + fpd[d], v);
+#pragma unroll
+        for (int f = 0; f < 5; ++f) gd[f][d] = acc[f] - lh.x * v[f];
         __builtin_amdgcn_sched_barrier(0);
     }
 }
 
 // Curved elements: the same BR1 lifting in the conservative form with the
 // metrics inside the derivative, J q_m = sum_d sum_l Dhat (Ja^d_m w)_l +
-// sum_faces lhat w* (n dS)_m, for NFLD consecutive LDS fields; sJa holds
-// Ja^d_m (row 3d+m) at every node of the tile, sN the outward n dS at every
-// face point.  Returns the physical gradients times 1/J (iJ of this node).
-template <int P, int NFLD, int NVS, int NFS, typename T, typename B_>
-__device__ __forceinline__ void lifted_grads_curved(const T (*fw)[NVS], const T (*fs)[NFS], const T (*sJa)[NVS],
+// sum_faces lhat w* (n dS)_m, for NFLD fields; node(n, v) and face(n, v) give
+// the fields at a tile node and a face point; sJ and sJz hold Ja^d (pair and
+// third component, row d) at every node of the tile, sN the outward n dS at
+// every face point.  Returns the physical gradients times 1/J (iJ of this node).
+template <int P, int NFLD, int NVS, int NFS, typename T, typename FN, typename FS>
+__device__ __forceinline__ void lifted_grads_curved(FN node, FS face, const V2<T> (*sJ)[NVS], const T (*sJz)[NVS],
                                                     const T (*sN)[NFS], int base, int fbase, int i, int j, int k,
-                                                    const B_ *sDh, const B_ *sLh, T iJ, T q[NFLD][3])
+                                                    const BasisS<P, T> &B, T iJ, T q[NFLD][3])
 {
     constexpr int n2 = P * P;
     const int idx[3] = {i, j, k};
@@ -706,28 +794,34 @@ __device__ __forceinline__ void lifted_grads_curved(const T (*fw)[NVS], const T 
     for (int f = 0; f < NFLD; ++f) q[f][0] = q[f][1] = q[f][2] = T(0);
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        const int id = idx[d];
         const int p = d == 0 ? j : i, r = d == 2 ? j : k;
+        T D[P], v[NFLD];
+        B.row(B.Dh + idx[d] * B.PS, D);
 #pragma unroll
         for (int l = 0; l < P; ++l) {
             const int n = base + line_node<P>(d, l, p, r);
-            const T D = T(sDh[id * P + l]);
-            const T a0 = D * sJa[3 * d][n], a1 = D * sJa[3 * d + 1][n], a2 = D * sJa[3 * d + 2][n];
+            const V2<T> jj = sJ[d][n];
+            const T a0 = D[l] * jj.x, a1 = D[l] * jj.y, a2 = D[l] * sJz[d][n];
+            node(n, v);
 #pragma unroll
             for (int f = 0; f < NFLD; ++f) {
-                const T v = fw[f][n];
-                q[f][0] += a0 * v;
-                q[f][1] += a1 * v;
-                q[f][2] += a2 * v;
+                q[f][0] += a0 * v[f];
+                q[f][1] += a1 * v[f];
+                q[f][2] += a2 * v[f];
             }
         }
-        const int pp = fbase + (2 * d + 1) * n2 + fpd[d], pm = fbase + (2 * d) * n2 + fpd[d];
-        const T lp = T(sLh[P + id]), lm = T(sLh[id]);
+        const V2<T> lh = B.Lh[idx[d]];
 #pragma unroll
-        for (int m = 0; m < 3; ++m) {
-            const T np_ = lp * sN[m][pp], nm_ = lm * sN[m][pm];
+        for (int sd = 0; sd < 2; ++sd) {
+            const int pt = fbase + (2 * d + 1 - sd) * n2 + fpd[d];
+            const T lw = sd ? lh.x : lh.y;
+            face(pt, v);
 #pragma unroll
-            for (int f = 0; f < NFLD; ++f) q[f][m] += np_ * fs[f][pp] + nm_ * fs[f][pm];
+            for (int m = 0; m < 3; ++m) {
+                const T nl = lw * sN[m][pt];
+#pragma unroll
+                for (int f = 0; f < NFLD; ++f) q[f][m] += nl * v[f];
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -737,14 +831,19 @@ __device__ __forceinline__ void lifted_grads_curved(const T (*fw)[NVS], const T 
         for (int m = 0; m < 3; ++m) q[f][m] *= iJ;
 }
 
-// Per-node metrics of a curved element tile into LDS (nine Ja rows) and
-// this node's 1/J; t is the node's thread, g its global node index.
+// Per-node metrics of a curved element tile into LDS (Ja^d as a pair and the
+// third component) and this node's 1/J; q is the node's place in the tile, g
+// its global node index.
 template <typename T, int NVS>
-__device__ __forceinline__ T stage_node_metrics(const MeshDev &m, size_t NN, size_t g, int t, T (*sJa)[NVS])
+__device__ __forceinline__ T stage_node_metrics(const MeshDev &m, size_t NN, size_t g, int q, V2<T> (*sJ)[NVS],
+                                                T (*sJz)[NVS])
 {
     const T *nm = (const T *)m.nmet;
 #pragma unroll
-    for (int r = 0; r < 9; ++r) sJa[r][t] = gld(nm + r * NN, (uint32_t)g);
+    for (int d = 0; d < 3; ++d) {
+        sJ[d][q] = V2<T>{gld(nm + (3 * d) * NN, (uint32_t)g), gld(nm + (3 * d + 1) * NN, (uint32_t)g)};
+        sJz[d][q] = gld(nm + (3 * d + 2) * NN, (uint32_t)g);
+    }
     return T(1) / gld(nm + 9 * NN, (uint32_t)g);
 }
 
@@ -754,24 +853,11 @@ template <typename T> __device__ __forceinline__ void to_physical(const T Ja[9],
     for (int m = 0; m < 3; ++m) q[m] = iJ * (Ja[m] * gd[0] + Ja[3 + m] * gd[1] + Ja[6 + m] * gd[2]);
 }
 
-// The element whose per-element data (metrics, face normals) a node thread
-// reads, as a wave-uniform index where it is one: with one element per
-// workgroup it is the workgroup's, and with 64 nodes per element (N = 3)
-// each wave holds exactly one element.  Those loads then become scalar
-// loads into scalar registers, issued at once and costing no vector
-// registers; otherwise the index is the thread's own.
-template <int EPB, int N3> __device__ __forceinline__ int metric_element(int e0, int e)
-{
-    if constexpr (EPB == 1) return e0;
-    if constexpr (N3 == 64) return __builtin_amdgcn_readfirstlane(e);
-    return e;
-}
-
-template <typename T> __device__ __forceinline__ void element_metrics(const MeshDev &m, int e, T Ja[9], T &iJ)
+template <bool UNI, typename T> __device__ __forceinline__ void element_metrics(const MeshDev &m, int e, T Ja[9], T &iJ)
 {
 #pragma unroll
-    for (int r = 0; r < 9; ++r) Ja[r] = T(gld(m.emet, (uint32_t)e * 10 + r));
-    iJ = T(1.0 / gld(m.emet, (uint32_t)e * 10 + 9));
+    for (int r = 0; r < 9; ++r) Ja[r] = em_at<UNI, T>(m, e, kEmJa + r);
+    iJ = em_at<UNI, T>(m, e, kEmIJ);
 }
 
 // ------------------------------------------------------------ k_prolong
@@ -782,17 +868,17 @@ __global__ __launch_bounds__(BS) void k_prolong(Launch<T> L)
     using G = Tile<P, BS>;
     Inst<T> a;
     int e0;
-    instance_of<T, BATCH>(L, a, e0, G::EPB);
-    __shared__ T sU[6][G::NV];
-    __shared__ T sDh[P * P], sL[2 * P], sLh[2 * P];
-    load_basis<P>(L.bas, sDh, sL, sLh);
+    instance_of<T, BATCH>(L, a, e0, G::EPB, blockIdx.x);
+    __shared__ V2<T> sU[3][G::NV];
+    __shared__ BasisS<P, T> B;
+    B.load(L.bas);
     const int E = a.mesh.E;
     const int t = threadIdx.x;
-    if (t < G::NV && e0 + t / G::n3 < E) {
-        const size_t g = (size_t)e0 * G::n3 + t;
-    const uint32_t g32 = (uint32_t)g;
+    const NodeTask<G> nt(t);
+    if (nt.in && e0 + nt.le < E) {
+        const uint32_t g32 = (uint32_t)e0 * G::n3 + nt.q;
 #pragma unroll
-        for (int v = 0; v < 6; ++v) sU[v][t] = gld(a.U + (v) * a.NN, g32);
+        for (int v = 0; v < 3; ++v) sU[v][nt.q] = V2<T>{gld(a.U + (2 * v) * a.NN, g32), gld(a.U + (2 * v + 1) * a.NN, g32)};
     }
     __syncthreads();
     const size_t NF = (size_t)E * 6 * G::n2;
@@ -804,7 +890,7 @@ __global__ __launch_bounds__(BS) void k_prolong(Launch<T> L)
         const int base = lt.le * G::n3;
         T um[6], up[6];
 #pragma unroll
-        for (int v = 0; v < 6; ++v) prolong2<P>(sU[v], base, sL, lt, um[v], up[v]);
+        for (int v = 0; v < 3; ++v) prolong2<P, T>(sU[v], base, B, lt, um + 2 * v, up + 2 * v);
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             const FaceIx<G::n2> o((size_t)e * 6 + 2 * lt.d + s, lt.fp);
@@ -836,26 +922,30 @@ __global__ __launch_bounds__(BS, (lift1_waves<P, T, BS, FULL, CV>())) void k_lif
     using G = Tile<P, BS>;
     Inst<T> a;
     int e0;
-    instance_of<T, BATCH>(L, a, e0, G::EPB);
+    instance_of<T, BATCH>(L, a, e0, G::EPB, blockIdx.x);
     static_assert(n_lines<P, BS>() <= BS, "one line per thread");
-    // node values of the lifted primitives (c last; slots 0..2 later hold
-    // grad c) and their BR1 face values: all five with FULL, else c only
-    constexpr int NW = FULL ? 5 : 4, NS = FULL ? 5 : 1;
+    // state (c only, or with FULL all of it) and primitives (FULL), BR1 face
+    // values of c or of all primitives
+    constexpr int NU = FULL ? 6 : 1, NS = FULL ? 5 : 1, kC = NU - 1;
     // curved elements: the metrics of every node and n dS of every face point
-    constexpr int NJ = CV ? 9 : 1, NQ = CV ? 3 : 1, NJV = CV ? G::NV : 1, NQF = CV ? G::NF : 1;
-    __shared__ T sU[6][G::NV];
-    __shared__ T sW[NW][G::NV];
+    constexpr int NJ = CV ? 3 : 1, NQ = CV ? 3 : 1, NJV = CV ? G::NV : 1, NQF = CV ? G::NF : 1;
+    __shared__ T sU[NU][G::NV];
+    __shared__ T sW[FULL ? 5 : 1][FULL ? G::NV : 1];
     __shared__ T sS[NS][G::NF];
-    __shared__ T sJa[NJ][NJV];
+    __shared__ V2<T> sG[G::NV];    // grad c
+    __shared__ T sGz[G::NV];
+    __shared__ V2<T> sJ[NJ][NJV];
+    __shared__ T sJz[NJ][NJV];
     __shared__ T sN[NQ][NQF];
-    __shared__ T sDh[P * P], sL[2 * P], sLh[2 * P];
-    load_basis<P>(L.bas, sDh, sL, sLh);
+    __shared__ BasisS<P, T> B;
+    B.load(L.bas);
     const int E = a.mesh.E;
     const int t = threadIdx.x;
-    const int le = t / G::n3, nd = t - le * G::n3;
+    const NodeTask<G> nt(t);
+    const int le = nt.le, nd = nt.nd, tq = nt.q;
     const int e = e0 + le;
-    const bool act = t < G::NV && e < E;
-    const size_t g = (size_t)e0 * G::n3 + t;
+    const bool act = nt.in && e < E;
+    const size_t g = (size_t)e0 * G::n3 + tq;
     const uint32_t g32 = (uint32_t)g;
     const size_t NF = (size_t)E * 6 * G::n2;
     constexpr bool full = FULL;
@@ -888,27 +978,28 @@ __global__ __launch_bounds__(BS, (lift1_waves<P, T, BS, FULL, CV>())) void k_lif
     }
     T iJn = T(0);
     if (act) {
-        T u6[6], w[5];
+        if constexpr (FULL) {
+            T u6[6], w[5];
 #pragma unroll
-        for (int v = 0; v < 6; ++v) { u6[v] = gld(a.U + (v) * a.NN, g32); sU[v][t] = u6[v]; }
-        primitives(u6, w);
-        if (full) {
+            for (int v = 0; v < 6; ++v) { u6[v] = gld(a.U + (v) * a.NN, g32); sU[v][tq] = u6[v]; }
+            primitives(u6, w);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) sW[k][t] = w[k];
+            for (int k = 0; k < 5; ++k) sW[k][tq] = w[k];
+        } else {
+            sU[kC][tq] = gld(a.U + 5 * a.NN, g32);
         }
-        sW[NW - 1][t] = w[4];
-        if constexpr (CV) iJn = stage_node_metrics<T, NJV>(a.mesh, a.NN, g, t, sJa);
+        if constexpr (CV) iJn = stage_node_metrics<T, NJV>(a.mesh, a.NN, g, tq, sJ, sJz);
     }
     __syncthreads();
     // BR1 face values w* on both faces of the line
     if (lact) {
         const int base = lt.le * G::n3;
         T uf[2][6];
-        if (full) {
+        if constexpr (FULL) {
 #pragma unroll
-            for (int v = 0; v < 6; ++v) prolong2<P>(sU[v], base, sL, lt, uf[0][v], uf[1][v]);
+            for (int v = 0; v < 6; ++v) prolong2<P, T>(sU[v], base, B, lt, uf[0][v], uf[1][v]);
         } else {
-            prolong2<P>(sU[5], base, sL, lt, uf[0][5], uf[1][5]);
+            prolong2<P, T>(sU[kC], base, B, lt, uf[0][5], uf[1][5]);
         }
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
@@ -947,61 +1038,58 @@ __global__ __launch_bounds__(BS, (lift1_waves<P, T, BS, FULL, CV>())) void k_lif
         const int i = nd % P, j = (nd / P) % P, k = nd / (P * P);
         const int base = le * G::n3, fbase = le * 6 * G::n2;
         if constexpr (CV) {
-            if (full) {
-                T q[5][3];
-                lifted_grads_curved<P, 5, G::NV, G::NF>(sW, sS, sJa, sN, base, fbase, i, j, k, sDh, sLh, iJn, q);
+            constexpr int NG = FULL ? 5 : 1;
+            auto node = [&](int n, T v[NG]) {
+#pragma unroll
+                for (int f = 0; f < NG; ++f) v[f] = FULL ? sW[f][FULL ? n : 0] : sU[kC][n];
+            };
+            auto face = [&](int n, T v[NG]) {
+#pragma unroll
+                for (int f = 0; f < NG; ++f) v[f] = sS[f][n];
+            };
+            T q[NG][3];
+            lifted_grads_curved<P, NG, G::NV, G::NF>(node, face, sJ, sJz, sN, base, fbase, i, j, k, B, iJn, q);
+            if constexpr (FULL) {
 #pragma unroll
                 for (int w = 0; w < 4; ++w)
 #pragma unroll
                     for (int m = 0; m < 3; ++m) gst(a.Q + ((3 * w + m)) * a.NN, g32, T(q[w][m]));
-                qc[0] = q[4][0];
-                qc[1] = q[4][1];
-                qc[2] = q[4][2];
-            } else {
-                T q[1][3];
-                lifted_grads_curved<P, 1, G::NV, G::NF>(sW + (NW - 1), sS + (NS - 1), sJa, sN, base, fbase, i, j, k,
-                                                        sDh, sLh, iJn, q);
-                qc[0] = q[0][0];
-                qc[1] = q[0][1];
-                qc[2] = q[0][2];
             }
+#pragma unroll
+            for (int m = 0; m < 3; ++m) qc[m] = q[NG - 1][m];
         } else {
             T Ja[9], iJ;
-            // (FP32: the scalar loads cost the one vector register that keeps 8 waves per SIMD)
-            element_metrics(a.mesh, sizeof(T) == 8 ? metric_element<G::EPB, G::n3>(e0, e) : e, Ja, iJ);
+            element_metrics<G::kUni>(a.mesh, e, Ja, iJ);
             if (full) {
 #pragma unroll
                 for (int w = 0; w < 4; ++w) {
                     T q[3];
-                    lifted_grad<P>(sW[w], sS[w], base, fbase, i, j, k, sDh, sLh, Ja, iJ, q);
+                    lifted_grad<P, T>(sW[w], sS[w], base, fbase, i, j, k, B, Ja, iJ, q);
 #pragma unroll
                     for (int m = 0; m < 3; ++m) gst(a.Q + ((3 * w + m)) * a.NN, g32, T(q[m]));
                 }
             }
-            lifted_grad<P>(sW[NW - 1], sS[NS - 1], base, fbase, i, j, k, sDh, sLh, Ja, iJ, qc);
+            lifted_grad<P, T>(sU[kC], sS[NS - 1], base, fbase, i, j, k, B, Ja, iJ, qc);
         }
-        if (full) {
+        if constexpr (FULL) {
 #pragma unroll
             for (int m = 0; m < 3; ++m) gst(a.Q + ((12 + m)) * a.NN, g32, T(qc[m]));
-            const double Tn = temperature<fast_fp64<T>()>(a.ph, (double)sU[0][t], (double)sU[1][t], (double)sU[2][t], (double)sU[3][t],
-                                          (double)sU[4][t], (double)sU[5][t], (double)qc[0], (double)qc[1],
+            const double Tn = temperature<fast_fp64<T>()>(a.ph, (double)sU[0][tq], (double)sU[1][tq], (double)sU[2][tq], (double)sU[3][tq],
+                                          (double)sU[4][tq], (double)sU[5][tq], (double)qc[0], (double)qc[1],
                                           (double)qc[2]);
             gst(a.TH, g32, T(Tn));
         }
     }
-    __syncthreads();
-    // reuse sW[0..2] for grad c to prolong it to the faces
     if (act) {
-        sW[0][t] = qc[0];
-        sW[1][t] = qc[1];
-        sW[2][t] = qc[2];
+        sG[tq] = V2<T>{qc[0], qc[1]};
+        sGz[tq] = qc[2];
     }
     __syncthreads();
     if (lact) {
         const int base = lt.le * G::n3;
-        T qf[2][3], uf[2][6];
-#pragma unroll
-        for (int m = 0; m < 3; ++m) prolong2<P>(sW[m], base, sL, lt, qf[0][m], qf[1][m]);
+        T qf[2][3];
+        prolong2<P, T>(sG, base, B, lt, qf[0], qf[1]);
+        prolong2<P, T>(sGz, base, B, lt, qf[0][2], qf[1][2]);
         // outward normal of each face of this line: on affine elements the -
         // face's is the exact negative of the + face's, as the mesh upload
         // forms them
@@ -1013,26 +1101,20 @@ __global__ __launch_bounds__(BS, (lift1_waves<P, T, BS, FULL, CV>())) void k_lif
                 face_normal<P, T, true>(a.mesh, (size_t)el * 6 + 2 * lt.d + s, lt.fp, nf[s], dS);
             }
         } else {
-            const uint32_t fq = ((uint32_t)el * 6 + 2 * lt.d + 1) * 4;
+            T dS;
+            face_normal<P, T, false>(a.mesh, (size_t)el * 6 + 2 * lt.d + 1, lt.fp, nf[1], dS);
 #pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                nf[1][m] = T(gld(a.mesh.fmet, fq + m));
-                nf[0][m] = -nf[1][m];
-            }
+            for (int m = 0; m < 3; ++m) nf[0][m] = -nf[1][m];
         }
 #pragma unroll
-        for (int v = 0; v < 6; ++v) prolong2<P>(sU[v], base, sL, lt, uf[0][v], uf[1][v]);
-#pragma unroll
         for (int s = 0; s < 2; ++s) {
-            const double Tf = temperature<fast_fp64<T>()>(a.ph, (double)uf[s][0], (double)uf[s][1], (double)uf[s][2], (double)uf[s][3],
-                                          (double)uf[s][4], (double)uf[s][5], (double)qf[s][0], (double)qf[s][1],
-                                          (double)qf[s][2]);
             const FaceIx<G::n2> o((size_t)el * 6 + 2 * lt.d + s, lt.fp);
-            const T gn = qf[s][0] * nf[s][0] + qf[s][1] * nf[s][1] + qf[s][2] * nf[s][2];
-            a.T2[o.at(kT2<T>(), 0)] = gn;
-            const T Th = T(Tf);
-            a.T2[o.at(kT2<T>(), 1)] = Th;
-            if constexpr (sizeof(T) == 4) a.T2[o.at(kT2<T>(), 2)] = T(Tf - (double)Th);
+            a.T2[o.at(kT2<T>(), 0)] = qf[s][0] * nf[s][0] + qf[s][1] * nf[s][1] + qf[s][2] * nf[s][2];
+            const double q0 = (double)qf[s][0], q1 = (double)qf[s][1], q2 = (double)qf[s][2];
+            const double g2 = q0 * q0 + q1 * q1 + q2 * q2;
+            const T gh = T(g2);
+            a.T2[o.at(kT2<T>(), 1)] = gh;
+            if constexpr (sizeof(T) == 4) a.T2[o.at(kT2<T>(), 2)] = T(g2 - (double)gh);
         }
         // wall faces also keep the vector grad c (Navier-slip traction), in
         // a loop of its own: inside the one above the branch costs ~40 VGPRs
@@ -1048,34 +1130,78 @@ __global__ __launch_bounds__(BS, (lift1_waves<P, T, BS, FULL, CV>())) void k_lif
 }
 
 // ------------------------------------------------------------ k_lift2
-template <int P, typename T, int BS, bool BATCH, bool CV = false>
-__global__ __launch_bounds__(BS) void k_lift2(Launch<T> L)
+// Tile of k_lift2: its own, since its workgroups are bound by the registers
+// and the LDS of the node phases and by the rounds of the face phases, not by
+// what the streaming kernels of the stage like.  One element per workgroup at
+// N = 4 and 5, two at N = 3, three at N = 2 (where the stage's tile is a
+// multiple of it), and as many threads as the face points need, in whole
+// waves, so that the face phases take one round: the second round of a few
+// face points cost a workgroup the latency of a whole one.
+template <int P, int BS> struct Lift2Tile {
+    static constexpr int kTile = Tile<P, BS>::EPB;
+    static constexpr int kBest = P >= 5 ? 1 : (P == 4 ? 2 : 3);
+    static constexpr int EPB = kTile % kBest == 0 ? kBest : kTile;
+    static constexpr int kSub = kTile / EPB;  // workgroups per tile
+    static constexpr int kMost = EPB * 6 * P * P > EPB * P * P * P ? EPB * 6 * P * P : EPB * P * P * P;
+    static constexpr int NT = (kMost + 63) / 64 * 64;
+    using G = Tile<P, NT, EPB>;
+    // workgroups for `tiles` tiles: the tiles of each XCD (tile mod 8, as the
+    // hardware deals out workgroups) keep their XCD
+    static int grid(int tiles) { return kSub == 1 ? tiles : (tiles + 7) / 8 * 8 * kSub; }
+};
+
+// FP64 instances on affine elements keep 4 waves per SIMD (128 registers)
+// where their LDS lets them.
+template <int P, typename T, bool CV> constexpr int lift2_waves() { return sizeof(T) == 8 && !CV && P > 3 ? 4 : 1; }
+
+template <int P, typename T, int BS, bool BATCH, bool CV = false, bool WALL = true>
+__global__ __launch_bounds__((Lift2Tile<P, BS>::NT), (lift2_waves<P, T, CV>())) void k_lift2(Launch<T> L, int tiles)
 {
-    using G = Tile<P, BS>;
+    using Q = Lift2Tile<P, BS>;
+    using G = typename Q::G;
+    constexpr int NT = Q::NT;
+    const int tile = Q::kSub == 1 ? blockIdx.x : blockIdx.x / (8 * Q::kSub) * 8 + blockIdx.x % 8;
+    if (tile >= tiles) return;
     Inst<T> a;
     int e0;
-    instance_of<T, BATCH>(L, a, e0, G::EPB);
-    // sX holds the primitives u, v, w, c [4][NV] and their BR1 face values
-    // [4][NF] while grad u and grad c are lifted, then grad u [9][NV]
-    constexpr int kX = 9 * G::NV > 4 * G::NV + 4 * G::NF ? 9 * G::NV : 4 * G::NV + 4 * G::NF;
+    instance_of<T, BATCH>(L, a, e0, Q::kTile, tile);
+    if (Q::kSub > 1) e0 += blockIdx.x / 8 % Q::kSub * Q::EPB;
+    // LDS, in rows of pairs of NV nodes: the primitives (rho, u), (v, w) and c
+    // and their BR1 face values while they are lifted; then
+    //   rows 0..2  (tau . n_d)_0, (tau . n_d)_1 of direction d
+    //   rows 3..5  (tau . n_d)_2, div u
+    //   rows 6..8  T, contravariant grad c_d; then grad T . n_d, lap c
+    // so that a face task reads three pairs; and the contravariant fluxes of
+    // the volume integral over rows 6..8 (directions 0 and 2) and rows 0, 3, 1
+    // (direction 1, whose values every thread has read by then).
+    // Curved elements, whose normal varies along a face: rows 0..4 grad u,
+    // rows 5..7 T, contravariant grad c_d, then 5, 6 grad T, lap c; fluxes
+    // over rows 5..7 and rows 8..10.
+    constexpr int kRows = CV ? 11 : 9, kT = CV ? 5 : 6;
+    constexpr int kLift = 5 * G::NV + 5 * G::NF;
+    constexpr int kX0 = (kLift + 1) / 2 + 2 * G::NV;                  // pairs, with the state beside them
+    constexpr int kX = kRows * G::NV > kX0 ? kRows * G::NV : kX0;
     // curved elements: the metrics of every node and n dS of every face point
-    constexpr int NJ = CV ? 9 : 1, NQ = CV ? 3 : 1, NJV = CV ? G::NV : 1, NQF = CV ? G::NF : 1;
-    __shared__ T sA[4][G::NV];     // T, grad c (curved: its contravariant components); then grad T, lap c
-    __shared__ T sX[kX];
-    __shared__ T sTs[G::NF], sFs[G::NF];
-    __shared__ T sJa[NJ][NJV];
+    constexpr int NJ = CV ? 3 : 1, NQ = CV ? 3 : 1, NJV = CV ? G::NV : 1, NQF = CV ? G::NF : 1;
+    __shared__ V2<T> sX[kX];
+    __shared__ V2<T> sTF[G::NF];   // T*, (grad c)* . n dS
+    __shared__ V2<T> sJ[NJ][NJV];
+    __shared__ T sJz[NJ][NJV];
     __shared__ T sN[NQ][NQF];
-    __shared__ T sDh[P * P], sL[2 * P], sLh[2 * P];
-    T(*sW)[G::NV] = reinterpret_cast<T(*)[G::NV]>(sX);
-    T(*sS)[G::NF] = reinterpret_cast<T(*)[G::NF]>(sX + 4 * G::NV);
-    T(*sGu)[G::NV] = reinterpret_cast<T(*)[G::NV]>(sX);
-    load_basis<P>(L.bas, sDh, sL, sLh);
+    __shared__ BasisS<P, T> B;
+    V2<T>(*sR)[G::NV] = reinterpret_cast<V2<T>(*)[G::NV]>(sX);
+    V2<T> *sSa = sX + 2 * G::NV, *sSb = sSa + G::NF;
+    T *sWc = reinterpret_cast<T *>(sSb + G::NF), *sSc = sWc + G::NV;
+    V2<T> *sM = sX + kX - 2 * G::NV;  // (m_x, m_y), (m_z, rho e)
+    const Five<T> fw{sX, sX + G::NV, sWc}, fs{sSa, sSb, sSc};
+    B.load(L.bas);
     const int E = a.mesh.E;
     const int t = threadIdx.x;
-    const int le = t / G::n3, nd = t - le * G::n3;
+    const NodeTask<G> nt(t);
+    const int le = nt.le, nd = nt.nd, tq = nt.q;
     const int e = e0 + le;
-    const bool act = t < G::NV && e < E;
-    const size_t g = (size_t)e0 * G::n3 + t;
+    const bool act = nt.in && e < E;
+    const size_t g = (size_t)e0 * G::n3 + tq;
     const uint32_t g32 = (uint32_t)g;
     const size_t NF = (size_t)E * 6 * G::n2;
     const T *TU = a.TU + (size_t)L.tb * 6 * NF;
@@ -1083,25 +1209,20 @@ __global__ __launch_bounds__(BS) void k_lift2(Launch<T> L)
     // face work runs as face tasks (one face point per thread, a second round
     // where the block has more face points than threads); the first round's
     // traces are loaded before the node loads: both sides' conserved state
-    // (rho, m, c; the own side's is the prolongation of the state, written by
-    // the previous stage) and both sides' grad c and T
-    // The own side's traces of the first round's face point (the whole
-    // conserved state and (grad c) . n, T; in FP32 also T's rounding error)
-    // stay in registers from this load to the flux pass at the end, instead
-    // of being read again from memory there, where they mostly miss the L2
-    // (where the block has more face points than threads, the second
-    // round's are read again).  FP32 instances keep them only where one
-    // round covers the block: with two rounds the registers cost a wave per
-    // SIMD, which measured slower than the re-read.
-    constexpr bool kKeep = sizeof(T) == 8 || G::NF <= BS;
+    // (the own side's is the prolongation of the state, written by the
+    // previous stage), (grad c) . n and |grad c|^2
+    // Of the first round's face point, the convective part of the flux and
+    // the face values that its viscous part needs stay in registers until
+    // that part is known; the second round's wait in the flux trace and are
+    // formed again from the own trace.
+    constexpr bool kKeep = G::NF <= NT;
     // FP64, where one round covers the block: the face point's normal and
-    // surface element are loaded with its traces too (their loads otherwise
-    // stall both face phases; in FP32 the registers would cost a wave per
-    // SIMD)
-    constexpr bool kOne = G::NF <= BS && sizeof(T) == 8;
+    // surface element are loaded with its traces too (in FP32 the registers
+    // would cost a wave per SIMD)
+    constexpr bool kOne = G::NF <= NT && sizeof(T) == 8;
     struct Tr {
         int nb;
-        T own[3], oth[2], wn[6], uo[6];
+        T own[3], oth[3], wn[6], uo[6];
         T n[3], dS;
     };
     auto load_tr = [&](int task, Tr &r) {
@@ -1111,24 +1232,38 @@ __global__ __launch_bounds__(BS) void k_lift2(Launch<T> L)
         if (el >= E) return;
         const FaceIx<G::n2> o((size_t)el * 6 + ft.f, ft.fp);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) r.own[k] = a.T2[o.at(kT2<T>(), k)];
-        if constexpr (kKeep && sizeof(T) == 4) r.own[2] = a.T2[o.at(kT2<T>(), 2)];
+        for (int k = 0; k < kT2gc<T>(); ++k) r.own[k] = a.T2[o.at(kT2<T>(), k)];
 #pragma unroll
-        for (int v = 0; v < 6; ++v)
-            if (v != 4 || kKeep) r.uo[v] = TU[o.at(6, v)];
+        for (int v = 0; v < 6; ++v) r.uo[v] = TU[o.at(6, v)];
         r.nb = gld(a.mesh.nbr, el * 6 + ft.f);
         if constexpr (kOne) face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + ft.f, ft.fp, r.n, r.dS);
-        if (r.nb >= 0) {
+        if (!WALL || r.nb >= 0) {
             const FaceIx<G::n2> on(nbr_face<P>(r.nb), nbr_point<P>(r.nb, ft.fp));
 #pragma unroll
-            for (int k = 0; k < 2; ++k) r.oth[k] = a.T2[on.at(kT2<T>(), k)];
+            for (int k = 0; k < kT2gc<T>(); ++k) r.oth[k] = a.T2[on.at(kT2<T>(), k)];
 #pragma unroll
-            for (int v = 0; v < 6; ++v)
-                if (v != 4) r.wn[v] = TU[on.at(6, v)];
+            for (int v = 0; v < 6; ++v) r.wn[v] = TU[on.at(6, v)];
         }
     };
-    Tr tr0;
-    if (t < G::NF) load_tr(t, tr0);
+    // face temperature from a conserved trace and |grad c|^2 (FP32: value and
+    // rounding error; always FP64 arithmetic)
+    auto face_T = [&](const T u[6], const T q[3]) {
+        double g2 = (double)q[1];
+        if constexpr (sizeof(T) == 4) g2 += (double)q[2];
+        return temperature_g2<fast_fp64<T>()>(a.ph, (double)u[0], (double)u[1], (double)u[2], (double)u[3],
+                                              (double)u[4], (double)u[5], g2);
+    };
+    // pressure (p_alpha for model 2) and sound speed of the convective flux
+    auto face_eos = [&](T rho, double Tf, T &p, T &cw) {
+        double pd, cs2;
+        eos<fast_fp64<T>()>(a.ph, (double)rho, Tf, pd, cs2);
+        p = T(pd + 0.5 * a.ph.ap * (double)rho * (double)rho);
+        cw = sqrt_to<T>(fabs(cs2 + a.ph.ap * (double)rho));
+    };
+    Tr tr;
+    if (t < G::NF) load_tr(t, tr);
+    // the state waits in LDS (rho and c among the primitives) while the face
+    // values are formed, where its registers are needed
     T un[6];
     T iJn = T(0);
     if (act) {
@@ -1136,46 +1271,90 @@ __global__ __launch_bounds__(BS) void k_lift2(Launch<T> L)
 #pragma unroll
         for (int v = 0; v < 6; ++v) un[v] = gld(a.U + (v) * a.NN, g32);
         primitives(un, w);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) sW[k][t] = w[1 + k];
-        if constexpr (CV) iJn = stage_node_metrics<T, NJV>(a.mesh, a.NN, g, t, sJa);
+        sM[tq] = V2<T>{un[1], un[2]};
+        sM[G::NV + tq] = V2<T>{un[3], un[4]};
+        sR[0][tq] = V2<T>{w[0], w[1]};
+        sR[1][tq] = V2<T>{w[2], w[3]};
+        sWc[tq] = w[4];
+        if constexpr (CV) iJn = stage_node_metrics<T, NJV>(a.mesh, a.NN, g, tq, sJ, sJz);
     }
-    __syncthreads();
-    // face values: BR1 w* of u, v, w, c; T* and (grad c)* . n dS of the second lifting
-    for (int task = t; task < G::NF; task += BS) {
+    // what the flux pass needs of the first round's face point
+    T Kc[6], fu[3], fc = T(0), frc = T(0), fgn = T(0), fdS = T(0);
+    bool fwall = true;
+    // face values: BR1 w* of the primitives; T* and (grad c)* . n dS of the
+    // second lifting; and on interior faces the convective part of the flux:
+    // the own side's flux with half of the Rusanov dissipation, F^C(u) . n +
+    // lam/2 (u - u_nbr), so that half the difference of the two sides' values
+    // (each with its own normal) is the central flux plus the dissipation
+    // (model 2: the HLLC flux, of which half the difference is itself)
+    for (int task = t; task < G::NF; task += NT) {
         const FaceTask<P> ft(task);
         const int el = e0 + ft.le, f = ft.f;
-        if (el >= E) continue;
-        Tr tr;
-        if (task == t) tr = tr0; else load_tr(task, tr);
-        // the surface element always; the normal where it is used (walls,
-        // and the lifting's n dS on curved elements)
-        T n[3] = {T(0), T(0), T(0)}, dS;
+        if (el >= E) break;
+        T n[3], dS;
         if constexpr (kOne) {
             n[0] = tr.n[0];
             n[1] = tr.n[1];
             n[2] = tr.n[2];
             dS = tr.dS;
-        } else if (CV || tr.nb < 0) {
-            face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp, n, dS);
         } else {
-            dS = face_dS<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp);
+            face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp, n, dS);
         }
+        const int slot = ft.le * 6 * G::n2 + f * G::n2 + ft.fp;
         const T *uf = tr.uo;
         T w[5];
         primitives(uf, w);
+        const double To = face_T(uf, tr.own);
         T Ts, Fs;
-        if (tr.nb >= 0) {
+        if (!WALL || tr.nb >= 0) {
             T v5[5];
             primitives(tr.wn, v5);
+            T po, co, pn, cn;
+            face_eos(uf[0], To, po, co);
+            __builtin_amdgcn_sched_barrier(0);  // one side after the other: registers
+            const double Tn = face_T(tr.wn, tr.oth);
+            face_eos(tr.wn[0], Tn, pn, cn);
+            __builtin_amdgcn_sched_barrier(0);
+            T K[6];
+            if (a.ph.model == 2) {
+                hllc(uf, po, co, tr.wn, pn, cn, n, K);
+            } else {
+                const T mn = uf[1] * n[0] + uf[2] * n[1] + uf[3] * n[2];
+                const T mo = tr.wn[1] * n[0] + tr.wn[2] * n[1] + tr.wn[3] * n[2];
+                const T ir = T(1) / uf[0], vn = mn * ir;
+                const T lo = fabs(vn) + co, ln = fabs(mo * (T(1) / tr.wn[0])) + cn;
+                const T hl = T(0.5) * (lo > ln ? lo : ln);
+                K[0] = mn + hl * (uf[0] - tr.wn[0]);
+                K[1] = uf[1] * vn + po * n[0] + hl * (uf[1] - tr.wn[1]);
+                K[2] = uf[2] * vn + po * n[1] + hl * (uf[2] - tr.wn[2]);
+                K[3] = uf[3] * vn + po * n[2] + hl * (uf[3] - tr.wn[3]);
+                K[4] = (uf[4] + po) * vn + hl * (uf[4] - tr.wn[4]);
+                K[5] = uf[5] * vn + hl * (uf[5] - tr.wn[5]);
+            }
+            if (kKeep && task == t) {
 #pragma unroll
-            for (int k = 1; k < 5; ++k) w[k] = T(0.5) * (w[k] + v5[k]);
-            Ts = T(0.5) * (tr.own[1] + tr.oth[1]);
+                for (int v = 0; v < 6; ++v) Kc[v] = K[v];
+                fu[0] = w[1];
+                fu[1] = w[2];
+                fu[2] = w[3];
+                fc = uf[5];
+                frc = uf[0] - uf[5];
+                fgn = tr.own[0];
+                fdS = dS;
+                fwall = false;
+            } else {
+                const FaceIx<G::n2> o((size_t)el * 6 + f, ft.fp);
+#pragma unroll
+                for (int v = 0; v < 6; ++v) a.TF[o.at(6, v)] = K[v];
+            }
+#pragma unroll
+            for (int k = 0; k < 5; ++k) w[k] = T(0.5) * (w[k] + v5[k]);
+            Ts = T(0.5 * (To + Tn));
             Fs = T(0.5) * (tr.own[0] - tr.oth[0]) * dS;
         } else {
             wall_primitives(a.mesh, el, f, n, w);
             const BcDev &bc = a.mesh.bcs[a.mesh.bcid[el * 6 + f] - 1];
-            Ts = bc.iso ? T(bc.twall) : tr.own[1];
+            Ts = bc.iso ? T(bc.twall) : T(To);
             if (bc.kind != 2) {
                 // static part of the contact-angle flux (a varying wall
                 // temperature is applied in the pass below; the dynamic part,
@@ -1186,23 +1365,23 @@ __global__ __launch_bounds__(BS) void k_lift2(Launch<T> L)
                 Fs = T(0);
             }
         }
-        const int slot = ft.le * 6 * G::n2 + f * G::n2 + ft.fp;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) sS[k][slot] = w[1 + k];
-        sTs[slot] = Ts;
-        sFs[slot] = Fs;
+        sSa[slot] = V2<T>{w[0], w[1]};
+        sSb[slot] = V2<T>{w[2], w[3]};
+        sSc[slot] = w[4];
+        sTF[slot] = V2<T>{Ts, Fs};
         if constexpr (CV) {
 #pragma unroll
             for (int m = 0; m < 3; ++m) sN[m][slot] = n[m] * dS;
         }
+        if (task + NT < G::NF) load_tr(task + NT, tr);
     }
-    if (a.mesh.var) {
+    if (WALL && a.mesh.var) {
         // walls whose temperature varies along them: T* and the static
         // contact-angle flux at the local wall temperature, through the table
         // (each thread rewrites only the face points it wrote above)
         double tb = 0.0;  // a batch instance's stage time
         if (BATCH && a.clk) tb = stage_time(a.t0, *a.clk, a.dt, L.cs);
-        for (int task = t; task < G::NF; task += BS) {
+        for (int task = t; task < G::NF; task += NT) {
             const FaceTask<P> ft(task);
             const int el = e0 + ft.le, f = ft.f;
             if (el >= E) continue;
@@ -1212,382 +1391,461 @@ __global__ __launch_bounds__(BS) void k_lift2(Launch<T> L)
             const WallPt wp = wall_point<P>(a.mesh, L.bas, bc, el, f, ft.fp, BATCH ? tb : L.t);
             const int slot = ft.le * 6 * G::n2 + f * G::n2 + ft.fp;
             const FaceIx<G::n2> o((size_t)el * 6 + f, ft.fp);
-            if (bc.iso) sTs[slot] = T(wp.Tw);
-            else a.TF[o.at(7, 6)] = 1.0 / wp.Tw;  // 1/T_w for the heat-transfer flux below (TF[6] is free on walls)
+            if (bc.iso) sTF[slot].x = T(wp.Tw);
+            else a.TF[o.at(6, 0)] = T(1.0 / wp.Tw);  // for the heat-transfer flux below, which then overwrites it
             const T c = TU[o.at(6, 5)];
-            sFs[slot] = T(wp.gcoef) * (c - T(wp.rl)) * (c - T(wp.rv)) * face_dS<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp);
+            sTF[slot].y = T(wp.gcoef) * (c - T(wp.rl)) * (c - T(wp.rv)) * face_dS<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp);
         }
     }
     __syncthreads();
-    // lifted grad u, grad c and the nodal temperature
-    T gu[9], gc[3];
-    double Tn = 0.0;
+    // lifted gradients, nodal temperature and pressure, and the source
     const int i = nd % P, j = (nd / P) % P, k = nd / (P * P);
-    T Ja[9], iJ = T(0);
+    const int base = le * G::n3, fbase = le * 6 * G::n2;
+    T gc[3] = {T(0), T(0), T(0)}, S[6];
+    T iJ = T(0), div = T(0), p = T(0);
+    double Tn = 0.0;
+    T gu[3][3];
     if (act) {
+        T grho[3];
         if constexpr (CV) {
-            T q[4][3];
-            lifted_grads_curved<P, 4, G::NV, G::NF>(sW, sS, sJa, sN, le * G::n3, le * 6 * G::n2, i, j, k, sDh, sLh,
-                                                    iJn, q);
+            T q[5][3];
+            lifted_grads_curved<P, 5, G::NV, G::NF>([&](int n, T v[5]) { fw.at(n, v); }, [&](int n, T v[5]) { fs.at(n, v); },
+                                                    sJ, sJz, sN, base, fbase, i, j, k, B, iJn, q);
 #pragma unroll
-            for (int w = 0; w < 3; ++w)
-#pragma unroll
-                for (int m = 0; m < 3; ++m) gu[3 * w + m] = q[w][m];
-#pragma unroll
-            for (int m = 0; m < 3; ++m) gc[m] = q[3][m];
+            for (int m = 0; m < 3; ++m) {
+                grho[m] = q[0][m];
+                gu[0][m] = q[1][m];
+                gu[1][m] = q[2][m];
+                gu[2][m] = q[3][m];
+                gc[m] = q[4][m];
+            }
             iJ = iJn;
         } else {
-            T gd[4][3];
-            lifted_grads<P, 4>(sW, sS, le * G::n3, le * 6 * G::n2, i, j, k, sDh, sLh, gd);
-            element_metrics(a.mesh, metric_element<G::EPB, G::n3>(e0, e), Ja, iJ);
+            T gd[5][3], Ja[9];
+            lifted_grads<P, T>(fw, fs, base, fbase, i, j, k, B, gd);
+            element_metrics<G::kUni>(a.mesh, e, Ja, iJ);
+            to_physical(Ja, iJ, gd[0], grho);
 #pragma unroll
-            for (int w = 0; w < 3; ++w) to_physical(Ja, iJ, gd[w], gu + 3 * w);
-            to_physical(Ja, iJ, gd[3], gc);
+            for (int m = 0; m < 3; ++m) to_physical(Ja, iJ, gd[1 + m], gu[m]);
+            to_physical(Ja, iJ, gd[4], gc);
+        }
+        {
+            const V2<T> m01 = sM[tq], m2e = sM[G::NV + tq];
+            un[0] = sR[0][tq].x;
+            un[1] = m01.x;
+            un[2] = m01.y;
+            un[3] = m2e.x;
+            un[4] = m2e.y;
+            un[5] = sWc[tq];
         }
         Tn = temperature<fast_fp64<T>()>(a.ph, (double)un[0], (double)un[1], (double)un[2], (double)un[3], (double)un[4],
-                         (double)un[5], (double)gc[0], (double)gc[1], (double)gc[2]);
+                                         (double)un[5], (double)gc[0], (double)gc[1], (double)gc[2]);
+        div = gu[0][0] + gu[1][1] + gu[2][2];
+        double pd, cs2;
+        eos<fast_fp64<T>()>(a.ph, (double)un[0], Tn, pd, cs2);
+        p = T(pd + 0.5 * a.ph.ap * (double)un[0] * (double)un[0]);  // p_alpha for model 2
+        const T ir = T(1) / un[0];
+        const T u[3] = {un[1] * ir, un[2] * ir, un[3] * ir};
+        source(a.ph, un[0], un[5], u, grho, gu, gc, S);
     }
     __syncthreads();
     if (act) {
-        sA[0][t] = T(Tn);
         if constexpr (CV) {
-            // contravariant components Ja^d . grad c for the divergence lifting
 #pragma unroll
-            for (int d = 0; d < 3; ++d)
-                sA[1 + d][t] = sJa[3 * d][t] * gc[0] + sJa[3 * d + 1][t] * gc[1] + sJa[3 * d + 2][t] * gc[2];
+            for (int r = 0; r < 4; ++r) sR[r][tq] = V2<T>{gu[2 * r / 3][2 * r % 3], gu[(2 * r + 1) / 3][(2 * r + 1) % 3]};
+            sR[4][tq].x = gu[2][2];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const V2<T> jj = sJ[d][tq];
+                sR[kT + d][tq] = V2<T>{T(Tn), jj.x * gc[0] + jj.y * gc[1] + sJz[d][tq] * gc[2]};
+            }
         } else {
+            // per direction d, at the nodes: tau . n_d with n_d the outward
+            // normal of face 2d+1 (face 2d has exactly -n_d on these affine
+            // elements); its face values are the prolongations of these nodal
+            // values (n_d is constant on the face), so a face task prolongs
+            // 6 fields instead of 13
+            // (gc: the contravariant components from here on)
+            const T mu = T(a.ph.mu), td = T(2.0 / 3.0) * div, g0 = gc[0], g1 = gc[1], g2 = gc[2];
 #pragma unroll
-            for (int m = 0; m < 3; ++m) sA[1 + m][t] = gc[m];
+            for (int d = 0; d < 3; ++d) {
+                const int jr = kEmJa + 3 * d, fr = (2 * d + 1) * 4;
+                gc[d] = em_at<G::kUni, T>(a.mesh, e, jr) * g0 + em_at<G::kUni, T>(a.mesh, e, jr + 1) * g1 +
+                        em_at<G::kUni, T>(a.mesh, e, jr + 2) * g2;
+                const T n0 = em_at<G::kUni, T>(a.mesh, e, fr), n1 = em_at<G::kUni, T>(a.mesh, e, fr + 1),
+                        n2 = em_at<G::kUni, T>(a.mesh, e, fr + 2);
+                T tn[3];
+#pragma unroll
+                for (int m = 0; m < 3; ++m)
+                    tn[m] = mu * ((gu[m][0] + gu[0][m]) * n0 + (gu[m][1] + gu[1][m]) * n1 + (gu[m][2] + gu[2][m]) * n2 -
+                                  td * (m == 0 ? n0 : (m == 1 ? n1 : n2)));
+                sR[d][tq] = V2<T>{tn[0], tn[1]};
+                sR[3 + d][tq] = V2<T>{tn[2], div};
+                sR[kT + d][tq] = V2<T>{T(Tn), gc[d]};
+            }
         }
-#pragma unroll
-        for (int r = 0; r < 9; ++r) sGu[r][t] = gu[r];
     }
     __syncthreads();
-    if (a.mesh.dyn) {
+    if (WALL && a.mesh.dyn) {
         // Navier-slip walls with gamma_1 != 0: the contact-angle flux gains
         // (gamma_1/gamma) div u, div u the trace of the lifted velocity gradient
-        for (int task = t; task < G::NF; task += BS) {
+        for (int task = t; task < G::NF; task += NT) {
             const FaceTask<P> ft(task);
             const int el = e0 + ft.le, f = ft.f;
             if (el >= E) continue;
             if (gld(a.mesh.nbr, el * 6 + f) >= 0) continue;  // interior: no wall-table entry
             const BcDev &bc = a.mesh.bcs[a.mesh.bcid[el * 6 + f] - 1];
             if (bc.kind != 3 || bc.g1 == 0.0) continue;
-            const T *Lf = sL + (f & 1) * P;
+            const T *Lf = B.Lf + (f & 1) * B.PS;
             const int lo = ft.le * G::n3 + ft.off, ls = ft.str;
-            T d0 = T(0), d1 = T(0), d2 = T(0);
+            T d0 = T(0);
 #pragma unroll
             for (int l = 0; l < P; ++l) {
-                d0 += T(Lf[l]) * sGu[0][lo + l * ls];
-                d1 += T(Lf[l]) * sGu[4][lo + l * ls];
-                d2 += T(Lf[l]) * sGu[8][lo + l * ls];
+                const int q = lo + l * ls;
+                d0 += Lf[l] * (CV ? sR[0][q].x + sR[2][q].x + sR[4][q].x : sR[3][q].y);
             }
             const T dS = face_dS<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp);
-            sFs[ft.le * 6 * G::n2 + f * G::n2 + ft.fp] += T(bc.g1_gam) * ((d0 + d1) + d2) * dS;
+            sTF[ft.le * 6 * G::n2 + f * G::n2 + ft.fp].y += T(bc.g1_gam) * d0 * dS;
         }
         __syncthreads();
     }
-    // grad T (BR1 with T*) and lap c (divergence lifting of grad c)
+    // grad T (BR1 with T*) and lap c (divergence lifting of grad c from its
+    // contravariant components)
     T gT[3] = {T(0), T(0), T(0)}, lap = T(0);
     if (act) {
         const int idx[3] = {i, j, k};
         const int fpd[3] = {j + P * k, i + P * k, i + P * j};
-        const int base = le * G::n3;
-        const int fbase = le * 6 * G::n2;
+        T gd[3], dl = T(0);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const int p = d == 0 ? j : i, q = d == 2 ? j : k;
+            T accT = T(0), ad = T(0), D[P];
+            B.row(B.Dh + idx[d] * B.PS, D);
+#pragma unroll
+            for (int l = 0; l < P; ++l) {
+                const V2<T> v = sR[kT + d][base + line_node<P>(d, l, p, q)];
+                if constexpr (!CV) accT += D[l] * v.x;
+                ad += D[l] * v.y;
+            }
+            const V2<T> lh = B.Lh[idx[d]], vp = sTF[fbase + (2 * d + 1) * G::n2 + fpd[d]], vm = sTF[fbase + (2 * d) * G::n2 + fpd[d]];
+            if constexpr (!CV) gd[d] = accT + (lh.y * vp.x - lh.x * vm.x);
+            dl += ad + lh.y * vp.y + lh.x * vm.y;
+        }
         if constexpr (CV) {
-            // lap c: Dhat sweeps of the contravariant components; grad T: the
-            // conservative lifting with the node metrics
-            T dl = T(0);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const int id = idx[d];
-                const int p = d == 0 ? j : i, q = d == 2 ? j : k;
-                T ad = T(0);
-#pragma unroll
-                for (int l = 0; l < P; ++l) ad += T(sDh[id * P + l]) * sA[1 + d][base + line_node<P>(d, l, p, q)];
-                const int fp = fbase + (2 * d + 1) * G::n2 + fpd[d], fm_ = fbase + (2 * d) * G::n2 + fpd[d];
-                dl += ad + T(sLh[P + id]) * sFs[fp] + T(sLh[id]) * sFs[fm_];
-            }
             T qT[1][3];
-            lifted_grads_curved<P, 1, G::NV, G::NF>(sA, &sTs, sJa, sN, base, fbase, i, j, k, sDh, sLh, iJ, qT);
-            gT[0] = qT[0][0];
-            gT[1] = qT[0][1];
-            gT[2] = qT[0][2];
-            lap = iJ * dl;
+            lifted_grads_curved<P, 1, G::NV, G::NF>([&](int n, T v[1]) { v[0] = sR[kT][n].x; }, [&](int n, T v[1]) { v[0] = sTF[n].x; },
+                                                    sJ, sJz, sN, base, fbase, i, j, k, B, iJ, qT);
+#pragma unroll
+            for (int m = 0; m < 3; ++m) gT[m] = qT[0][m];
         } else {
-            T gd[3], dl = T(0);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const int id = idx[d];
-                const int p = d == 0 ? j : i, q = d == 2 ? j : k;
-                T accT = T(0), a0 = T(0), a1 = T(0), a2 = T(0);
-#pragma unroll
-                for (int l = 0; l < P; ++l) {
-                    const int n = base + line_node<P>(d, l, p, q);
-                    const T D = T(sDh[id * P + l]);
-                    accT += D * sA[0][n];
-                    a0 += D * sA[1][n];
-                    a1 += D * sA[2][n];
-                    a2 += D * sA[3][n];
-                }
-                const int fp = fbase + (2 * d + 1) * G::n2 + fpd[d], fm_ = fbase + (2 * d) * G::n2 + fpd[d];
-                accT += T(sLh[P + id]) * sTs[fp] - T(sLh[id]) * sTs[fm_];
-                gd[d] = accT;
-                dl += Ja[3 * d + 0] * a0 + Ja[3 * d + 1] * a1 + Ja[3 * d + 2] * a2 +
-                      T(sLh[P + id]) * sFs[fp] + T(sLh[id]) * sFs[fm_];
-            }
-#pragma unroll
-            for (int m = 0; m < 3; ++m) gT[m] = iJ * (Ja[m] * gd[0] + Ja[3 + m] * gd[1] + Ja[6 + m] * gd[2]);
-            lap = iJ * dl;
+            T Ja[9], iJ2;
+            element_metrics<G::kUni>(a.mesh, e, Ja, iJ2);
+            to_physical(Ja, iJ, gd, gT);
         }
-        gst(a.G2 + (0) * a.NN, g32, T(gT[0]));
-        gst(a.G2 + (1) * a.NN, g32, T(gT[1]));
-        gst(a.G2 + (2) * a.NN, g32, T(gT[2]));
-        gst(a.G2 + (3) * a.NN, g32, T(lap));
+        lap = iJ * dl;
+        if (L.mode == 2) {  // the second lifting's output alone
+            gst(a.G2 + (0) * a.NN, g32, T(gT[0]));
+            gst(a.G2 + (1) * a.NN, g32, T(gT[1]));
+            gst(a.G2 + (2) * a.NN, g32, T(gT[2]));
+            gst(a.G2 + (3) * a.NN, g32, T(lap));
+        }
     }
+    if (L.mode == 2) return;
+    // j_e = k grad T + (gamma zeta - gamma c div u) grad c
+    const T zc = T(a.ph.gam) * (T(a.ph.beta) * (T(a.ph.gam) * lap + T(a.ph.alpha) * (un[0] - un[5])) - un[5] * div);
     __syncthreads();
-    if constexpr (CV) {
-        // curved elements: the normal varies along the face, so the face
-        // tasks prolong grad u (already in sX), grad T and lap c and take
-        // their normal components at each face point: grad T in sA[1..3],
-        // lap c in sTs
-        if (act) {
-            sA[1][t] = gT[0];
-            sA[2][t] = gT[1];
-            sA[3][t] = gT[2];
-            sTs[t] = lap;
-        }
-    } else {
-        // per direction d, at the nodes: tau . n_d (3) and grad T . n_d with n_d
-        // the outward normal of face 2d+1 (face 2d has exactly -n_d on these
-        // affine elements), plus div u and lap c.  Their face values are the
-        // prolongations of these nodal values (n_d is constant on the face), so
-        // a face task prolongs 12 fields instead of 19.  Layout: direction 0 in
-        // sA, directions 1 and 2 and div u in sX (each thread overwrites only its
-        // own node's grad u, which it has read), lap c in sTs.
-        if (act) {
-            T gg[9];
-#pragma unroll
-            for (int r = 0; r < 9; ++r) gg[r] = sGu[r][t];
-            const T div = gg[0] + gg[4] + gg[8];
-            const T td = T(2.0 / 3.0) * div, mu = T(a.ph.mu);
+    if (act) {
+        if constexpr (CV) {
+            sR[kT][tq] = V2<T>{gT[0], gT[1]};
+            sR[kT + 1][tq] = V2<T>{gT[2], lap};
+        } else {
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-                const uint32_t fq = ((uint32_t)metric_element<G::EPB, G::n3>(e0, e) * 6 + 2 * d + 1) * 4;
-                const T n0 = T(gld(a.mesh.fmet, fq)), n1 = T(gld(a.mesh.fmet, fq + 1)), n2 = T(gld(a.mesh.fmet, fq + 2));
-                T *out = d == 0 ? &sA[0][0] : sX + (d - 1) * 4 * G::NV;
-                out[0 * G::NV + t] = mu * ((gg[0] + gg[0]) * n0 + (gg[1] + gg[3]) * n1 + (gg[2] + gg[6]) * n2 - td * n0);
-                out[1 * G::NV + t] = mu * ((gg[3] + gg[1]) * n0 + (gg[4] + gg[4]) * n1 + (gg[5] + gg[7]) * n2 - td * n1);
-                out[2 * G::NV + t] = mu * ((gg[6] + gg[2]) * n0 + (gg[7] + gg[5]) * n1 + (gg[8] + gg[8]) * n2 - td * n2);
-                out[3 * G::NV + t] = gT[0] * n0 + gT[1] * n1 + gT[2] * n2;
+                const int fr = (2 * d + 1) * 4;
+                const T n0 = em_at<G::kUni, T>(a.mesh, e, fr), n1 = em_at<G::kUni, T>(a.mesh, e, fr + 1),
+                        n2 = em_at<G::kUni, T>(a.mesh, e, fr + 2);
+                sR[kT + d][tq] = V2<T>{gT[0] * n0 + gT[1] * n1 + gT[2] * n2, lap};
             }
-            sX[8 * G::NV + t] = div;
-            sTs[t] = lap;
         }
     }
     __syncthreads();
-    // own-face flux traces, one face point per task: G = (F^C - F^V).n and
-    // the wave speed; on walls the complete wall flux in G.  Each field group
-    // is folded into the six flux components as soon as it is prolonged, so
-    // few values stay live.
-    for (int task = t; task < G::NF; task += BS) {
+    // own-face flux traces, one face point per task: on interior faces half
+    // of the convective part from above and of -F^V . n, times dS, so that the
+    // numerical flux is the difference of the two sides' traces; on walls (a
+    // pass of its own, whose values would cost the common one registers) the
+    // complete wall flux times dS
+    struct Pro {  // prolongation of one row of sX to a face point
+        const T *Lr;
+        int lo, ls;
+        __device__ __forceinline__ V2<T> operator()(const V2<T> *fld) const
         {
-            const FaceTask<P> ft(task);
-            const int el = e0 + ft.le, f = ft.f;
-            if (el >= E) continue;
-            const T *Lf = sL + (f & 1) * P;
-            const int lo = ft.le * G::n3 + ft.off, ls = ft.str;
-            auto pro = [&](const T *fld) {
-                T acc = T(0);
+            T w[P], x = T(0), y = T(0);
+            BasisS<P, T>::row(Lr, w);
 #pragma unroll
-                for (int l = 0; l < P; ++l) acc += T(Lf[l]) * fld[lo + l * ls];
-                return acc;
-            };
-            const FaceIx<G::n2> o((size_t)el * 6 + f, ft.fp);
-            T nrm[3], dSf;
-            bool wall;
-            if constexpr (kOne) {  // task == t: the values loaded with the traces
-                nrm[0] = tr0.n[0];
-                nrm[1] = tr0.n[1];
-                nrm[2] = tr0.n[2];
-                dSf = tr0.dS;
-                wall = tr0.nb < 0;
-            } else {
-                face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp, nrm, dSf);
-                wall = gld(a.mesh.nbr, el * 6 + f) < 0;
+            for (int l = 0; l < P; ++l) {
+                const V2<T> v = fld[lo + l * ls];
+                x += w[l] * v.x;
+                y += w[l] * v.y;
             }
-            const T n0 = nrm[0], n1 = nrm[1], n2 = nrm[2];
-            int kind = 0;  // interior faces have no wall-table entry
-            if (wall) kind = a.mesh.bcs[a.mesh.bcid[el * 6 + f] - 1].kind;
-            // state and convective part
-            // scheduling barriers keep each field group's LDS loads next to the
-            // arithmetic that consumes them (otherwise all of them are hoisted
-            // and the register demand limits occupancy)
-            T rho, m0, m1, m2, E, c, gcn;
-            double Tf;
-            if (kKeep && task == t) {
-                rho = tr0.uo[0]; m0 = tr0.uo[1]; m1 = tr0.uo[2]; m2 = tr0.uo[3]; E = tr0.uo[4]; c = tr0.uo[5];
-                gcn = tr0.own[0];
-                Tf = (double)tr0.own[1];
-                if constexpr (sizeof(T) == 4) Tf += (double)tr0.own[2];
-            } else {
-                rho = TU[o.at(6, 0)]; m0 = TU[o.at(6, 1)]; m1 = TU[o.at(6, 2)]; m2 = TU[o.at(6, 3)];
-                E = TU[o.at(6, 4)]; c = TU[o.at(6, 5)];
-                gcn = a.T2[o.at(kT2<T>(), 0)];
-                // the face temperature as recovered in FP64 (FP32: value + rounding error)
-                Tf = (double)a.T2[o.at(kT2<T>(), 1)];
-                if constexpr (sizeof(T) == 4) Tf += (double)a.T2[o.at(kT2<T>(), 2)];
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            const T ir = T(1) / rho;
-            const T u0 = m0 * ir, u1 = m1 * ir, u2 = m2 * ir;
-            const T mn = m0 * n0 + m1 * n1 + m2 * n2;
-            const T un = mn * ir;
-            double pd, cs2;
-            eos<fast_fp64<T>()>(a.ph, (double)rho, Tf, pd, cs2);
-            // model 2: p_alpha and its sound speed (ap = 0 for model 1)
-            const T p = T(pd + 0.5 * a.ph.ap * (double)rho * (double)rho);
-            const T cw = sqrt_to<T>(fabs(cs2 + a.ph.ap * (double)rho));
-            const T lam = fabs(un) + cw;
-            // interior faces of model 2 store p_alpha, -F^V.n and the sound
-            // speed; the HLLC flux is formed from both sides' traces later
-            const bool hl = !wall && a.ph.model == 2;
-            T G0, G1, G2_, G3, G4, G5;
-            if (hl) {
-                G0 = p;
-                G1 = G2_ = G3 = G4 = G5 = T(0);
-            } else if (!wall) {
-                G0 = mn;
-                G1 = m0 * un + p * n0;
-                G2_ = m1 * un + p * n1;
-                G3 = m2 * un + p * n2;
-                G4 = (E + p) * un;
-                G5 = c * un;
-            } else if (kind == 1) {  // ghost velocity 2 u_w - u (same rho, c, T)
-                const BcDev &bc = a.mesh.bcs[a.mesh.bcid[el * 6 + f] - 1];
-                const T w0 = T(bc.uw[0]), w1 = T(bc.uw[1]), w2 = T(bc.uw[2]);
-                const T r0 = m0 - rho * w0, r1 = m1 - rho * w1, r2 = m2 - rho * w2;
-                G0 = T(0);
-                G1 = r0 * un + p * n0 + lam * r0;
-                G2_ = r1 * un + p * n1 + lam * r1;
-                G3 = r2 * un + p * n2 + lam * r2;
-                // energy: -(u.n + lam)/2 times the ghost's extra kinetic energy
-                // 2 rho (|u_w|^2 - u_w . u)
-                G4 = -(un + lam) * rho * (w0 * (w0 - u0) + w1 * (w1 - u1) + w2 * (w2 - u2));
-                G5 = T(0);
-            } else {                 // mirrored normal velocity only
-                const T q = mn * un + p + lam * mn;
-                G0 = T(0);
-                G1 = q * n0;
-                G2_ = q * n1;
-                G3 = q * n2;
-                G4 = T(0);
-                G5 = T(0);
-            }
-            // viscous traction tau n = mu ((grad u + grad u^T) n - 2/3 div u n)
-            __builtin_amdgcn_sched_barrier(0);
-            // affine elements: the nodal normal components of direction f/2,
-            // with the face's sign; curved: the normal components are taken
-            // of the prolonged gradients at this face point
-            const T sgn = (f & 1) ? T(1) : T(-1);
-            const T *nf = (f >> 1) == 0 ? &sA[0][0] : sX + ((f >> 1) - 1) * 4 * G::NV;
-            auto grad_T_n = [&]() {
-                if constexpr (CV) return pro(sA[1]) * n0 + pro(sA[2]) * n1 + pro(sA[3]) * n2;
-                else return sgn * pro(nf + 3 * G::NV);
-            };
-            T div, tn0, tn1, tn2;
-            if constexpr (CV) {
-                T gf[9];
-#pragma unroll
-                for (int r = 0; r < 9; ++r) gf[r] = pro(sGu[r]);  // gf[3 j + i] = d u_j / d x_i
-                div = gf[0] + gf[4] + gf[8];
-                const T td = T(2.0 / 3.0) * div, mu = T(a.ph.mu);
-                tn0 = mu * ((gf[0] + gf[0]) * n0 + (gf[1] + gf[3]) * n1 + (gf[2] + gf[6]) * n2 - td * n0);
-                tn1 = mu * ((gf[3] + gf[1]) * n0 + (gf[4] + gf[4]) * n1 + (gf[5] + gf[7]) * n2 - td * n1);
-                tn2 = mu * ((gf[6] + gf[2]) * n0 + (gf[7] + gf[5]) * n1 + (gf[8] + gf[8]) * n2 - td * n2);
-            } else {
-                div = pro(sX + 8 * G::NV);
-                tn0 = sgn * pro(nf);
-                tn1 = sgn * pro(nf + G::NV);
-                tn2 = sgn * pro(nf + 2 * G::NV);
-            }
-            if (!wall) {
-                G1 -= tn0;
-                G2_ -= tn1;
-                G3 -= tn2;
-                G4 -= tn0 * u0 + tn1 * u1 + tn2 * u2;
-            } else if (kind == 1) {  // traction, and its work at the wall velocity
-                const BcDev &bc = a.mesh.bcs[a.mesh.bcid[el * 6 + f] - 1];
-                G1 -= tn0;
-                G2_ -= tn1;
-                G3 -= tn2;
-                G4 -= tn0 * T(bc.uw[0]) + tn1 * T(bc.uw[1]) + tn2 * T(bc.uw[2]);
-            } else {
-                const T tnn = tn0 * n0 + tn1 * n1 + tn2 * n2;
-                G1 -= tnn * n0;
-                G2_ -= tnn * n1;
-                G3 -= tnn * n2;
-                if (kind == 3) {
-                    // Navier slip: tangential traction gamma_1 div u grad_G c -
-                    // gamma_2 (u_t - u_w,t), and its work on u_t
-                    const BcDev &bc = a.mesh.bcs[a.mesh.bcid[el * 6 + f] - 1];
-                    const T gc0 = a.T2[o.at(kT2<T>(), kT2gc<T>())], gc1 = a.T2[o.at(kT2<T>(), kT2gc<T>() + 1)],
-                            gc2 = a.T2[o.at(kT2<T>(), kT2gc<T>() + 2)];
-                    const T gcn = gc0 * n0 + gc1 * n1 + gc2 * n2;
-                    const T w0 = T(bc.uw[0]), w1 = T(bc.uw[1]), w2 = T(bc.uw[2]);
-                    const T wn = w0 * n0 + w1 * n1 + w2 * n2;
-                    const T a1 = T(bc.g1) * div, a2 = T(bc.g2);
-                    const T ut0 = u0 - un * n0, ut1 = u1 - un * n1, ut2 = u2 - un * n2;
-                    const T t0 = a1 * (gc0 - gcn * n0) - a2 * (ut0 - (w0 - wn * n0));
-                    const T t1 = a1 * (gc1 - gcn * n1) - a2 * (ut1 - (w1 - wn * n1));
-                    const T t2 = a1 * (gc2 - gcn * n2) - a2 * (ut2 - (w2 - wn * n2));
-                    G1 -= t0;
-                    G2_ -= t1;
-                    G3 -= t2;
-                    G4 -= t0 * ut0 + t1 * ut1 + t2 * ut2;
-                }
-            }
-            // heat flux
-            __builtin_amdgcn_sched_barrier(0);
-            // (interior faces have no wall-table entry: bcid is 0 there)
-            if (!wall) {
-                const T gTn = grad_T_n();
-                G4 -= T(a.ph.kappa) * gTn;
-            } else if (kind != 2) {
-                const BcDev &bc = a.mesh.bcs[a.mesh.bcid[el * 6 + f] - 1];
-                if (bc.iso) {
-                    const T gTn = grad_T_n();
-                    G4 -= T(a.ph.kappa) * gTn;
-                } else {  // heat transfer, eq. bc_energy_alpha
-                    const double itw = bc.var ? (double)a.TF[o.at(7, 6)] : bc.inv_tw;
-                    G4 -= T(-bc.g3 * (itw - 1.0 / Tf));
-                }
-            }
-            // order-parameter terms of j_e and F^V_c
-            __builtin_amdgcn_sched_barrier(0);
-            if (!wall) {
-                const T lapc = pro(sTs);
-                const T zeta = T(a.ph.beta) * (T(a.ph.gam) * lapc + T(a.ph.alpha) * (rho - c));
-                G4 -= -T(a.ph.gam) * c * gcn * div + T(a.ph.gam) * gcn * zeta;
-                G5 -= T(a.ph.gam * a.ph.beta) * gcn;
-                a.TF[o.at(7, 6)] = hl ? cw : lam;
-            } else if (kind != 2) {
-                // contact-angle flux g (with gamma_1 div u on Navier-slip
-                // walls), as the second lifting used it: sFs holds g dS; and
-                // the wall value zeta_c = -gamma_1 gamma_4 div u
-                const BcDev &bc = a.mesh.bcs[a.mesh.bcid[el * 6 + f] - 1];
-                const T gw = sFs[ft.le * 6 * G::n2 + f * G::n2 + ft.fp] / dSf;
-                const T zeta = -T(bc.g1 * bc.g4) * div;
-                G4 -= -T(a.ph.gam) * c * gw * div + T(a.ph.gam) * gw * zeta;
-                G5 -= T(a.ph.gam * a.ph.beta) * gw;
-            }
-            a.TF[o.at(7, 0)] = G0;
-            a.TF[o.at(7, 1)] = G1;
-            a.TF[o.at(7, 2)] = G2_;
-            a.TF[o.at(7, 3)] = G3;
-            a.TF[o.at(7, 4)] = G4;
-            a.TF[o.at(7, 5)] = G5;
+            T r[2] = {x, y};
+            bound(r, 2);
+            return V2<T>{r[0], r[1]};
         }
+    };
+    // the face values of tau n (traction mu ((grad u + grad u^T) n - 2/3 div u
+    // n)), div u, grad T . n and lap c.  Affine elements: from the nodal
+    // normal components of direction f/2, with the face's sign; curved: from
+    // the prolonged gradients and the normal of this face point.
+    auto viscous = [&](const Pro &pro, int f, const T n[3], T tn[3], T &dv, T &gTn, T &lapf) {
+        if constexpr (CV) {
+            T gf[10];
+#pragma unroll
+            for (int r = 0; r < 5; ++r) {
+                const V2<T> v = pro(sR[r]);
+                gf[2 * r] = v.x;  // gf[3 j + i] = d u_j / d x_i
+                gf[2 * r + 1] = v.y;
+            }
+            dv = gf[0] + gf[4] + gf[8];
+            const T td = T(2.0 / 3.0) * dv, mu = T(a.ph.mu);
+            tn[0] = mu * ((gf[0] + gf[0]) * n[0] + (gf[1] + gf[3]) * n[1] + (gf[2] + gf[6]) * n[2] - td * n[0]);
+            tn[1] = mu * ((gf[3] + gf[1]) * n[0] + (gf[4] + gf[4]) * n[1] + (gf[5] + gf[7]) * n[2] - td * n[1]);
+            tn[2] = mu * ((gf[6] + gf[2]) * n[0] + (gf[7] + gf[5]) * n[1] + (gf[8] + gf[8]) * n[2] - td * n[2]);
+            const V2<T> x = pro(sR[kT]), y = pro(sR[kT + 1]);
+            gTn = x.x * n[0] + x.y * n[1] + y.x * n[2];
+            lapf = y.y;
+        } else {
+            const T sgn = (f & 1) ? T(1) : T(-1);
+            const int d = f >> 1;
+            const V2<T> x = pro(sR[d]), y = pro(sR[3 + d]), z = pro(sR[kT + d]);
+            tn[0] = sgn * x.x;
+            tn[1] = sgn * x.y;
+            tn[2] = sgn * y.x;
+            dv = y.y;
+            gTn = sgn * z.x;
+            lapf = z.y;
+        }
+    };
+    for (int task = t; task < G::NF; task += NT) {
+        const FaceTask<P> ft(task);
+        const int el = e0 + ft.le, f = ft.f;
+        if (el >= E) break;
+        const bool keep = kKeep && task == t;
+        if (WALL && (keep ? fwall : gld(a.mesh.nbr, el * 6 + f) < 0)) continue;
+        const Pro pro{B.Lf + (f & 1) * B.PS, ft.le * G::n3 + ft.off, ft.str};
+        const FaceIx<G::n2> o((size_t)el * 6 + f, ft.fp);
+        T K[6], dS;
+        T u0, u1, u2, c, rc, gcn, n[3] = {T(0), T(0), T(0)};
+        if (keep) {
+#pragma unroll
+            for (int v = 0; v < 6; ++v) K[v] = Kc[v];
+            u0 = fu[0]; u1 = fu[1]; u2 = fu[2];
+            c = fc;
+            rc = frc;
+            gcn = fgn;
+            dS = fdS;
+            if constexpr (CV) face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp, n, dS);
+        } else {
+#pragma unroll
+            for (int v = 0; v < 6; ++v) K[v] = a.TF[o.at(6, v)];
+            const T uo[6] = {TU[o.at(6, 0)], TU[o.at(6, 1)], TU[o.at(6, 2)], TU[o.at(6, 3)], T(0), TU[o.at(6, 5)]};
+            T w[5];
+            primitives(uo, w);
+            u0 = w[1]; u1 = w[2]; u2 = w[3];
+            c = uo[5];
+            rc = uo[0] - uo[5];
+            gcn = a.T2[o.at(kT2<T>(), 0)];
+            if constexpr (CV) face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp, n, dS);
+            else dS = face_dS<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp);
+        }
+        // scheduling barriers keep each field group's LDS loads next to the
+        // arithmetic that consumes them (otherwise all of them are hoisted
+        // and the register demand limits occupancy)
+        __builtin_amdgcn_sched_barrier(0);
+        T tn[3], dv, gTn, lapc;
+        viscous(pro, f, n, tn, dv, gTn, lapc);
+        K[1] -= tn[0];
+        K[2] -= tn[1];
+        K[3] -= tn[2];
+        K[4] -= tn[0] * u0 + tn[1] * u1 + tn[2] * u2;
+        K[4] -= T(a.ph.kappa) * gTn;
+        // order-parameter terms of j_e and F^V_c
+        const T zeta = T(a.ph.beta) * (T(a.ph.gam) * lapc + T(a.ph.alpha) * rc);
+        K[4] -= -T(a.ph.gam) * c * gcn * dv + T(a.ph.gam) * gcn * zeta;
+        K[5] -= T(a.ph.gam * a.ph.beta) * gcn;
+        dS *= T(0.5);
+#pragma unroll
+        for (int v = 0; v < 6; ++v) a.TF[o.at(6, v)] = K[v] * dS;
+    }
+    if (WALL && a.mesh.wall)
+    for (int task = t; task < G::NF; task += NT) {
+        const FaceTask<P> ft(task);
+        const int el = e0 + ft.le, f = ft.f;
+        if (el >= E) break;
+        if (gld(a.mesh.nbr, el * 6 + f) >= 0) continue;
+        const BcDev &bc = a.mesh.bcs[a.mesh.bcid[el * 6 + f] - 1];
+        const int kind = bc.kind;
+        const Pro pro{B.Lf + (f & 1) * B.PS, ft.le * G::n3 + ft.off, ft.str};
+        const FaceIx<G::n2> o((size_t)el * 6 + f, ft.fp);
+        T K[6], n[3], dS;
+        face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp, n, dS);
+        T u6[6], q[3];
+#pragma unroll
+        for (int v = 0; v < 6; ++v) u6[v] = TU[o.at(6, v)];
+#pragma unroll
+        for (int k2 = 0; k2 < kT2gc<T>(); ++k2) q[k2] = a.T2[o.at(kT2<T>(), k2)];
+        const double Tf = face_T(u6, q);
+        T p, cw;
+        face_eos(u6[0], Tf, p, cw);
+        const T rho = u6[0], c = u6[5], ir = T(1) / rho;
+        const T u0 = u6[1] * ir, u1 = u6[2] * ir, u2 = u6[3] * ir;
+        const T mn = u6[1] * n[0] + u6[2] * n[1] + u6[3] * n[2], vn = mn * ir, lam = fabs(vn) + cw;
+        T tn[3], dv, gTn, lapc;
+        viscous(pro, f, n, tn, dv, gTn, lapc);
+        const T w0 = T(bc.uw[0]), w1 = T(bc.uw[1]), w2 = T(bc.uw[2]);
+        K[0] = K[4] = K[5] = T(0);
+        if (kind == 1) {
+            // ghost velocity 2 u_w - u (same rho, c, T); energy: -(u.n + lam)/2
+            // times the ghost's extra kinetic energy 2 rho (|u_w|^2 - u_w . u);
+            // the traction, and its work at the wall velocity
+            const T r0 = u6[1] - rho * w0, r1 = u6[2] - rho * w1, r2 = u6[3] - rho * w2;
+            K[1] = r0 * vn + p * n[0] + lam * r0 - tn[0];
+            K[2] = r1 * vn + p * n[1] + lam * r1 - tn[1];
+            K[3] = r2 * vn + p * n[2] + lam * r2 - tn[2];
+            K[4] = -(vn + lam) * rho * (w0 * (w0 - u0) + w1 * (w1 - u1) + w2 * (w2 - u2));
+            K[4] -= tn[0] * w0 + tn[1] * w1 + tn[2] * w2;
+        } else {
+            // mirrored normal velocity only; normal part of the traction
+            const T s_ = mn * vn + p + lam * mn - (tn[0] * n[0] + tn[1] * n[1] + tn[2] * n[2]);
+            K[1] = s_ * n[0];
+            K[2] = s_ * n[1];
+            K[3] = s_ * n[2];
+            if (kind == 3) {
+                // Navier slip: tangential traction gamma_1 div u grad_G c -
+                // gamma_2 (u_t - u_w,t), and its work on u_t
+                const T gc0 = a.T2[o.at(kT2<T>(), kT2gc<T>())], gc1 = a.T2[o.at(kT2<T>(), kT2gc<T>() + 1)],
+                        gc2 = a.T2[o.at(kT2<T>(), kT2gc<T>() + 2)];
+                const T gcn = gc0 * n[0] + gc1 * n[1] + gc2 * n[2];
+                const T wn = w0 * n[0] + w1 * n[1] + w2 * n[2];
+                const T a1 = T(bc.g1) * dv, a2 = T(bc.g2);
+                const T ut0 = u0 - vn * n[0], ut1 = u1 - vn * n[1], ut2 = u2 - vn * n[2];
+                const T t0 = a1 * (gc0 - gcn * n[0]) - a2 * (ut0 - (w0 - wn * n[0]));
+                const T t1 = a1 * (gc1 - gcn * n[1]) - a2 * (ut1 - (w1 - wn * n[1]));
+                const T t2 = a1 * (gc2 - gcn * n[2]) - a2 * (ut2 - (w2 - wn * n[2]));
+                K[1] -= t0;
+                K[2] -= t1;
+                K[3] -= t2;
+                K[4] -= t0 * ut0 + t1 * ut1 + t2 * ut2;
+            }
+        }
+        if (kind != 2) {
+            if (bc.iso) {
+                K[4] -= T(a.ph.kappa) * gTn;
+            } else {  // heat transfer, eq. bc_energy_alpha
+                const double itw = bc.var ? (double)a.TF[o.at(6, 0)] : bc.inv_tw;
+                K[4] -= T(-bc.g3 * (itw - 1.0 / Tf));
+            }
+            // contact-angle flux g (with gamma_1 div u on Navier-slip
+            // walls), as the second lifting used it: sTF holds g dS; and
+            // the wall value zeta_c = -gamma_1 gamma_4 div u
+            const T gw = sTF[ft.le * 6 * G::n2 + f * G::n2 + ft.fp].y / dS;
+            const T zeta = -T(bc.g1 * bc.g4) * dv;
+            K[4] -= -T(a.ph.gam) * c * gw * dv + T(a.ph.gam) * gw * zeta;
+            K[5] -= T(a.ph.gam * a.ph.beta) * gw;
+        }
+#pragma unroll
+        for (int v = 0; v < 6; ++v) a.TF[o.at(6, v)] = K[v] * dS;
+    }
+    // the RK register of this node, requested now so that the loads complete
+    // during the volume integral
+    T Rn[6];
+    if (L.mode == 1 && act && !L.first) {
+#pragma unroll
+        for (int v = 0; v < 6; ++v) Rn[v] = gld(a.R + (v) * a.NN, g32);
+    }
+    // volume integral sum_d Dhat_d (Ja^d . F): the contravariant fluxes of
+    // direction d+1 are written while direction d is read, one barrier per
+    // direction
+    T acc[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
+    const T irn = T(1) / un[0];
+    // row q of the fluxes of direction 1 (odd) or 0 and 2
+    auto frow = [&](bool odd, int q) { return odd ? (CV ? 8 + q : (q == 0 ? 0 : (q == 1 ? 3 : 1))) : kT + q; };
+    auto put_flux = [&](int d) {
+        // contravariant fluxes Ja^d . F of (F^C - F^V), F^V = (0, tau, tau u +
+        // j_e, gamma beta grad c): on affine elements Ja^d . tau is dS_d times
+        // tau . n_d
+        T J[3], tj[3], gj;
+        if constexpr (CV) {
+            const V2<T> jj = sJ[d][tq];
+            J[0] = jj.x;
+            J[1] = jj.y;
+            J[2] = sJz[d][tq];
+            T gg[10];
+#pragma unroll
+            for (int r = 0; r < 5; ++r) {
+                const V2<T> v = sR[r][tq];
+                gg[2 * r] = v.x;
+                gg[2 * r + 1] = v.y;
+            }
+            const T mu = T(a.ph.mu), td = T(2.0 / 3.0) * div;
+#pragma unroll
+            for (int m = 0; m < 3; ++m)
+                tj[m] = mu * ((gg[3 * m] + gg[m]) * J[0] + (gg[3 * m + 1] + gg[3 + m]) * J[1] +
+                              (gg[3 * m + 2] + gg[6 + m]) * J[2] - td * J[m]);
+            gj = J[0] * gc[0] + J[1] * gc[1] + J[2] * gc[2];
+        } else {
+#pragma unroll
+            for (int m = 0; m < 3; ++m) J[m] = em_at<G::kUni, T>(a.mesh, e, kEmJa + 3 * d + m);
+            const T dS = em_at<G::kUni, T>(a.mesh, e, (2 * d + 1) * 4 + 3);
+            const V2<T> x = sR[d][tq], y = sR[3 + d][tq];
+            tj[0] = dS * x.x;
+            tj[1] = dS * x.y;
+            tj[2] = dS * y.x;
+            gj = d == 0 ? gc[0] : (d == 1 ? gc[1] : gc[2]);
+        }
+        const T qj = J[0] * gT[0] + J[1] * gT[1] + J[2] * gT[2];
+        const T mJ = J[0] * un[1] + J[1] * un[2] + J[2] * un[3], uJ = mJ * irn;
+        const T tw = (tj[0] * un[1] + tj[1] * un[2] + tj[2] * un[3]) * irn;
+        sR[frow(d & 1, 0)][tq] = V2<T>{mJ, un[1] * uJ + p * J[0] - tj[0]};
+        sR[frow(d & 1, 1)][tq] = V2<T>{un[2] * uJ + p * J[1] - tj[1], un[3] * uJ + p * J[2] - tj[2]};
+        sR[frow(d & 1, 2)][tq] = V2<T>{(un[4] + p) * uJ - tw - (T(a.ph.kappa) * qj + zc * gj),
+                                       un[5] * uJ - T(a.ph.gam * a.ph.beta) * gj};
+    };
+    __syncthreads();
+    if (act) put_flux(0);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        __syncthreads();
+        if (act) {
+            if (d < 2) put_flux(d + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            const V2<T> *r0 = sR[frow(d & 1, 0)], *r1 = sR[frow(d & 1, 1)], *r2 = sR[frow(d & 1, 2)];
+            const int id = d == 0 ? i : (d == 1 ? j : k);
+            const int str = d == 0 ? 1 : (d == 1 ? P : P * P);
+            const int lo = base + nd - id * str;
+            T D[P];
+            B.row(B.Dh + id * B.PS, D);
+#pragma unroll
+            for (int l = 0; l < P; ++l) {
+                const V2<T> x = r0[lo + l * str], y = r1[lo + l * str], z = r2[lo + l * str];
+                acc[0] += D[l] * x.x;
+                acc[1] += D[l] * x.y;
+                acc[2] += D[l] * y.x;
+                acc[3] += D[l] * y.y;
+                acc[4] += D[l] * z.x;
+                acc[5] += D[l] * z.y;
+                if (l % 2 == 1) bound(acc, 6);
+            }
+        }
+    }
+    // the volume part W = S - iJ acc of U_t, into the register (RK) or the
+    // output (U_t alone); k_update adds the surface part
+    if (!act) return;
+    const T A = T(L.A), dt = T(a.dt);
+#pragma unroll
+    for (int v = 0; v < 6; ++v) {
+        const T W = -acc[v] * iJ + S[v];
+        if (L.mode == 0) gst(a.Ut + (v) * a.NN, g32, W);
+        else gst(a.R + (v) * a.NN, g32, L.first ? dt * W : A * Rn[v] + dt * W);
     }
 }
 
@@ -1598,268 +1856,89 @@ __global__ __launch_bounds__(BS) void k_update(Launch<T> L)
     using G = Tile<P, BS>;
     Inst<T> a;
     int e0;
-    instance_of<T, BATCH>(L, a, e0, G::EPB);
-    // sF: primitives; contravariant fluxes (even directions); new state.
-    // sB: BR1 face values of the primitives [5][NF], then the contravariant
-    // fluxes of the odd direction [6][NV].
-    constexpr int kB = 5 * G::NF > 6 * G::NV ? 5 * G::NF : 6 * G::NV;
-    __shared__ T sF[6][G::NV];
-    __shared__ T sB[kB];
-    __shared__ T sFs[6][G::NF];    // surface flux (F* . n) dS
-    // curved elements: the metrics of every node and n dS of every face point
-    constexpr int NJ = CV ? 9 : 1, NQ = CV ? 3 : 1, NJV = CV ? G::NV : 1, NQF = CV ? G::NF : 1;
-    __shared__ T sJa[NJ][NJV];
-    __shared__ T sN[NQ][NQF];
-    T(*sS)[G::NF] = reinterpret_cast<T(*)[G::NF]>(sB);
-    T(*sF2)[G::NV] = reinterpret_cast<T(*)[G::NV]>(sB);
-    __shared__ T sDh[P * P], sL[2 * P], sLh[2 * P];
-    load_basis<P>(L.bas, sDh, sL, sLh);
+    instance_of<T, BATCH>(L, a, e0, G::EPB, blockIdx.x);
+    __shared__ V2<T> sF[3][G::NV];     // new state
+    __shared__ V2<T> sFs[3][G::NF];    // surface flux (F* . n) dS
+    __shared__ BasisS<P, T> B;
+    B.load(L.bas);
     const int E = a.mesh.E;
     const int t = threadIdx.x;
-    const int le = t / G::n3, nd = t - le * G::n3;
+    const NodeTask<G> nt(t);
+    const int le = nt.le, nd = nt.nd, tq = nt.q;
     const int e = e0 + le;
-    const bool act = t < G::NV && e < E;
-    const size_t g = (size_t)e0 * G::n3 + t;
+    const bool act = nt.in && e < E;
+    const size_t g = (size_t)e0 * G::n3 + tq;
     const uint32_t g32 = (uint32_t)g;
     const size_t NF = (size_t)E * 6 * G::n2;
-    const T *TUr = a.TU + (size_t)L.tb * 6 * NF;
 
-    // face tasks (one face point per thread, a second round where the block
-    // has more face points than threads); the first round's traces are
-    // requested before the node loads so that both are in flight together
-    struct Tr {
-        int nb;
-        T uo[6], un[6], G[7], Gn[7];
-    };
-    auto load_tr = [&](int task, Tr &r) {
-        const FaceTask<P> ft(task);
-        const int el = e0 + ft.le;
-        r.nb = -1;
-        if (el >= E) return;
-        const FaceIx<G::n2> o((size_t)el * 6 + ft.f, ft.fp);
-        r.nb = gld(a.mesh.nbr, el * 6 + ft.f);
-#pragma unroll
-        for (int v = 0; v < 6; ++v) r.uo[v] = TUr[o.at(6, v)];
-#pragma unroll
-        for (int v = 0; v < 6; ++v) r.G[v] = a.TF[o.at(7, v)];
-        if (r.nb >= 0) {
-            const FaceIx<G::n2> on(nbr_face<P>(r.nb), nbr_point<P>(r.nb, ft.fp));
-            r.G[6] = a.TF[o.at(7, 6)];
-#pragma unroll
-            for (int v = 0; v < 7; ++v) r.Gn[v] = a.TF[on.at(7, v)];
-#pragma unroll
-            for (int v = 0; v < 6; ++v) r.un[v] = TUr[on.at(6, v)];
-        }
-    };
-    // (only where one round covers the block: holding a round's traces across
-    // the node loads costs too many registers otherwise)
-    constexpr bool kEarly = G::NF <= BS;
-    Tr tr0;
-    if (kEarly && t < G::NF) load_tr(t, tr0);
-    Pt<T> s;
-    T iJn = T(0);
-    if (act) {
-        if constexpr (CV) iJn = stage_node_metrics<T, NJV>(a.mesh, a.NN, g, t, sJa);
-        s.rho = gldn<NT>(a.U + (0) * a.NN, g32);
-        s.m[0] = gldn<NT>(a.U + (1) * a.NN, g32);
-        s.m[1] = gldn<NT>(a.U + (2) * a.NN, g32);
-        s.m[2] = gldn<NT>(a.U + (3) * a.NN, g32);
-        s.E = gldn<NT>(a.U + (4) * a.NN, g32);
-        s.c = gldn<NT>(a.U + (5) * a.NN, g32);
-        const T u6[6] = {s.rho, s.m[0], s.m[1], s.m[2], s.E, s.c};
-        T w[5];
-        primitives(u6, w);
-#pragma unroll
-        for (int k = 0; k < 5; ++k) sF[k][t] = w[k];
-    }
-    // per face point: BR1 face values of the primitives, and the Rusanov +
-    // central viscous flux (F* . n) dS from both sides' traces (the own
-    // side's conserved trace is the prolongation of the current state,
-    // written by the previous stage)
+    // per face point: (F* . n) dS, the difference of the two sides' flux
+    // traces (the wall flux on walls)
     for (int task = t; task < G::NF; task += BS) {
         const FaceTask<P> ft(task);
-        const int el = e0 + ft.le, f = ft.f;
+        const int el = e0 + ft.le;
         if (el >= E) continue;
-        Tr tr;
-        if (kEarly) tr = tr0; else load_tr(task, tr);
-        // the surface element always; the normal where it is used (walls,
-        // model 2's HLLC, the lifting's n dS on curved elements)
-        T n[3] = {T(0), T(0), T(0)}, dS;
-        if (CV || tr.nb < 0 || a.ph.model == 2)
-            face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp, n, dS);
-        else
-            dS = face_dS<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp);
-        const int slot = ft.le * 6 * G::n2 + f * G::n2 + ft.fp;
-        if constexpr (CV) {
+        const FaceIx<G::n2> o((size_t)el * 6 + ft.f, ft.fp);
+        const int nb = gld(a.mesh.nbr, el * 6 + ft.f);
+        T K[6], Kn[6];
 #pragma unroll
-            for (int m = 0; m < 3; ++m) sN[m][slot] = n[m] * dS;
+        for (int v = 0; v < 6; ++v) K[v] = a.TF[o.at(6, v)];
+        if (nb >= 0) {
+            const FaceIx<G::n2> on(nbr_face<P>(nb), nbr_point<P>(nb, ft.fp));
+#pragma unroll
+            for (int v = 0; v < 6; ++v) Kn[v] = a.TF[on.at(6, v)];
+#pragma unroll
+            for (int v = 0; v < 6; ++v) K[v] -= Kn[v];
         }
-        T w[5];
-        primitives(tr.uo, w);
-        if (tr.nb >= 0 && a.ph.model == 2) {
-            // HLLC on the convective part, central viscous flux: the traces
-            // hold p_alpha, -F^V.n (own normal) and the sound speed
-            // (face values and the viscous part go to LDS first, so that
-            // they are not held in registers across the HLLC arithmetic)
-            T wn[5];
-            primitives(tr.un, wn);
+        const int slot = ft.le * 6 * G::n2 + ft.f * G::n2 + ft.fp;
 #pragma unroll
-            for (int k = 0; k < 5; ++k) sS[k][slot] = T(0.5) * (w[k] + wn[k]);
+        for (int v = 0; v < 3; ++v) sFs[v][slot] = V2<T>{K[2 * v], K[2 * v + 1]};
+    }
+    // this node's state and register (and compensation of an FP32 instance)
+    T u6[6], Rn[6], Cn[6], iJ = T(0);
+    const bool rk = L.mode == 1;
+    if (act) {
+        T *R = rk ? a.R : a.Ut;  // holds the volume part
 #pragma unroll
-            for (int v = 1; v < 6; ++v) sFs[v][slot] = T(0.5) * (tr.G[v] - tr.Gn[v]) * dS;
-            T Fc[6];
-            hllc(tr.uo, tr.G[0], tr.G[6], tr.un, tr.Gn[0], tr.Gn[6], n, Fc);
-            sFs[0][slot] = Fc[0] * dS;
-#pragma unroll
-            for (int v = 1; v < 6; ++v) sFs[v][slot] += Fc[v] * dS;
-            continue;
-        } else if (tr.nb >= 0) {
-            T wn[5];
-            const T lam = tr.G[6] > tr.Gn[6] ? tr.G[6] : tr.Gn[6];
+        for (int v = 0; v < 6; ++v) Rn[v] = gldn<NT>(R + (v) * a.NN, g32);
+        if (rk) {
 #pragma unroll
             for (int v = 0; v < 6; ++v) {
-                const T Fn = T(0.5) * (tr.G[v] - tr.Gn[v]) - T(0.5) * lam * (tr.un[v] - tr.uo[v]);
-                sFs[v][slot] = Fn * dS;
+                u6[v] = gldn<NT>(a.U + (v) * a.NN, g32);
+                if constexpr (sizeof(T) == 4) Cn[v] = a.Ck ? gldn<NT>(a.Ck + (v) * a.NN, g32) : T(0);
             }
-            primitives(tr.un, wn);
-#pragma unroll
-            for (int k = 0; k < 5; ++k) w[k] = T(0.5) * (w[k] + wn[k]);
-        } else {
-#pragma unroll
-            for (int v = 0; v < 6; ++v) sFs[v][slot] = tr.G[v] * dS;
-            wall_primitives(a.mesh, el, f, n, w);
         }
-#pragma unroll
-        for (int k = 0; k < 5; ++k) sS[k][slot] = w[k];
+        if constexpr (CV) iJ = T(1) / gld((const T *)a.mesh.nmet + 9 * a.NN, g32);
+        else iJ = em_at<G::kUni, T>(a.mesh, e, kEmIJ);
     }
     __syncthreads();
-    // lifted gradients, temperature, pressure and the point-wise source
-    T S[6] = {T(0), T(0), T(0), T(0), T(0), T(0)}, iJ = T(0);
-    T Fx[6][3];
-    const int i = nd % P, j = (nd / P) % P, k = nd / (P * P);
-    const int base = le * G::n3;
-    if (act) {
-#pragma unroll
-        for (int m = 0; m < 3; ++m) s.gT[m] = gldn<NT>(a.G2 + (m) * a.NN, g32);
-        s.lapc = gldn<NT>(a.G2 + (3) * a.NN, g32);
-        T grho[3];
-        if constexpr (CV) {
-            T q[5][3];
-            lifted_grads_curved<P, 5, G::NV, G::NF>(sF, sS, sJa, sN, base, le * 6 * G::n2, i, j, k, sDh, sLh, iJn, q);
-            iJ = iJn;
-#pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                grho[m] = q[0][m];
-                s.gu[0][m] = q[1][m];
-                s.gu[1][m] = q[2][m];
-                s.gu[2][m] = q[3][m];
-                s.gc[m] = q[4][m];
-            }
-        } else {
-            T gd[5][3];
-            lifted_grads<P, 5>(sF, sS, base, le * 6 * G::n2, i, j, k, sDh, sLh, gd);
-            T Ja[9];
-            element_metrics(a.mesh, metric_element<G::EPB, G::n3>(e0, e), Ja, iJ);
-            to_physical(Ja, iJ, gd[0], grho);
-#pragma unroll
-            for (int jj = 0; jj < 3; ++jj) to_physical(Ja, iJ, gd[1 + jj], s.gu[jj]);
-            to_physical(Ja, iJ, gd[4], s.gc);
-        }
-        // the temperature stays FP64 through the pressure in both precisions
-        const double Tn = temperature<fast_fp64<T>()>(a.ph, (double)s.rho, (double)s.m[0], (double)s.m[1],
-                                                      (double)s.m[2], (double)s.E, (double)s.c, (double)s.gc[0],
-                                                      (double)s.gc[1], (double)s.gc[2]);
-        double pd, cs2;
-        eos<fast_fp64<T>()>(a.ph, (double)s.rho, Tn, pd, cs2);
-        s.p = T(pd + 0.5 * a.ph.ap * (double)s.rho * (double)s.rho);  // p_alpha for model 2
-        s.ir = T(1) / s.rho;
-        source(a.ph, s, grho, S);
-        flux_tensor(a.ph, s, Fx);
-    }
-    // the RK register (and the compensation of an FP32 instance) of this
-    // node, requested now so that the loads complete during the volume
-    // integral
-    T Rn[6], Cn[6];
-    if (L.mode == 1 && act) {
-#pragma unroll
-        for (int v = 0; v < 6; ++v) {
-            Rn[v] = L.first ? T(0) : gldn<NT>(a.R + (v) * a.NN, g32);
-            if constexpr (sizeof(T) == 4) Cn[v] = a.Ck ? gldn<NT>(a.Ck + (v) * a.NN, g32) : T(0);
-        }
-    }
-    // volume integral sum_d Dhat_d (Ja^d . F): the contravariant fluxes of
-    // direction d go to buffer d & 1, so direction d+1 is written while
-    // direction d is read, one barrier per direction
     T acc[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
-    auto put_flux = [&](int d, T (*buf)[G::NV]) {
-        T Jd[3];
-        if constexpr (CV) {
-            Jd[0] = sJa[3 * d][t];
-            Jd[1] = sJa[3 * d + 1][t];
-            Jd[2] = sJa[3 * d + 2][t];
-        } else {
-            const uint32_t eq = (uint32_t)metric_element<G::EPB, G::n3>(e0, e) * 10 + 3 * d;
-            Jd[0] = T(gld(a.mesh.emet, eq));
-            Jd[1] = T(gld(a.mesh.emet, eq + 1));
-            Jd[2] = T(gld(a.mesh.emet, eq + 2));
-        }
-#pragma unroll
-        for (int v = 0; v < 6; ++v) buf[v][t] = Jd[0] * Fx[v][0] + Jd[1] * Fx[v][1] + Jd[2] * Fx[v][2];
-    };
-    __syncthreads();
-    if (act) put_flux(0, sF);
-#pragma unroll 1
-    for (int d = 0; d < 3; ++d) {
-        __syncthreads();
-        if (act) {
-            if (d < 2) put_flux(d + 1, (d & 1) ? sF : sF2);
-            __builtin_amdgcn_sched_barrier(0);
-            const T(*buf)[G::NV] = (d & 1) ? sF2 : sF;
-            // the line through this node along d, addressed branch-free:
-            // node l is lo + l * str
-            const int id = d == 0 ? i : (d == 1 ? j : k);
-            const int str = d == 0 ? 1 : (d == 1 ? P : P * P);
-            const int lo = base + nd - id * str;
-#pragma unroll
-            for (int l = 0; l < P; ++l) {
-                const T D = T(sDh[id * P + l]);
-#pragma unroll
-                for (int v = 0; v < 6; ++v) acc[v] += D * buf[v][lo + l * str];
-            }
-        }
-    }
     if (act) {
+        const int i = nd % P, j = (nd / P) % P, k = nd / (P * P);
         const int idx[3] = {i, j, k};
         const int fpd[3] = {j + P * k, i + P * k, i + P * j};
         const int fbase = le * 6 * G::n2;
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            const int id = idx[d];
-            const T lp = T(sLh[P + id]), lm = T(sLh[id]);
+            const V2<T> lh = B.Lh[idx[d]];
 #pragma unroll
-            for (int v = 0; v < 6; ++v)
-                acc[v] += lp * sFs[v][fbase + (2 * d + 1) * G::n2 + fpd[d]] +
-                          lm * sFs[v][fbase + (2 * d) * G::n2 + fpd[d]];
+            for (int v = 0; v < 3; ++v) {
+                const V2<T> fp = sFs[v][fbase + (2 * d + 1) * G::n2 + fpd[d]], fm = sFs[v][fbase + (2 * d) * G::n2 + fpd[d]];
+                acc[2 * v] += lh.y * fp.x + lh.x * fm.x;
+                acc[2 * v + 1] += lh.y * fp.y + lh.x * fm.y;
+            }
+        }
+        if (!rk) {
+#pragma unroll
+            for (int v = 0; v < 6; ++v) gst(a.Ut + (v) * a.NN, g32, Rn[v] - acc[v] * iJ);
         }
     }
-    T Ut[6];
-#pragma unroll
-    for (int v = 0; v < 6; ++v) Ut[v] = -acc[v] * iJ + S[v];
-    if (L.mode == 0) {
-        if (act) {
-#pragma unroll
-            for (int v = 0; v < 6; ++v) gst(a.Ut + (v) * a.NN, g32, T(Ut[v]));
-        }
-        return;
-    }
+    if (!rk) return;
     // low-storage RK stage
-    __syncthreads();
     if (act) {
-        const T A = T(L.A), B = T(L.B), dt = T(a.dt);
-        T u6[6] = {s.rho, s.m[0], s.m[1], s.m[2], s.E, s.c};
+        const T B = T(L.B), dJ = T(a.dt) * iJ;
 #pragma unroll
         for (int v = 0; v < 6; ++v) {
-            const T r = L.first ? dt * Ut[v] : A * Rn[v] + dt * Ut[v];
+            const T r = Rn[v] - dJ * acc[v];
             if (!L.last) gstn<NT>(a.R + (v) * a.NN, g32, T(r));
             T u;
             if (sizeof(T) == 4 && a.Ck) {
@@ -1872,8 +1951,10 @@ __global__ __launch_bounds__(BS) void k_update(Launch<T> L)
                 u = u6[v] + B * r;
             }
             gstn<NT>(a.U + (v) * a.NN, g32, T(u));
-            sF[v][t] = u;
+            u6[v] = u;
         }
+#pragma unroll
+        for (int v = 0; v < 3; ++v) sF[v][tq] = V2<T>{u6[2 * v], u6[2 * v + 1]};
     }
     __syncthreads();
     const int ltask = line_of_thread<P, BS>(t);
@@ -1885,7 +1966,7 @@ __global__ __launch_bounds__(BS) void k_update(Launch<T> L)
         const int b2 = lt.le * G::n3;
         T um[6], up[6];
 #pragma unroll
-        for (int v = 0; v < 6; ++v) prolong2<P>(sF[v], b2, sL, lt, um[v], up[v]);
+        for (int v = 0; v < 3; ++v) prolong2<P, T>(sF[v], b2, B, lt, um + 2 * v, up + 2 * v);
 #pragma unroll
         for (int sd = 0; sd < 2; ++sd) {
             const FaceIx<G::n2> o((size_t)el * 6 + 2 * lt.d + sd, lt.fp);

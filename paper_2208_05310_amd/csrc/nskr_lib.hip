@@ -33,11 +33,13 @@ struct nskr_ctx {
     int E = 0;
     size_t NN = 0, NF = 0;
     int *d_nbr = nullptr, *d_bcid = nullptr;
-    double *d_emet = nullptr, *d_fmet = nullptr, *d_egeo = nullptr;
+    double *d_emet = nullptr, *d_egeo = nullptr;
+    void *d_em = nullptr;        // per-element records of the stage kernels (element type)
     bool curved = false;         // some element is not affine: per-node metrics
     void *d_nmet = nullptr, *d_fnrm = nullptr;  // curved: node metrics, face-point normals (element type)
     double *d_xnode = nullptr;   // curved: node coordinates
     BcDev *d_bcs = nullptr;
+    int wall = 0;                // some face is a wall
     int dyn = 0;                 // a Navier-slip wall with gamma_1 != 0
     double *d_stab = nullptr;    // wall-temperature table (walls with a temperature gradient)
     int var = 0;                 // some wall has a temperature gradient or rate
@@ -81,9 +83,8 @@ static hipEvent_t take_event(nskr_ctx *c)
 // Launch one stage kernel.  With profiling on, the event pair rides on the
 // dispatch itself, so the recorded interval is the kernel's own begin-to-end
 // time (no dispatch gap, no marker packets between kernels).
-template <typename T>
-static void stage_launch(nskr_ctx *c, int kind, void (*kern)(Launch<T>), unsigned grid, unsigned block,
-                         hipStream_t s, const Launch<T> &L)
+template <typename K, typename... A>
+static void stage_launch(nskr_ctx *c, int kind, K kern, unsigned grid, unsigned block, hipStream_t s, const A &...args)
 {
     hipEvent_t a = nullptr, b = nullptr;
     if (c->prof) {
@@ -91,13 +92,13 @@ static void stage_launch(nskr_ctx *c, int kind, void (*kern)(Launch<T>), unsigne
         b = take_event(c);
     }
     if (a && b) {
-        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, s, a, b, 0, L);
+        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, s, a, b, 0, args...);
         c->prof_events.push_back({kind, {a, b}});
         return;
     }
     if (a) c->event_pool.push_back(a);
     if (b) c->event_pool.push_back(b);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, s, L);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, s, args...);
 }
 
 static const char *g_null_msg = "nskr: null context";
@@ -688,8 +689,8 @@ template <int P, typename T, int BS, bool CV> struct Impl {
     static MeshDev mesh(const nskr_ctx *c)
     {
         MeshDev m;
-        m.E = c->E; m.nbr = c->d_nbr; m.bcid = c->d_bcid; m.emet = c->d_emet; m.fmet = c->d_fmet;
-        m.egeo = c->d_egeo; m.bcs = c->d_bcs; m.dyn = c->dyn; m.stab = c->d_stab; m.var = c->var;
+        m.E = c->E; m.nbr = c->d_nbr; m.bcid = c->d_bcid; m.emet = c->d_emet; m.em = c->d_em;
+        m.egeo = c->d_egeo; m.bcs = c->d_bcs; m.wall = c->wall; m.dyn = c->dyn; m.stab = c->d_stab; m.var = c->var;
         m.nmet = c->d_nmet; m.fnrm = c->d_fnrm; m.xnode = c->d_xnode;
         return m;
     }
@@ -717,47 +718,56 @@ template <int P, typename T, int BS, bool CV> struct Impl {
     // every stage kernel's static LDS fits the device's per-block limit
     static int fits(int maxlds)
     {
-        const void *fns[] = {reinterpret_cast<const void *>(&k_prolong<P, T, BS, false>),
-                             reinterpret_cast<const void *>(&k_lift1<P, T, BS, false, false, CV>),
-                             reinterpret_cast<const void *>(&k_lift1<P, T, BS, false, true, CV>),
-                             reinterpret_cast<const void *>(&k_lift2<P, T, BS, false, CV>),
-                             reinterpret_cast<const void *>(&k_update<P, T, BS, false, CV, false>),
-                             reinterpret_cast<const void *>(&k_update<P, T, BS, false, CV, true>)};
-        for (const void *f : fns) {
+        constexpr int n2 = Lift2Tile<P, BS>::NT;
+        const std::pair<const void *, int> fns[] = {
+            {reinterpret_cast<const void *>(&k_prolong<P, T, BS, false>), BS},
+            {reinterpret_cast<const void *>(&k_lift1<P, T, BS, false, false, CV>), BS},
+            {reinterpret_cast<const void *>(&k_lift1<P, T, BS, false, true, CV>), BS},
+            {reinterpret_cast<const void *>(&k_lift2<P, T, BS, false, CV, true>), n2},
+            {reinterpret_cast<const void *>(&k_lift2<P, T, BS, false, CV, false>), n2},
+            {reinterpret_cast<const void *>(&k_update<P, T, BS, false, CV, false>), BS},
+            {reinterpret_cast<const void *>(&k_update<P, T, BS, false, CV, true>), BS}};
+        for (const auto &f : fns) {
             hipFuncAttributes at;
-            if (hipFuncGetAttributes(&at, f) != hipSuccess) return 0;
-            if ((int)at.sharedSizeBytes > maxlds || at.maxThreadsPerBlock < BS) return 0;
+            if (hipFuncGetAttributes(&at, f.first) != hipSuccess) return 0;
+            if ((int)at.sharedSizeBytes > maxlds || at.maxThreadsPerBlock < f.second) return 0;
         }
         return 1;
     }
     // single-instance launches
     static void prolong(nskr_ctx *c, const Launch<T> &L, hipStream_t s)
     {
-        stage_launch<T>(c, 0, &k_prolong<P, T, BS, false>, nblk(c), BS, s, L);
+        stage_launch(c, 0, &k_prolong<P, T, BS, false>, nblk(c), BS, s, L);
     }
     static void lift1(nskr_ctx *c, const Launch<T> &L, hipStream_t s)
     {
         if (L.full)
-            stage_launch<T>(c, 1, &k_lift1<P, T, BS, false, true, CV>, nblk(c), BS, s, L);
+            stage_launch(c, 1, &k_lift1<P, T, BS, false, true, CV>, nblk(c), BS, s, L);
         else
-            stage_launch<T>(c, 1, &k_lift1<P, T, BS, false, false, CV>, nblk(c), BS, s, L);
+            stage_launch(c, 1, &k_lift1<P, T, BS, false, false, CV>, nblk(c), BS, s, L);
     }
     static void lift2(nskr_ctx *c, const Launch<T> &L, hipStream_t s)
     {
-        stage_launch<T>(c, 2, &k_lift2<P, T, BS, false, CV>, nblk(c), BS, s, L);
+        using Q = Lift2Tile<P, BS>;
+        const int n = nblk(c);
+        if (c->wall)
+            stage_launch(c, 2, &k_lift2<P, T, BS, false, CV, true>, Q::grid(n), Q::NT, s, L, n);
+        else
+            stage_launch(c, 2, &k_lift2<P, T, BS, false, CV, false>, Q::grid(n), Q::NT, s, L, n);
     }
     static void update(nskr_ctx *c, const Launch<T> &L, hipStream_t s)
     {
         if (c->stream_nodes)
-            stage_launch<T>(c, 3, &k_update<P, T, BS, false, CV, true>, nblk(c), BS, s, L);
+            stage_launch(c, 3, &k_update<P, T, BS, false, CV, true>, nblk(c), BS, s, L);
         else
-            stage_launch<T>(c, 3, &k_update<P, T, BS, false, CV, false>, nblk(c), BS, s, L);
+            stage_launch(c, 3, &k_update<P, T, BS, false, CV, false>, nblk(c), BS, s, L);
     }
     // batched launches over a group table
     // one RK step of every instance of a group; the face traces of the first
     // stage come from the previous step's last update (or from prime())
-    static void step_batched(const Launch<T> &L0, int nblocks, hipStream_t s)
+    static void step_batched(const Launch<T> &L0, int nblocks, bool wall, hipStream_t s)
     {
+        using Q = Lift2Tile<P, BS>;
         Launch<T> L = L0;
         for (int st = 0; st < 5; ++st) {
             L.mode = 1;
@@ -769,7 +779,10 @@ template <int P, typename T, int BS, bool CV> struct Impl {
             L.tw = kTraceBuf[st + 1];
             L.cs = kRkC[st];
             hipLaunchKernelGGL((k_lift1<P, T, BS, true, false, CV>), dim3(nblocks), dim3(BS), 0, s, L);
-            hipLaunchKernelGGL((k_lift2<P, T, BS, true, CV>), dim3(nblocks), dim3(BS), 0, s, L);
+            if (wall)
+                hipLaunchKernelGGL((k_lift2<P, T, BS, true, CV, true>), dim3(Q::grid(nblocks)), dim3(Q::NT), 0, s, L, nblocks);
+            else
+                hipLaunchKernelGGL((k_lift2<P, T, BS, true, CV, false>), dim3(Q::grid(nblocks)), dim3(Q::NT), 0, s, L, nblocks);
             hipLaunchKernelGGL((k_update<P, T, BS, true, CV>), dim3(nblocks), dim3(BS), 0, s, L);
         }
     }
@@ -838,6 +851,7 @@ template <int P, typename T, int BS, bool CV> struct Impl {
     {
         Launch<T> L = launch(c, inst(c, U, nullptr, nullptr, 0.0));
         L.full = 1;  // every lifted gradient and the nodal temperature
+        L.mode = 2;
         prolong(c, L, s);
         lift1(c, L, s);
         lift2(c, L, s);
@@ -1258,13 +1272,14 @@ int nskr_create(const nskr_params *p, int N, int device, nskr_ctx **out)
 
 static void free_mesh(nskr_ctx *c)
 {
-    void *ptrs[] = {c->d_nbr, c->d_bcid, c->d_emet, c->d_fmet, c->d_egeo, c->d_bcs, c->d_Q, c->d_TH,
+    void *ptrs[] = {c->d_nbr, c->d_bcid, c->d_emet, c->d_em, c->d_egeo, c->d_bcs, c->d_Q, c->d_TH,
                     c->d_G2, c->d_T2, c->d_TF, c->d_TU, c->d_part, c->d_out, c->d_noise, c->d_drop, c->d_Ck,
                     c->d_stab, c->d_clk, c->d_nmet, c->d_fnrm, c->d_xnode, c->d_bmap};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     c->d_nbr = c->d_bcid = nullptr;
-    c->d_emet = c->d_fmet = c->d_egeo = nullptr;
+    c->d_emet = c->d_egeo = nullptr;
+    c->d_em = nullptr;
     c->d_nmet = c->d_fnrm = nullptr;
     c->d_xnode = nullptr;
     c->curved = false;
@@ -1349,7 +1364,7 @@ int nskr_mesh_upload(nskr_ctx *c, const nskr_mesh *m, nskr_stream sv)
     // offsets from a per-field base: every such array stays below 4 GiB
     {
         const double tsz = c->p.precision == 0 ? 8.0 : 4.0, nn = (double)E * n3;
-        const double worst = fmax(fmax(nn * 8.0, (double)E * 24 * 8), (double)E * 6 * n2 * 4 * tsz);
+        const double worst = fmax(fmax(nn * 8.0, (double)E * kEm * 8), (double)E * 6 * n2 * 4 * tsz);
         if (worst >= 4294967296.0)
             return fail(c, NSKR_E_UNSUPPORTED, "mesh too large for one context (a node or face-point array exceeds "
                                                "4 GiB); split it into several instances");
@@ -1637,9 +1652,11 @@ int nskr_mesh_upload(nskr_ctx *c, const nskr_mesh *m, nskr_stream sv)
         }
     // connectivity codes: (6 nb + nf) 8 + orientation, -1 on walls
     std::vector<int> code((size_t)E * 6);
+    int wall = 0;
     for (int e = 0; e < E; ++e)
         for (int f = 0; f < 6; ++f) {
             const int nb = m->nbr[e * 6 + f];
+            if (nb < 0) wall = 1;
             code[(size_t)e * 6 + f] = nb < 0 ? -1 : ((nb * 6 + m->nbr_face[e * 6 + f]) << 3) | orient(e, f);
         }
     // wall constants
@@ -1689,6 +1706,7 @@ int nskr_mesh_upload(nskr_ctx *c, const nskr_mesh *m, nskr_stream sv)
     const std::vector<double> *tab = var ? &wall_table_host(vdw) : nullptr;
     free_mesh(c);
     c->E = E;
+    c->wall = wall;
     c->dyn = dyn;
     c->var = var;
     c->trate = trate;
@@ -1702,11 +1720,11 @@ int nskr_mesh_upload(nskr_ctx *c, const nskr_mesh *m, nskr_stream sv)
     c->curved = curved;
     if (curved) c->bs = 256;  // the only workgroup size built for curved elements
     int rc = NSKR_OK;
-    const size_t n_emet = curved ? 0 : emet.size(), n_fmet = curved ? 0 : fmet.size();
+    const size_t n_emet = curved ? 0 : emet.size(), n_em = curved ? 0 : (size_t)E * kEm;
     if ((rc = dalloc(c, (void **)&c->d_nbr, sizeof(int) * E * 6)) ||
         (rc = dalloc(c, (void **)&c->d_bcid, sizeof(int) * E * 6)) ||
         (!curved && (rc = dalloc(c, (void **)&c->d_emet, sizeof(double) * n_emet))) ||
-        (!curved && (rc = dalloc(c, (void **)&c->d_fmet, sizeof(double) * n_fmet))) ||
+        (!curved && (rc = dalloc(c, &c->d_em, ts * n_em))) ||
         (rc = dalloc(c, (void **)&c->d_egeo, sizeof(double) * egeo.size())) ||
         (curved && (rc = dalloc(c, &c->d_nmet, ts * nmet.size()))) ||
         (curved && (rc = dalloc(c, &c->d_fnrm, ts * fnrm.size()))) ||
@@ -1714,7 +1732,7 @@ int nskr_mesh_upload(nskr_ctx *c, const nskr_mesh *m, nskr_stream sv)
         (rc = dalloc(c, (void **)&c->d_bcs, sizeof(BcDev) * bcs.size())) ||
         (rc = dalloc(c, &c->d_Q, ts * 15 * c->NN)) || (rc = dalloc(c, &c->d_TH, ts * c->NN)) ||
         (rc = dalloc(c, &c->d_G2, ts * 4 * c->NN)) || (rc = dalloc(c, &c->d_T2, ts * (ts == 4 ? kT2<float>() : kT2<double>()) * c->NF)) ||
-        (rc = dalloc(c, &c->d_TF, ts * 7 * c->NF)) || (rc = dalloc(c, &c->d_TU, ts * 3 * 6 * c->NF)) ||
+        (rc = dalloc(c, &c->d_TF, ts * 6 * c->NF)) || (rc = dalloc(c, &c->d_TU, ts * 3 * 6 * c->NF)) ||
         (rc = dalloc(c, (void **)&c->d_part, sizeof(double) * NSKR_NSUMS * (size_t)nblk)) ||
         (rc = dalloc(c, (void **)&c->d_out, sizeof(double) * NSKR_NSUMS)) ||
         (c->p.precision == 1 && c->p.kahan && (rc = dalloc(c, &c->d_Ck, ts * 6 * c->NN))) ||
@@ -1735,7 +1753,14 @@ int nskr_mesh_upload(nskr_ctx *c, const nskr_mesh *m, nskr_stream sv)
     HIPCHK(c, hipMemcpy(c->d_bcid, m->bc, sizeof(int) * E * 6, hipMemcpyHostToDevice));
     if (!curved) {
         HIPCHK(c, hipMemcpy(c->d_emet, emet.data(), sizeof(double) * emet.size(), hipMemcpyHostToDevice));
-        HIPCHK(c, hipMemcpy(c->d_fmet, fmet.data(), sizeof(double) * fmet.size(), hipMemcpyHostToDevice));
+        std::vector<double> em(n_em, 0.0);
+        for (int e = 0; e < E; ++e) {
+            double *r = &em[(size_t)e * kEm];
+            for (int q = 0; q < 24; ++q) r[q] = fmet[(size_t)e * 24 + q];
+            for (int q = 0; q < 9; ++q) r[kEmJa + q] = emet[(size_t)e * 10 + q];
+            r[kEmIJ] = 1.0 / emet[(size_t)e * 10 + 9];
+        }
+        HIPCHK(c, upload_real(c->d_em, em));
     } else {
         HIPCHK(c, upload_real(c->d_nmet, nmet));
         HIPCHK(c, upload_real(c->d_fnrm, fnrm));
@@ -2037,6 +2062,7 @@ struct BatchSlot {
 };
 
 struct BatchGroup {
+    bool wall = false;     // some member has walls
     int N = 0, prec = 0, bs = 0, nblocks = 0;
     bool curved = false;
     void *d_tab = nullptr;
@@ -2112,6 +2138,7 @@ static int build_group(nskr_batch *b, BatchGroup &g, const std::vector<int> &mem
         tab.push_back(Impl<P, T, BS, CV>::inst(sl.c, sl.U, sl.R, nullptr, sl.dt));
         tab.back().clk = sl.c->trate ? sl.c->d_clk : nullptr;
         tab.back().t0 = sl.t0;
+        if (sl.c->wall) g.wall = true;
         const int nb = (sl.c->E + G::EPB - 1) / G::EPB;
         for (int j = 0; j < nb; ++j) {
             bi.push_back((int)k);
@@ -2137,7 +2164,7 @@ template <int P, typename T, int BS, bool CV> static void launch_group(const Bat
     L.blk_inst = g.d_bi;
     L.blk_e0 = g.d_be;
     L.bas = g.bas;
-    Impl<P, T, BS, CV>::step_batched(L, g.nblocks, s);
+    Impl<P, T, BS, CV>::step_batched(L, g.nblocks, g.wall, s);
 }
 
 template <typename F> static int group_dispatch(const BatchGroup &g, F &&f)
