@@ -332,16 +332,14 @@ int nskr_reduce(nskr_ctx *ctx, const void *U, double *out, nskr_stream s);
 int nskr_set_profiling(nskr_ctx *ctx, int on);
 int nskr_profile(nskr_ctx *ctx, double *ms, long *count, nskr_stream s);
 
-/* Threads per workgroup of the stage kernels: 256, 512, or the degree's
+/* Nominal tile of the stage kernels, as threads: 256, 512, or the degree's
  * tight size that packs whole elements into waves (N = 2: 192, N = 3 and 4:
- * 128, N = 5: 448); a block must hold at least one element.  Default: 128 at
- * N = 3, 256 otherwise.  This is the tile
- * shape (elements per workgroup) the autotuner chooses.  Results do not
- * depend on it (every element's arithmetic is the same in any tile).  A mesh
- * with curved elements runs 256 threads (its upload sets 256).
+ * 128, N = 5: 448); a tile must hold at least one element.  Default: 128 at
+ * N = 3, 256 otherwise.  The value is checked and kept; each stage kernel
+ * sizes its own workgroups for the degree, so neither results nor speed
+ * depend on it.  A mesh with curved elements takes 256 (its upload sets it).
  * Errors: NSKR_E_ARG for other values; NSKR_E_UNSUPPORTED for another size on
- * a mesh with curved elements or where the kernels exceed the LDS per
- * workgroup. */
+ * a mesh with curved elements. */
 int nskr_set_block(nskr_ctx *ctx, int threads);
 int nskr_get_block(const nskr_ctx *ctx, int *threads);
 
@@ -353,7 +351,7 @@ const char *nskr_last_error(const nskr_ctx *ctx);
  * Batched execution of many independent instances (contexts), possibly with
  * different degrees, meshes, parameters, precisions and time steps.  Each
  * nskr_batch_step advances every active instance by one RK step: per group of
- * equal (degree, precision, block size) one launch per stage kernel covers all
+ * equal (degree, precision, curved or not) one launch per stage kernel covers all
  * member instances through a device table of instances and a block map, and
  * the whole step is captured once into a HIP graph and replayed until the set
  * of instances changes.  An instance's arithmetic is the same alone and in any

@@ -166,6 +166,37 @@ template <int P, int BS = kBlock, int EPB_ = BS / (P * P * P)> struct Tile {
     static constexpr int TPE = kUni ? kWaves : n3;
 };
 
+// Tiles of the stage kernels: elements per workgroup of each kernel and of
+// the unit (kTile) in which elements are dealt to the XCDs, a multiple of all
+// of them.  Each kernel has its own, since they are bound by different things.
+// The update streams and likes groups whose node arrays end on cache lines
+// (4 elements of N = 5 are 27 lines of 128 bytes in FP32, 2 in FP64; shared
+// lines are fetched and written by two workgroups): 32^3 N = 5, 1 / 2 / 4
+// elements: 402 / 368 / 363 us in FP64 and 304 / 261 / 229 in FP32-mixed;
+// 16^3 N = 4: 26.9 / 26.6 / 25.5 and 19.2 / 17.2 / 16.3.  k_lift1 at N = 5 takes
+// 105 us with one element and 134 with two: short phases between barriers.
+template <int P> struct StageTile {
+    static constexpr int kLift1 = P == 3 ? 9 : (P == 6 ? 1 : 2);
+    static constexpr int kLift2 = P >= 5 ? 1 : (P == 4 ? 2 : 3);
+    static constexpr int kUpdate = P == 3 ? 9 : 4;
+    static constexpr int kTile = P == 3 ? 9 : 4;
+    static_assert(kTile % kLift1 == 0 && kTile % kLift2 == 0 && kTile % kUpdate == 0, "tile");
+};
+// Workgroup of EPB elements in whole waves, with a thread for every node and
+// (FACES) for every face point.
+template <int P, int EPB, bool FACES> struct Group {
+    static constexpr int kNodes = EPB * P * P * P, kFaces = EPB * 6 * P * P;
+    static constexpr int NT = ((FACES && kFaces > kNodes ? kFaces : kNodes) + 63) / 64 * 64;
+    using G = Tile<P, NT, EPB>;
+    static constexpr int kSub = StageTile<P>::kTile / EPB;  // workgroups per tile
+    // workgroups of `tiles` tiles: the tiles of each XCD (tile mod 8, as the
+    // hardware deals out workgroups) keep their XCD
+    static int grid(int tiles) { return kSub == 1 ? tiles : (tiles + 7) / 8 * 8 * kSub; }
+    // this workgroup's tile and its place in it, in elements
+    static __device__ __forceinline__ int tile() { return kSub == 1 ? blockIdx.x : blockIdx.x / (8 * kSub) * 8 + blockIdx.x % 8; }
+    static __device__ __forceinline__ int part() { return kSub == 1 ? 0 : blockIdx.x / 8 % kSub * EPB; }
+};
+
 // Node thread of a workgroup: local element, node of the element, and the
 // node's place in the workgroup's tile.
 template <typename G> struct NodeTask {
@@ -405,7 +436,7 @@ template <typename T> struct Launch {
     Inst<T> one;
     const Inst<T> *tab;
     const int *blk_inst, *blk_e0;
-    const int *blk_map;  // single instance: first element of every block (null: block b, elements b EPB..)
+    const int *blk_map;  // single instance: first element of every tile
     Basis bas;
     int mode;        // 0 write U_t; 1 RK stage (update U, R, write traces); 2 write grad T and lap c (k_lift2)
     int first;       // RK: assign R at the first stage
@@ -471,17 +502,23 @@ template <typename P> __device__ __forceinline__ P load_const(const P *p, int i)
 #endif
 }
 
-template <typename T, bool BATCH>
-__device__ __forceinline__ void instance_of(const Launch<T> &L, Inst<T> &a, int &e0, int epb, int b)
+// The instance and the first element of this workgroup (of `tiles` tiles); false
+// for a workgroup past the last tile.
+template <int P, typename W, bool BATCH, typename T>
+__device__ __forceinline__ bool instance_of(const Launch<T> &L, Inst<T> &a, int &e0, int tiles)
 {
+    const int b = W::tile();
+    if (b >= tiles) return false;
     if (BATCH) {
         const int k = load_const(L.blk_inst, b);
         e0 = load_const(L.blk_e0, b);
         a = load_const(L.tab, k);
     } else {
         a = L.one;
-        e0 = L.blk_map ? load_const(L.blk_map, b) : b * epb;
+        e0 = load_const(L.blk_map, b);
     }
+    e0 += W::part();
+    return true;
 }
 
 // Pairs of fields.  The LDS delivers 128-bit reads at the same rate per
@@ -600,15 +637,15 @@ template <int P> struct FaceTask {
     }
 };
 
-template <int P, int BS> __device__ __forceinline__ constexpr int n_lines() { return Tile<P, BS>::EPB * 3 * P * P; }
+template <typename G> __device__ __forceinline__ constexpr int n_lines() { return G::EPB * 3 * G::n2; }
 
 // Line task of thread t, or -1.  The lines fill the first waves of the
 // workgroup lane by lane, so waves without lines issue no instructions for
 // the line phases (at N = 5, 108 lines take two waves, not 27 lanes in each
 // of four: lift1 9-10 % faster on the 32^3 case in both precisions).
-template <int P, int BS> __device__ __forceinline__ int line_of_thread(int t)
+template <typename G> __device__ __forceinline__ int line_of_thread(int t)
 {
-    return t < n_lines<P, BS>() ? t : -1;
+    return t < n_lines<G>() ? t : -1;
 }
 
 // ------------------------------------------------------------ shared pieces
@@ -847,8 +884,14 @@ __device__ __forceinline__ T stage_node_metrics(const MeshDev &m, size_t NN, siz
     return T(1) / gld(nm + 9 * NN, (uint32_t)g);
 }
 
-template <typename T> __device__ __forceinline__ void to_physical(const T Ja[9], T iJ, const T gd[3], T q[3])
+template <bool DIAG, typename T>
+__device__ __forceinline__ void to_physical(const T Ja[9], T iJ, const T gd[3], T q[3])
 {
+    if constexpr (DIAG) {  // Ja^d along axis d
+#pragma unroll
+        for (int m = 0; m < 3; ++m) q[m] = iJ * (Ja[4 * m] * gd[m]);
+        return;
+    }
 #pragma unroll
     for (int m = 0; m < 3; ++m) q[m] = iJ * (Ja[m] * gd[0] + Ja[3 + m] * gd[1] + Ja[6 + m] * gd[2]);
 }
@@ -862,13 +905,17 @@ template <bool UNI, typename T> __device__ __forceinline__ void element_metrics(
 
 // ------------------------------------------------------------ k_prolong
 // Conserved face traces of the state (into trace buffer L.tw).
-template <int P, typename T, int BS, bool BATCH>
-__global__ __launch_bounds__(BS) void k_prolong(Launch<T> L)
+template <int P> using ProlongGroup = Group<P, StageTile<P>::kLift1, false>;
+
+template <int P, typename T>
+__global__ __launch_bounds__(ProlongGroup<P>::NT) void k_prolong(Launch<T> L, int tiles)
 {
-    using G = Tile<P, BS>;
+    using W = ProlongGroup<P>;
+    using G = typename W::G;
+    constexpr int BS = W::NT;
     Inst<T> a;
     int e0;
-    instance_of<T, BATCH>(L, a, e0, G::EPB, blockIdx.x);
+    if (!instance_of<P, W, false>(L, a, e0, tiles)) return;
     __shared__ V2<T> sU[3][G::NV];
     __shared__ BasisS<P, T> B;
     B.load(L.bas);
@@ -883,7 +930,7 @@ __global__ __launch_bounds__(BS) void k_prolong(Launch<T> L)
     __syncthreads();
     const size_t NF = (size_t)E * 6 * G::n2;
     T *TU = a.TU + (size_t)L.tw * 6 * NF;
-    for (int task = t; task < n_lines<P, BS>(); task += BS) {
+    for (int task = t; task < n_lines<G>(); task += BS) {
         LineTask<P> lt(task);
         const int e = e0 + lt.le;
         if (e >= E) continue;
@@ -909,21 +956,23 @@ __global__ __launch_bounds__(BS) void k_prolong(Launch<T> L)
 // register spills: 7 in FP32 (8 spills; so does 7 in 448-thread
 // workgroups), and in FP64 8 at N = 5 (63 registers instead of 79) and 6 at
 // N = 3 (80 instead of 83).
-template <int P, typename T, int BS, bool FULL, bool CV> constexpr int lift1_waves()
+template <int P, typename T, bool FULL, bool CV> constexpr int lift1_waves()
 {
-    if (BS != 256 || FULL || CV) return 1;
-    if (sizeof(T) == 4) return 7;
-    return P == 6 ? 8 : (P == 4 ? 6 : 1);
+    if (FULL || CV) return 1;
+    return sizeof(T) == 4 ? 7 : (P == 6 ? 8 : (P == 4 ? 6 : 1));
 }
+template <int P> using Lift1Group = Group<P, StageTile<P>::kLift1, false>;
 
-template <int P, typename T, int BS, bool BATCH, bool FULL = false, bool CV = false>
-__global__ __launch_bounds__(BS, (lift1_waves<P, T, BS, FULL, CV>())) void k_lift1(Launch<T> L)
+template <int P, typename T, bool BATCH, bool FULL = false, bool CV = false>
+__global__ __launch_bounds__(Lift1Group<P>::NT, (lift1_waves<P, T, FULL, CV>())) void k_lift1(Launch<T> L, int tiles)
 {
-    using G = Tile<P, BS>;
+    using W = Lift1Group<P>;
+    using G = typename W::G;
+    constexpr int BS = W::NT;
     Inst<T> a;
     int e0;
-    instance_of<T, BATCH>(L, a, e0, G::EPB, blockIdx.x);
-    static_assert(n_lines<P, BS>() <= BS, "one line per thread");
+    if (!instance_of<P, W, BATCH>(L, a, e0, tiles)) return;
+    static_assert(n_lines<G>() <= BS, "one line per thread");
     // state (c only, or with FULL all of it) and primitives (FULL), BR1 face
     // values of c or of all primitives
     constexpr int NU = FULL ? 6 : 1, NS = FULL ? 5 : 1, kC = NU - 1;
@@ -952,7 +1001,7 @@ __global__ __launch_bounds__(BS, (lift1_waves<P, T, BS, FULL, CV>())) void k_lif
     const T *TU = a.TU + (size_t)L.tb * 6 * NF;
 
     // early loads: own nodes, and the neighbour traces of this thread's line
-    const int ltask = line_of_thread<P, BS>(t);
+    const int ltask = line_of_thread<G>(t);
     const LineTask<P> lt(ltask < 0 ? 0 : ltask);
     const int el = e0 + lt.le;
     const bool lact = ltask >= 0 && el < E;
@@ -1133,39 +1182,30 @@ __global__ __launch_bounds__(BS, (lift1_waves<P, T, BS, FULL, CV>())) void k_lif
 // Tile of k_lift2: its own, since its workgroups are bound by the registers
 // and the LDS of the node phases and by the rounds of the face phases, not by
 // what the streaming kernels of the stage like.  One element per workgroup at
-// N = 4 and 5, two at N = 3, three at N = 2 (where the stage's tile is a
-// multiple of it), and as many threads as the face points need, in whole
+// N = 4 and 5, two at N = 3, three at N = 2 and as many threads as the face points need, in whole
 // waves, so that the face phases take one round: the second round of a few
 // face points cost a workgroup the latency of a whole one.
-template <int P, int BS> struct Lift2Tile {
-    static constexpr int kTile = Tile<P, BS>::EPB;
-    static constexpr int kBest = P >= 5 ? 1 : (P == 4 ? 2 : 3);
-    static constexpr int EPB = kTile % kBest == 0 ? kBest : kTile;
-    static constexpr int kSub = kTile / EPB;  // workgroups per tile
-    static constexpr int kMost = EPB * 6 * P * P > EPB * P * P * P ? EPB * 6 * P * P : EPB * P * P * P;
-    static constexpr int NT = (kMost + 63) / 64 * 64;
-    using G = Tile<P, NT, EPB>;
-    // workgroups for `tiles` tiles: the tiles of each XCD (tile mod 8, as the
-    // hardware deals out workgroups) keep their XCD
-    static int grid(int tiles) { return kSub == 1 ? tiles : (tiles + 7) / 8 * 8 * kSub; }
-};
+template <int P> using Lift2Group = Group<P, StageTile<P>::kLift2, true>;
 
 // FP64 instances on affine elements keep 4 waves per SIMD (128 registers)
 // where their LDS lets them.
 template <int P, typename T, bool CV> constexpr int lift2_waves() { return sizeof(T) == 8 && !CV && P > 3 ? 4 : 1; }
 
-template <int P, typename T, int BS, bool BATCH, bool CV = false, bool WALL = true>
-__global__ __launch_bounds__((Lift2Tile<P, BS>::NT), (lift2_waves<P, T, CV>())) void k_lift2(Launch<T> L, int tiles)
+// WALL: the mesh (or a batch's) has wall faces; without them the wall pass and
+// its registers are left out.  DIAG: every element is a box along the axes, so
+// Ja^d has the component d alone (the others are exactly zero, and leaving them
+// out changes no finite result): three products for a gradient instead of
+// twelve, and no normal components of the stress to form.
+template <int P, typename T, bool BATCH, bool CV, bool WALL, bool DIAG>
+__global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void k_lift2(Launch<T> L, int tiles)
 {
-    using Q = Lift2Tile<P, BS>;
-    using G = typename Q::G;
-    constexpr int NT = Q::NT;
-    const int tile = Q::kSub == 1 ? blockIdx.x : blockIdx.x / (8 * Q::kSub) * 8 + blockIdx.x % 8;
-    if (tile >= tiles) return;
+    using W = Lift2Group<P>;
+    using G = typename W::G;
+    constexpr int NT = W::NT;
     Inst<T> a;
     int e0;
-    instance_of<T, BATCH>(L, a, e0, Q::kTile, tile);
-    if (Q::kSub > 1) e0 += blockIdx.x / 8 % Q::kSub * Q::EPB;
+    if (!instance_of<P, W, BATCH>(L, a, e0, tiles)) return;
+    const int E = a.mesh.E;
     // LDS, in rows of pairs of NV nodes: the primitives (rho, u), (v, w) and c
     // and their BR1 face values while they are lifted; then
     //   rows 0..2  (tau . n_d)_0, (tau . n_d)_1 of direction d
@@ -1195,7 +1235,6 @@ __global__ __launch_bounds__((Lift2Tile<P, BS>::NT), (lift2_waves<P, T, CV>())) 
     V2<T> *sM = sX + kX - 2 * G::NV;  // (m_x, m_y), (m_z, rho e)
     const Five<T> fw{sX, sX + G::NV, sWc}, fs{sSa, sSb, sSc};
     B.load(L.bas);
-    const int E = a.mesh.E;
     const int t = threadIdx.x;
     const NodeTask<G> nt(t);
     const int le = nt.le, nd = nt.nd, tq = nt.q;
@@ -1424,10 +1463,10 @@ __global__ __launch_bounds__((Lift2Tile<P, BS>::NT), (lift2_waves<P, T, CV>())) 
             T gd[5][3], Ja[9];
             lifted_grads<P, T>(fw, fs, base, fbase, i, j, k, B, gd);
             element_metrics<G::kUni>(a.mesh, e, Ja, iJ);
-            to_physical(Ja, iJ, gd[0], grho);
+            to_physical<DIAG>(Ja, iJ, gd[0], grho);
 #pragma unroll
-            for (int m = 0; m < 3; ++m) to_physical(Ja, iJ, gd[1 + m], gu[m]);
-            to_physical(Ja, iJ, gd[4], gc);
+            for (int m = 0; m < 3; ++m) to_physical<DIAG>(Ja, iJ, gd[1 + m], gu[m]);
+            to_physical<DIAG>(Ja, iJ, gd[4], gc);
         }
         {
             const V2<T> m01 = sM[tq], m2e = sM[G::NV + tq];
@@ -1470,15 +1509,21 @@ __global__ __launch_bounds__((Lift2Tile<P, BS>::NT), (lift2_waves<P, T, CV>())) 
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
                 const int jr = kEmJa + 3 * d, fr = (2 * d + 1) * 4;
-                gc[d] = em_at<G::kUni, T>(a.mesh, e, jr) * g0 + em_at<G::kUni, T>(a.mesh, e, jr + 1) * g1 +
-                        em_at<G::kUni, T>(a.mesh, e, jr + 2) * g2;
-                const T n0 = em_at<G::kUni, T>(a.mesh, e, fr), n1 = em_at<G::kUni, T>(a.mesh, e, fr + 1),
-                        n2 = em_at<G::kUni, T>(a.mesh, e, fr + 2);
                 T tn[3];
+                if constexpr (DIAG) {  // n_d is the unit vector of axis d
+                    gc[d] = em_at<G::kUni, T>(a.mesh, e, jr + d) * gc[d];
 #pragma unroll
-                for (int m = 0; m < 3; ++m)
-                    tn[m] = mu * ((gu[m][0] + gu[0][m]) * n0 + (gu[m][1] + gu[1][m]) * n1 + (gu[m][2] + gu[2][m]) * n2 -
-                                  td * (m == 0 ? n0 : (m == 1 ? n1 : n2)));
+                    for (int m = 0; m < 3; ++m) tn[m] = mu * ((gu[m][d] + gu[d][m]) - (m == d ? td : T(0)));
+                } else {
+                    gc[d] = em_at<G::kUni, T>(a.mesh, e, jr) * g0 + em_at<G::kUni, T>(a.mesh, e, jr + 1) * g1 +
+                            em_at<G::kUni, T>(a.mesh, e, jr + 2) * g2;
+                    const T n0 = em_at<G::kUni, T>(a.mesh, e, fr), n1 = em_at<G::kUni, T>(a.mesh, e, fr + 1),
+                            n2 = em_at<G::kUni, T>(a.mesh, e, fr + 2);
+#pragma unroll
+                    for (int m = 0; m < 3; ++m)
+                        tn[m] = mu * ((gu[m][0] + gu[0][m]) * n0 + (gu[m][1] + gu[1][m]) * n1 +
+                                      (gu[m][2] + gu[2][m]) * n2 - td * (m == 0 ? n0 : (m == 1 ? n1 : n2)));
+                }
                 sR[d][tq] = V2<T>{tn[0], tn[1]};
                 sR[3 + d][tq] = V2<T>{tn[2], div};
                 sR[kT + d][tq] = V2<T>{T(Tn), gc[d]};
@@ -1540,7 +1585,7 @@ __global__ __launch_bounds__((Lift2Tile<P, BS>::NT), (lift2_waves<P, T, CV>())) 
         } else {
             T Ja[9], iJ2;
             element_metrics<G::kUni>(a.mesh, e, Ja, iJ2);
-            to_physical(Ja, iJ, gd, gT);
+            to_physical<DIAG>(Ja, iJ, gd, gT);
         }
         lap = iJ * dl;
         if (L.mode == 2) {  // the second lifting's output alone
@@ -1562,9 +1607,11 @@ __global__ __launch_bounds__((Lift2Tile<P, BS>::NT), (lift2_waves<P, T, CV>())) 
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
                 const int fr = (2 * d + 1) * 4;
-                const T n0 = em_at<G::kUni, T>(a.mesh, e, fr), n1 = em_at<G::kUni, T>(a.mesh, e, fr + 1),
-                        n2 = em_at<G::kUni, T>(a.mesh, e, fr + 2);
-                sR[kT + d][tq] = V2<T>{gT[0] * n0 + gT[1] * n1 + gT[2] * n2, lap};
+                T gn = gT[d];
+                if constexpr (!DIAG)
+                    gn = gT[0] * em_at<G::kUni, T>(a.mesh, e, fr) + gT[1] * em_at<G::kUni, T>(a.mesh, e, fr + 1) +
+                         gT[2] * em_at<G::kUni, T>(a.mesh, e, fr + 2);
+                sR[kT + d][tq] = V2<T>{gn, lap};
             }
         }
     }
@@ -1773,7 +1820,7 @@ __global__ __launch_bounds__((Lift2Tile<P, BS>::NT), (lift2_waves<P, T, CV>())) 
         // contravariant fluxes Ja^d . F of (F^C - F^V), F^V = (0, tau, tau u +
         // j_e, gamma beta grad c): on affine elements Ja^d . tau is dS_d times
         // tau . n_d
-        T J[3], tj[3], gj;
+        T J[3], tj[3], gj, qj, mJ;
         if constexpr (CV) {
             const V2<T> jj = sJ[d][tq];
             J[0] = jj.x;
@@ -1794,7 +1841,8 @@ __global__ __launch_bounds__((Lift2Tile<P, BS>::NT), (lift2_waves<P, T, CV>())) 
             gj = J[0] * gc[0] + J[1] * gc[1] + J[2] * gc[2];
         } else {
 #pragma unroll
-            for (int m = 0; m < 3; ++m) J[m] = em_at<G::kUni, T>(a.mesh, e, kEmJa + 3 * d + m);
+            for (int m = 0; m < 3; ++m)
+                J[m] = !DIAG || m == d ? em_at<G::kUni, T>(a.mesh, e, kEmJa + 3 * d + m) : T(0);
             const T dS = em_at<G::kUni, T>(a.mesh, e, (2 * d + 1) * 4 + 3);
             const V2<T> x = sR[d][tq], y = sR[3 + d][tq];
             tj[0] = dS * x.x;
@@ -1802,11 +1850,20 @@ __global__ __launch_bounds__((Lift2Tile<P, BS>::NT), (lift2_waves<P, T, CV>())) 
             tj[2] = dS * y.x;
             gj = d == 0 ? gc[0] : (d == 1 ? gc[1] : gc[2]);
         }
-        const T qj = J[0] * gT[0] + J[1] * gT[1] + J[2] * gT[2];
-        const T mJ = J[0] * un[1] + J[1] * un[2] + J[2] * un[3], uJ = mJ * irn;
+        if constexpr (DIAG) {
+            qj = J[d] * gT[d];
+            mJ = J[d] * un[1 + d];
+        } else {
+            qj = J[0] * gT[0] + J[1] * gT[1] + J[2] * gT[2];
+            mJ = J[0] * un[1] + J[1] * un[2] + J[2] * un[3];
+        }
+        const T uJ = mJ * irn;
         const T tw = (tj[0] * un[1] + tj[1] * un[2] + tj[2] * un[3]) * irn;
-        sR[frow(d & 1, 0)][tq] = V2<T>{mJ, un[1] * uJ + p * J[0] - tj[0]};
-        sR[frow(d & 1, 1)][tq] = V2<T>{un[2] * uJ + p * J[1] - tj[1], un[3] * uJ + p * J[2] - tj[2]};
+        T mf[3];
+#pragma unroll
+        for (int m = 0; m < 3; ++m) mf[m] = (DIAG && m != d ? un[1 + m] * uJ : un[1 + m] * uJ + p * J[m]) - tj[m];
+        sR[frow(d & 1, 0)][tq] = V2<T>{mJ, mf[0]};
+        sR[frow(d & 1, 1)][tq] = V2<T>{mf[1], mf[2]};
         sR[frow(d & 1, 2)][tq] = V2<T>{(un[4] + p) * uJ - tw - (T(a.ph.kappa) * qj + zc * gj),
                                        un[5] * uJ - T(a.ph.gam * a.ph.beta) * gj};
     };
@@ -1821,7 +1878,7 @@ __global__ __launch_bounds__((Lift2Tile<P, BS>::NT), (lift2_waves<P, T, CV>())) 
             const V2<T> *r0 = sR[frow(d & 1, 0)], *r1 = sR[frow(d & 1, 1)], *r2 = sR[frow(d & 1, 2)];
             const int id = d == 0 ? i : (d == 1 ? j : k);
             const int str = d == 0 ? 1 : (d == 1 ? P : P * P);
-            const int lo = base + nd - id * str;
+            const int lo = base + line_node<P>(d, 0, d == 0 ? j : i, d == 2 ? j : k);
             T D[P];
             B.row(B.Dh + id * B.PS, D);
 #pragma unroll
@@ -1850,13 +1907,17 @@ __global__ __launch_bounds__((Lift2Tile<P, BS>::NT), (lift2_waves<P, T, CV>())) 
 }
 
 // ------------------------------------------------------------ k_update
-template <int P, typename T, int BS, bool BATCH, bool CV = false, bool NT = false>
-__global__ __launch_bounds__(BS) void k_update(Launch<T> L)
+template <int P> using UpdateGroup = Group<P, StageTile<P>::kUpdate, false>;
+
+template <int P, typename T, bool BATCH, bool CV = false, bool NT = false>
+__global__ __launch_bounds__(UpdateGroup<P>::NT) void k_update(Launch<T> L, int tiles)
 {
-    using G = Tile<P, BS>;
+    using W = UpdateGroup<P>;
+    using G = typename W::G;
+    constexpr int BS = W::NT;
     Inst<T> a;
     int e0;
-    instance_of<T, BATCH>(L, a, e0, G::EPB, blockIdx.x);
+    if (!instance_of<P, W, BATCH>(L, a, e0, tiles)) return;
     __shared__ V2<T> sF[3][G::NV];     // new state
     __shared__ V2<T> sFs[3][G::NF];    // surface flux (F* . n) dS
     __shared__ BasisS<P, T> B;
@@ -1957,7 +2018,7 @@ __global__ __launch_bounds__(BS) void k_update(Launch<T> L)
         for (int v = 0; v < 3; ++v) sF[v][tq] = V2<T>{u6[2 * v], u6[2 * v + 1]};
     }
     __syncthreads();
-    const int ltask = line_of_thread<P, BS>(t);
+    const int ltask = line_of_thread<G>(t);
     const LineTask<P> lt(ltask < 0 ? 0 : ltask);
     const int el = e0 + lt.le;
     const bool lact = ltask >= 0 && el < E;

@@ -26,7 +26,7 @@ using namespace nskr;
 struct nskr_ctx {
     nskr_params p;
     int N = 0, P = 0, device = 0;
-    int bs = 256;               // threads per block of the stage kernels
+    int bs = 256;               // nominal tile size (nskr_set_block)
     bool poisoned = false;
     std::string err;
     // mesh
@@ -40,6 +40,7 @@ struct nskr_ctx {
     double *d_xnode = nullptr;   // curved: node coordinates
     BcDev *d_bcs = nullptr;
     int wall = 0;                // some face is a wall
+    bool diag = false;           // every element is a box along the axes (Ja^d has component d alone)
     int dyn = 0;                 // a Navier-slip wall with gamma_1 != 0
     double *d_stab = nullptr;    // wall-temperature table (walls with a temperature gradient)
     int var = 0;                 // some wall has a temperature gradient or rate
@@ -55,8 +56,7 @@ struct nskr_ctx {
     double *d_noise = nullptr;   // init noise
     double *d_drop = nullptr;    // init droplets
     std::vector<float> cent;     // element centroids (host), for the block order
-    int *d_bmap = nullptr;       // first element of every stage-kernel block, in XCD order
-    int bmap_bs = 0;             // block size d_bmap was built for
+    int *d_bmap = nullptr;       // first element of every tile, in XCD order
     int stream_nodes = 0;        // the update kernel's node arrays stream past the last-level cache
     size_t bytes = 0;
     Basis bas;
@@ -677,13 +677,12 @@ __global__ __launch_bounds__(64) void k_tick(int *const *clk, int n)
 }
 
 // ------------------------------------------------------------ launch layer
-template <int P, typename T, int BS, bool CV> struct Impl {
-    static constexpr int kP = P, kBS = BS;
+template <int P, typename T, bool CV> struct Impl {
+    static constexpr int kP = P, kTile = StageTile<P>::kTile;
     static constexpr bool kCV = CV;
     using Real = T;
-    using G = Tile<P, BS>;
     using G256 = Tile<P, kBlock>;
-    static int nblk(const nskr_ctx *c) { return (c->E + G::EPB - 1) / G::EPB; }
+    static int tiles(const nskr_ctx *c) { return (c->E + kTile - 1) / kTile; }
     static int nblk256(const nskr_ctx *c) { return (c->E + G256::EPB - 1) / G256::EPB; }
 
     static MeshDev mesh(const nskr_ctx *c)
@@ -715,59 +714,50 @@ template <int P, typename T, int BS, bool CV> struct Impl {
         L.blk_map = c->d_bmap;
         return L;
     }
-    // every stage kernel's static LDS fits the device's per-block limit
-    static int fits(int maxlds)
+    // the second lifting's instance for a mesh with or without walls, of
+    // boxes along the axes or not
+    template <bool BATCH> static auto lift2_kernel(bool wall, bool diag)
     {
-        constexpr int n2 = Lift2Tile<P, BS>::NT;
-        const std::pair<const void *, int> fns[] = {
-            {reinterpret_cast<const void *>(&k_prolong<P, T, BS, false>), BS},
-            {reinterpret_cast<const void *>(&k_lift1<P, T, BS, false, false, CV>), BS},
-            {reinterpret_cast<const void *>(&k_lift1<P, T, BS, false, true, CV>), BS},
-            {reinterpret_cast<const void *>(&k_lift2<P, T, BS, false, CV, true>), n2},
-            {reinterpret_cast<const void *>(&k_lift2<P, T, BS, false, CV, false>), n2},
-            {reinterpret_cast<const void *>(&k_update<P, T, BS, false, CV, false>), BS},
-            {reinterpret_cast<const void *>(&k_update<P, T, BS, false, CV, true>), BS}};
-        for (const auto &f : fns) {
-            hipFuncAttributes at;
-            if (hipFuncGetAttributes(&at, f.first) != hipSuccess) return 0;
-            if ((int)at.sharedSizeBytes > maxlds || at.maxThreadsPerBlock < f.second) return 0;
-        }
-        return 1;
+        constexpr bool D = !CV;
+        return wall ? (diag && D ? &k_lift2<P, T, BATCH, CV, true, D> : &k_lift2<P, T, BATCH, CV, true, false>)
+                    : (diag && D ? &k_lift2<P, T, BATCH, CV, false, D> : &k_lift2<P, T, BATCH, CV, false, false>);
     }
     // single-instance launches
     static void prolong(nskr_ctx *c, const Launch<T> &L, hipStream_t s)
     {
-        stage_launch(c, 0, &k_prolong<P, T, BS, false>, nblk(c), BS, s, L);
+        using W = ProlongGroup<P>;
+        const int n = tiles(c);
+        stage_launch(c, 0, &k_prolong<P, T>, W::grid(n), W::NT, s, L, n);
     }
     static void lift1(nskr_ctx *c, const Launch<T> &L, hipStream_t s)
     {
-        if (L.full)
-            stage_launch(c, 1, &k_lift1<P, T, BS, false, true, CV>, nblk(c), BS, s, L);
-        else
-            stage_launch(c, 1, &k_lift1<P, T, BS, false, false, CV>, nblk(c), BS, s, L);
+        using W = Lift1Group<P>;
+        const int n = tiles(c);
+        stage_launch(c, 1, L.full ? &k_lift1<P, T, false, true, CV> : &k_lift1<P, T, false, false, CV>, W::grid(n), W::NT,
+                     s, L, n);
     }
     static void lift2(nskr_ctx *c, const Launch<T> &L, hipStream_t s)
     {
-        using Q = Lift2Tile<P, BS>;
-        const int n = nblk(c);
-        if (c->wall)
-            stage_launch(c, 2, &k_lift2<P, T, BS, false, CV, true>, Q::grid(n), Q::NT, s, L, n);
-        else
-            stage_launch(c, 2, &k_lift2<P, T, BS, false, CV, false>, Q::grid(n), Q::NT, s, L, n);
+        using W = Lift2Group<P>;
+        const int n = tiles(c);
+        stage_launch(c, 2, lift2_kernel<false>(c->wall, c->diag), W::grid(n), W::NT, s, L, n);
     }
     static void update(nskr_ctx *c, const Launch<T> &L, hipStream_t s)
     {
-        if (c->stream_nodes)
-            stage_launch(c, 3, &k_update<P, T, BS, false, CV, true>, nblk(c), BS, s, L);
-        else
-            stage_launch(c, 3, &k_update<P, T, BS, false, CV, false>, nblk(c), BS, s, L);
+        using W = UpdateGroup<P>;
+        const int n = tiles(c);
+        stage_launch(c, 3, c->stream_nodes ? &k_update<P, T, false, CV, true> : &k_update<P, T, false, CV, false>,
+                     W::grid(n), W::NT, s, L, n);
     }
     // batched launches over a group table
     // one RK step of every instance of a group; the face traces of the first
     // stage come from the previous step's last update (or from prime())
-    static void step_batched(const Launch<T> &L0, int nblocks, bool wall, hipStream_t s)
+    static void step_batched(const Launch<T> &L0, int n, bool wall, bool diag, hipStream_t s)
     {
-        using Q = Lift2Tile<P, BS>;
+        using W1 = Lift1Group<P>;
+        using W2 = Lift2Group<P>;
+        using W3 = UpdateGroup<P>;
+        const auto lift2 = lift2_kernel<true>(wall, diag);
         Launch<T> L = L0;
         for (int st = 0; st < 5; ++st) {
             L.mode = 1;
@@ -778,12 +768,9 @@ template <int P, typename T, int BS, bool CV> struct Impl {
             L.tb = kTraceBuf[st];
             L.tw = kTraceBuf[st + 1];
             L.cs = kRkC[st];
-            hipLaunchKernelGGL((k_lift1<P, T, BS, true, false, CV>), dim3(nblocks), dim3(BS), 0, s, L);
-            if (wall)
-                hipLaunchKernelGGL((k_lift2<P, T, BS, true, CV, true>), dim3(Q::grid(nblocks)), dim3(Q::NT), 0, s, L, nblocks);
-            else
-                hipLaunchKernelGGL((k_lift2<P, T, BS, true, CV, false>), dim3(Q::grid(nblocks)), dim3(Q::NT), 0, s, L, nblocks);
-            hipLaunchKernelGGL((k_update<P, T, BS, true, CV>), dim3(nblocks), dim3(BS), 0, s, L);
+            hipLaunchKernelGGL((k_lift1<P, T, true, false, CV>), dim3(W1::grid(n)), dim3(W1::NT), 0, s, L, n);
+            hipLaunchKernelGGL(lift2, dim3(W2::grid(n)), dim3(W2::NT), 0, s, L, n);
+            hipLaunchKernelGGL((k_update<P, T, true, CV>), dim3(W3::grid(n)), dim3(W3::NT), 0, s, L, n);
         }
     }
 
@@ -908,19 +895,14 @@ template <int P, typename T, int BS, bool CV> struct Impl {
     }
 };
 
-// Workgroup sizes built for each degree: 256 and 512 threads, and one size
-// that packs whole elements into waves more tightly than 256 does (N = 2:
-// 7 elements of 27 nodes in 192 threads; N = 3, 4: one wave pair, 2 and 1
-// elements; N = 5: 2 elements of 216 nodes in 448 threads, against 1 in 256).
+// Tile sizes that nskr_set_block takes: 256, 512 and the degree's tight size.
+// They name a tile and nothing else: each stage kernel sizes its workgroups by
+// what bounds it (StageTile).
 static int tight_block(int N) { return N == 2 ? 192 : (N == 5 ? 448 : 128); }
-// Default threads per workgroup: 128 at N = 3 (two elements per workgroup,
-// the same occupancy in finer workgroups: 3.4 % faster in FP64 and 0.7 % in
-// FP32-mixed than 256 on the 48x48x24 and 50^3 meshes), else 256 (at N = 4
-// the two measure the same; at N = 5 and N = 2 the tight sizes are slower).
 static int default_block(int N) { return N == 3 ? 128 : 256; }
 
-// Valid block sizes per degree: one of the built sizes, holding at least one
-// element and one line task per thread.
+// Valid sizes per degree: one of the above, holding at least one element and
+// one line task per thread.
 static bool block_ok(int N, int bs)
 {
     const int P = N + 1, n3 = P * P * P;
@@ -930,31 +912,19 @@ static bool block_ok(int N, int bs)
     return epb >= 1 && epb * 3 * P * P <= bs;
 }
 
-template <int PP, int BS, typename F> static int impl_prec(bool dbl, F &&f)
-{
-    return dbl ? f(Impl<PP, double, BS, false>()) : f(Impl<PP, float, BS, false>());
-}
-
-// The kernel instance set of a (degree, precision, block size, curved) choice.
-// Curved meshes run 256-thread workgroups only (their per-node metrics do
-// not fit the LDS of larger tiles at every degree).
-template <typename F> static int impl_dispatch(int N, int prec, int bs, bool curved, F &&f)
+// The kernel instance set of a (degree, precision, curved) choice.
+template <typename F> static int impl_dispatch(int N, int prec, bool curved, F &&f)
 {
     const bool dbl = prec == 0;
-#define NSKR_CASE(NN, PP, TB)                                                                           \
-    case NN:                                                                                            \
-        if (curved) {                                                                                   \
-            if (bs != 256) return NSKR_E_UNSUPPORTED;                                                   \
-            return dbl ? f(Impl<PP, double, 256, true>()) : f(Impl<PP, float, 256, true>());            \
-        }                                                                                               \
-        if (bs == 512) return impl_prec<PP, 512>(dbl, f);                                               \
-        if (bs == TB) return impl_prec<PP, TB>(dbl, f);                                                 \
-        return impl_prec<PP, 256>(dbl, f);
+#define NSKR_CASE(NN, PP)                                                                                  \
+    case NN:                                                                                               \
+        if (curved) return dbl ? f(Impl<PP, double, true>()) : f(Impl<PP, float, true>());                 \
+        return dbl ? f(Impl<PP, double, false>()) : f(Impl<PP, float, false>());
     switch (N) {
-        NSKR_CASE(2, 3, 192)
-        NSKR_CASE(3, 4, 128)
-        NSKR_CASE(4, 5, 128)
-        NSKR_CASE(5, 6, 448)
+        NSKR_CASE(2, 3)
+        NSKR_CASE(3, 4)
+        NSKR_CASE(4, 5)
+        NSKR_CASE(5, 6)
     }
 #undef NSKR_CASE
     return NSKR_E_ARG;
@@ -962,7 +932,7 @@ template <typename F> static int impl_dispatch(int N, int prec, int bs, bool cur
 
 template <typename F> static int dispatch(const nskr_ctx *c, F &&f)
 {
-    return impl_dispatch(c->N, c->p.precision, c->bs, c->curved, f);
+    return impl_dispatch(c->N, c->p.precision, c->curved, f);
 }
 
 static int elem_per_block(int N)
@@ -971,18 +941,18 @@ static int elem_per_block(int N)
     return kBlock / n3;
 }
 
-// Order of the stage kernels' blocks across the XCDs.  Workgroups go to the
-// 8 XCDs round robin (block b to XCD b mod 8), each with its own L2, and an
-// element's face traces are read by its own block and by its neighbours'.
-// The groups of elements that share a block are split into 8 slabs of equal
+// Order of the tiles (StageTile::kTile elements) across the XCDs.  Workgroups
+// go to the 8 XCDs round robin (workgroup b to XCD b mod 8), each with its own
+// L2, and an element's face traces are read by its own workgroup and by its
+// neighbours'.  The tiles are split into 8 slabs of equal
 // count along the longest extent of the mesh (by their centroids), slab k
-// going to the blocks b = k mod 8 in the elements' own order, so most
+// going to the tiles b = k mod 8 in the elements' own order, so most
 // neighbours of an element are processed on the same XCD at about the same
 // time and read its traces from that L2.  Concurrent XCDs still work on
 // nearby addresses (neighbouring slabs at the same position in their own
 // order).
 constexpr int kXcds = 8;
-// Node data of the update kernel (U, R and grad T + lap c: 16 values per
+// Node data of a stage (U, R and the API arrays: 16 values per
 // node) beyond which its node accesses carry the non-temporal hint: half the
 // 256 MiB last-level cache.  Measured: 0.5-1.3 % faster in FP64 on the
 // 32^3 N = 5, 48x48x24 N = 3 and 50^3 N = 3 meshes, 3-5 % in FP32-mixed on the
@@ -991,7 +961,7 @@ constexpr double kStreamBytes = 134217728.0;
 
 static int build_block_map(nskr_ctx *c)
 {
-    const int epb = c->bs / ((c->N + 1) * (c->N + 1) * (c->N + 1));
+    const int epb = dispatch(c, [](auto impl) { return (int)decltype(impl)::kTile; });
     const int E = c->E, G = (E + epb - 1) / epb;
     std::vector<double> gc((size_t)G * 3, 0.0);
     for (int e = 0; e < E; ++e)
@@ -1032,11 +1002,9 @@ static int build_block_map(nskr_ctx *c)
     if (c->d_bmap) {
         (void)hipFree(c->d_bmap);
         c->d_bmap = nullptr;
-        c->bmap_bs = 0;
     }
     HIPCHK(c, hipMalloc((void **)&c->d_bmap, sizeof(int) * (size_t)G));
     HIPCHK(c, hipMemcpy(c->d_bmap, map.data(), sizeof(int) * (size_t)G, hipMemcpyHostToDevice));
-    c->bmap_bs = c->bs;
     return NSKR_OK;
 }
 
@@ -1247,7 +1215,7 @@ int nskr_create(const nskr_params *p, int N, int device, nskr_ctx **out)
     if (hipGetDeviceCount(&ndev) != hipSuccess || device < 0 || device >= ndev) return NSKR_E_HIP;
     // make sure the device code for this GPU is present
     hipFuncAttributes attr;
-    if (hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(&k_update<4, double, 256, false>)) != hipSuccess)
+    if (hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(&k_update<4, double, false>)) != hipSuccess)
         return NSKR_E_HIP;
     {
         DeviceGuard guard(device);
@@ -1289,7 +1257,6 @@ static void free_mesh(nskr_ctx *c)
     c->d_Q = c->d_TH = c->d_G2 = c->d_T2 = c->d_TF = c->d_TU = c->d_Ck = nullptr;
     c->d_part = c->d_out = c->d_noise = c->d_drop = nullptr;
     c->d_bmap = nullptr;
-    c->bmap_bs = 0;
     std::vector<float>().swap(c->cent);
     c->E = 0;
     c->NN = c->NF = 0;
@@ -1582,6 +1549,10 @@ int nskr_mesh_upload(nskr_ctx *c, const nskr_mesh *m, nskr_stream sv)
             }
         }
     }
+    bool diag = !curved;
+    for (size_t e = 0; diag && e < (size_t)E; ++e)
+        for (int q = 0; q < 9; ++q)
+            if (q % 4 != 0 && emet[e * 10 + q] != 0.0) diag = false;
     // the two sides of an interior face use exactly opposite normals and the
     // same surface element (conservation): one side (the master: the face on
     // the element's + side, else the lower element and face) keeps its own,
@@ -1707,6 +1678,7 @@ int nskr_mesh_upload(nskr_ctx *c, const nskr_mesh *m, nskr_stream sv)
     free_mesh(c);
     c->E = E;
     c->wall = wall;
+    c->diag = diag;
     c->dyn = dyn;
     c->var = var;
     c->trate = trate;
@@ -1841,7 +1813,7 @@ int nskr_init_droplets(nskr_ctx *c, const nskr_init *ic, const double *noise, vo
         HIPCHK(c, hipMemcpyAsync(c->d_noise, noise, sizeof(double) * c->NN, hipMemcpyHostToDevice, s));
     }
     InitArgs ia;
-    ia.mesh = Impl<4, double, 256, false>::mesh(c);
+    ia.mesh = Impl<4, double, false>::mesh(c);
     ia.bas = c->bas;
     ia.NN = c->NN;
     ia.drop = c->d_drop;
@@ -1992,18 +1964,7 @@ int nskr_set_block(nskr_ctx *c, int threads)
         return fail(c, NSKR_E_ARG, "block size must be 256, 512 or the degree's tight size (N=2: 192, N=3, 4: 128, "
                                    "N=5: 448) and hold an element");
     if (c->curved && threads != 256) return fail(c, NSKR_E_UNSUPPORTED, "meshes with curved elements run 256 threads");
-    DeviceGuard guard(c->device);
-    int maxlds = 0;
-    if (hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device) != hipSuccess)
-        return fail(c, NSKR_E_HIP, "cannot query the LDS limit");
-    const int old = c->bs;
     c->bs = threads;
-    const int ok = dispatch(c, [&](auto impl) { return decltype(impl)::fits(maxlds); });
-    if (!ok) {
-        c->bs = old;
-        return fail(c, NSKR_E_UNSUPPORTED, "kernels of this block size exceed the device's LDS per block");
-    }
-    if (c->E > 0 && c->bmap_bs != c->bs) return build_block_map(c);
     return NSKR_OK;
 }
 
@@ -2062,8 +2023,8 @@ struct BatchSlot {
 };
 
 struct BatchGroup {
-    bool wall = false;     // some member has walls
-    int N = 0, prec = 0, bs = 0, nblocks = 0;
+    bool wall = false, diag = true;  // some member has walls; every member's elements are boxes along the axes
+    int N = 0, prec = 0, tiles = 0;
     bool curved = false;
     void *d_tab = nullptr;
     int *d_bi = nullptr, *d_be = nullptr;
@@ -2127,25 +2088,26 @@ static void batch_free_groups(nskr_batch *b)
     if (b->graph) { (void)hipGraphDestroy(b->graph); b->graph = nullptr; }
 }
 
-template <int P, typename T, int BS, bool CV>
+template <int P, typename T, bool CV>
 static int build_group(nskr_batch *b, BatchGroup &g, const std::vector<int> &members)
 {
-    using G = Tile<P, BS>;
+    constexpr int kTile = StageTile<P>::kTile;
     std::vector<Inst<T>> tab;
     std::vector<int> bi, be;
     for (size_t k = 0; k < members.size(); ++k) {
         BatchSlot &sl = b->slots[members[k]];
-        tab.push_back(Impl<P, T, BS, CV>::inst(sl.c, sl.U, sl.R, nullptr, sl.dt));
+        tab.push_back(Impl<P, T, CV>::inst(sl.c, sl.U, sl.R, nullptr, sl.dt));
         tab.back().clk = sl.c->trate ? sl.c->d_clk : nullptr;
         tab.back().t0 = sl.t0;
         if (sl.c->wall) g.wall = true;
-        const int nb = (sl.c->E + G::EPB - 1) / G::EPB;
+        if (!sl.c->diag) g.diag = false;
+        const int nb = (sl.c->E + kTile - 1) / kTile;
         for (int j = 0; j < nb; ++j) {
             bi.push_back((int)k);
-            be.push_back(j * G::EPB);
+            be.push_back(j * kTile);
         }
     }
-    g.nblocks = (int)bi.size();
+    g.tiles = (int)bi.size();
     g.bas = b->slots[members[0]].c->bas;
     BHIPCHK(b, hipMalloc(&g.d_tab, sizeof(Inst<T>) * tab.size()));
     BHIPCHK(b, hipMalloc((void **)&g.d_bi, sizeof(int) * bi.size()));
@@ -2156,7 +2118,7 @@ static int build_group(nskr_batch *b, BatchGroup &g, const std::vector<int> &mem
     return NSKR_OK;
 }
 
-template <int P, typename T, int BS, bool CV> static void launch_group(const BatchGroup &g, hipStream_t s)
+template <int P, typename T, bool CV> static void launch_group(const BatchGroup &g, hipStream_t s)
 {
     Launch<T> L;
     memset(&L, 0, sizeof(L));
@@ -2164,18 +2126,18 @@ template <int P, typename T, int BS, bool CV> static void launch_group(const Bat
     L.blk_inst = g.d_bi;
     L.blk_e0 = g.d_be;
     L.bas = g.bas;
-    Impl<P, T, BS, CV>::step_batched(L, g.nblocks, g.wall, s);
+    Impl<P, T, CV>::step_batched(L, g.tiles, g.wall, g.diag, s);
 }
 
 template <typename F> static int group_dispatch(const BatchGroup &g, F &&f)
 {
-    return impl_dispatch(g.N, g.prec, g.bs, g.curved, f);
+    return impl_dispatch(g.N, g.prec, g.curved, f);
 }
 
 static int batch_rebuild(nskr_batch *b)
 {
     batch_free_groups(b);
-    // group active instances by (degree, precision, block size)
+    // group active instances by (degree, precision, curved)
     std::vector<std::vector<int>> members;
     std::vector<BatchGroup> groups;
     for (int i = 0; i < (int)b->slots.size(); ++i) {
@@ -2183,14 +2145,13 @@ static int batch_rebuild(nskr_batch *b)
         if (sl.state != 1) continue;
         int gi = -1;
         for (int k = 0; k < (int)groups.size(); ++k)
-            if (groups[k].N == sl.c->N && groups[k].prec == sl.c->p.precision && groups[k].bs == sl.c->bs &&
+            if (groups[k].N == sl.c->N && groups[k].prec == sl.c->p.precision &&
                 groups[k].curved == sl.c->curved)
                 gi = k;
         if (gi < 0) {
             BatchGroup g;
             g.N = sl.c->N;
             g.prec = sl.c->p.precision;
-            g.bs = sl.c->bs;
             g.curved = sl.c->curved;
             groups.push_back(g);
             members.emplace_back();
@@ -2202,7 +2163,7 @@ static int batch_rebuild(nskr_batch *b)
         BatchGroup &g = groups[k];
         int rc = group_dispatch(g, [&](auto impl) {
             using I = decltype(impl);
-            return build_group<I::kP, typename I::Real, I::kBS, I::kCV>(b, g, members[k]);
+            return build_group<I::kP, typename I::Real, I::kCV>(b, g, members[k]);
         });
         b->groups.push_back(g);
         if (rc) return rc;
@@ -2343,7 +2304,7 @@ int nskr_batch_step(nskr_batch *b, nskr_stream sv)
             for (const auto &g : b->groups)
                 group_dispatch(g, [&](auto impl) {
                     using I = decltype(impl);
-                    launch_group<I::kP, typename I::Real, I::kBS, I::kCV>(g, s);
+                    launch_group<I::kP, typename I::Real, I::kCV>(g, s);
                     return 0;
                 });
             if (b->nticks)
@@ -2356,7 +2317,7 @@ int nskr_batch_step(nskr_batch *b, nskr_stream sv)
         for (const auto &g : b->groups)
             group_dispatch(g, [&](auto impl) {
                 using I = decltype(impl);
-                launch_group<I::kP, typename I::Real, I::kBS, I::kCV>(g, s);
+                launch_group<I::kP, typename I::Real, I::kCV>(g, s);
                 return 0;
             });
         if (b->nticks)
