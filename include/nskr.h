@@ -288,10 +288,10 @@ int nskr_dt(nskr_ctx *ctx, const void *U, double *dt, nskr_stream s);
 
 /* nskr_dt for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
- * same time step, bit for bit, with the reduction's partial maxima and
- * results in a static device array of 4 MiB instead of the context's
- * memory.  It calls no allocating routine; the traces and lifted gradients
- * it evaluates are the context's own, allocated at mesh upload.  Limit: a
+ * same time step, bit for bit, with the reduction's partial maxima in a
+ * static device array of 4 MiB instead of the context's memory.  It calls no
+ * allocating routine; its result goes through the context's pinned host
+ * memory, allocated at mesh upload.  Limit: a
  * mesh of at most 131072 element tiles of the 256-thread reduction kernel
  * (tiles = nelems / floor(256 / (N+1)^3), rounded up; the 32^3 N = 5 mesh
  * has 32768), else NSKR_E_ARG with nothing enqueued.  Every call on one GPU

@@ -178,8 +178,8 @@ template <int P, int BS = kBlock, int EPB_ = BS / (P * P * P)> struct Tile {
 template <int P> struct StageTile {
     static constexpr int kLift1 = P == 3 ? 9 : (P == 6 ? 1 : 2);
     static constexpr int kLift2 = P >= 5 ? 1 : (P == 4 ? 2 : 3);
-    static constexpr int kUpdate = P == 3 ? 9 : 4;
-    static constexpr int kTile = P == 3 ? 9 : 4;
+    static constexpr int kUpdate = P == 3 ? 9 : (P == 4 ? 2 : 4);
+    static constexpr int kTile = P == 3 ? 9 : (P == 4 ? 2 : 4);
     static_assert(kTile % kLift1 == 0 && kTile % kLift2 == 0 && kTile % kUpdate == 0, "tile");
 };
 // Workgroup of EPB elements in whole waves, with a thread for every node and
@@ -1907,7 +1907,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
 }
 
 // ------------------------------------------------------------ k_update
-template <int P> using UpdateGroup = Group<P, StageTile<P>::kUpdate, false>;
+template <int P> using UpdateGroup = Group<P, StageTile<P>::kUpdate, P == 4>;
 
 template <int P, typename T, bool BATCH, bool CV = false, bool NT = false>
 __global__ __launch_bounds__(UpdateGroup<P>::NT) void k_update(Launch<T> L, int tiles)

@@ -52,7 +52,7 @@ struct nskr_ctx {
     void *d_Ck = nullptr;        // Kahan compensation of the FP32 state update
     int *d_clk = nullptr;        // batch: steps since admission (walls whose temperature changes in time)
     double *d_part = nullptr;    // reduction partials
-    double *d_out = nullptr;     // final reduction values (device)
+    double *h_out = nullptr;     // final reduction values (pinned host memory that the kernels write)
     double *d_noise = nullptr;   // init noise
     double *d_drop = nullptr;    // init droplets
     std::vector<float> cent;     // element centroids (host), for the block order
@@ -403,11 +403,14 @@ __device__ __forceinline__ double wave_reduce(int kd, double v)
 }
 
 struct RateArgs {
-    MeshDev mesh; Phys ph; size_t NN; double *part; int nblk;
+    MeshDev mesh; Phys ph; size_t NN; double *part;
+    int tiles;   // element tiles, dealt to the workgroups in turn
     double sig;  // spectral radius of the lifted first derivative (wall limit)
+    double T0;   // initial temperature (kInitEnergy)
+    Basis bas;
 };
 
-// Number of time-step rates reduced by k_dt_rates: the advective rate, the
+// Number of time-step rates reduced by k_nodal: the advective rate, the
 // mesh factor, the diffusivity and the wall rate.
 constexpr int kNRates = 4;
 
@@ -445,59 +448,6 @@ __device__ double wall_rate(const RateArgs &a, int e, const double *em, double r
     return r;
 }
 
-template <int P, typename T, bool CV>
-__global__ __launch_bounds__(kBlock) void k_dt_rates(const T *U, const T *Q, RateArgs a)
-{
-    using G = Tile<P>;
-    __shared__ double sr[kNRates][kBlock / 64];
-    const int t = threadIdx.x;
-    const int e0 = blockIdx.x * G::EPB, le = t / G::n3, e = e0 + le;
-    const size_t g = (size_t)e0 * G::n3 + t;
-    double r0 = 0, r1 = 0, r2 = 0, r3 = 0;
-    if (t < G::NV && e < a.mesh.E) {
-        double rho = U[g], m0 = U[a.NN + g], m1 = U[2 * a.NN + g], m2 = U[3 * a.NN + g];
-        double E = U[4 * a.NN + g], c = U[5 * a.NN + g];
-        double Tn = temperature(a.ph, rho, m0, m1, m2, E, c, Q[12 * a.NN + g], Q[13 * a.NN + g], Q[14 * a.NN + g]);
-        double p, cs2;
-        eos(a.ph, rho, Tn, p, cs2);
-        double cs = sqrt(fabs(cs2 + a.ph.ap * rho));  // sound speed of the convective flux
-        double em[10];
-        if (CV) {
-            const T *nm = (const T *)a.mesh.nmet;
-            for (int r = 0; r < 10; ++r) em[r] = (double)nm[r * a.NN + g];
-        } else {
-            for (int r = 0; r < 10; ++r) em[r] = a.mesh.emet[(size_t)e * 10 + r];
-        }
-        double iJ = 1.0 / em[9];
-        for (int d = 0; d < 3; ++d) {
-            const double *Ja = em + 3 * d;
-            double nJ = sqrt(Ja[0] * Ja[0] + Ja[1] * Ja[1] + Ja[2] * Ja[2]);
-            r0 += (fabs(m0 * Ja[0] + m1 * Ja[1] + m2 * Ja[2]) / rho + cs * nJ) * iJ;
-            double h = 0.5 * nJ * iJ;
-            r1 += h * h;
-        }
-        r2 = fmax(fmax(4.0 * a.ph.mu / (3.0 * rho), a.ph.kappa / (rho * a.ph.R * a.ph.cv)), a.ph.gam * a.ph.beta);
-        if (a.mesh.dyn) {
-            const double gc[3] = {(double)Q[12 * a.NN + g], (double)Q[13 * a.NN + g], (double)Q[14 * a.NN + g]};
-            r3 = wall_rate<P>(a, e, em, rho, gc);
-        }
-        if (!isfinite(r0) || !isfinite(r2) || !isfinite(r3)) r0 = r2 = INFINITY;
-    }
-    const double rv[kNRates] = {r0, r1, r2, r3};
-    const int w = t >> 6, lane = t & 63;
-#pragma unroll
-    for (int k = 0; k < kNRates; ++k) {
-        const double m = wave_reduce(2, rv[k]);
-        if (lane == 0) sr[k][w] = m;
-    }
-    __syncthreads();
-    if (t < kNRates) {
-        double m = sr[t][0];
-        for (int q = 1; q < kBlock / 64; ++q) m = fmax(m, sr[t][q]);
-        a.part[(size_t)t * a.nblk + blockIdx.x] = m;
-    }
-}
-
 // Final pass of a two-level reduction: workgroup k reduces partials
 // part[k][0..nblk) with the operation of kind(k) (0 sum, 1 min, 2 max): each
 // thread over a fixed stride, then the wave shuffles and the waves in order,
@@ -528,69 +478,226 @@ __global__ __launch_bounds__(kBlock) void k_max_final(const double *part, int nb
 // Integrals: kinds 0 = sum, 1 = min, 2 = max for the NSKR_SUM_* slots.
 __device__ __forceinline__ int sum_kind(int k) { return k == 10 || k == 12 ? 1 : (k == 11 || k == 13 ? 2 : 0); }
 
-template <int P, typename T, bool CV>
-__global__ __launch_bounds__(kBlock) void k_integrals(const T *U, const T *Q, RateArgs a, Basis bas)
+// Lifted grad c at one node of a tile, straight from the state: the BR1 face
+// values need the neighbours' c at the face, which each line thread forms
+// from the neighbour's own line of nodes (in the order of the trace that the
+// stage kernels would read), so no trace pass and no stored gradient.  sC:
+// c at the tile's nodes; sS: room for the face values.
+template <int P, typename T, bool CV, typename G>
+__device__ __forceinline__ void lifted_c(const T *U, const MeshDev &m, size_t NN, int t, int e0, const NodeTask<G> &nt, bool act,
+                                         T c, const BasisS<P, T> &B, T *sC, T *sS, V2<T> (*sJ)[CV ? G::NV : 1],
+                                         T (*sJz)[CV ? G::NV : 1], T (*sN)[CV ? G::NF : 1], T qc[3])
 {
-    using G = Tile<P>;
-    __shared__ double sr[NSKR_NSUMS][kBlock / 64];
-    const int t = threadIdx.x;
-    const int e0 = blockIdx.x * G::EPB, le = t / G::n3, e = e0 + le, nd = t - le * G::n3;
-    const size_t g = (size_t)e0 * G::n3 + t;
-    double v[NSKR_NSUMS];
-    for (int k = 0; k < NSKR_NSUMS; ++k) v[k] = 0.0;
-    v[10] = v[12] = INFINITY;
-    v[11] = v[13] = -INFINITY;
-    if (t < G::NV && e < a.mesh.E) {
-        const int i = nd % P, j = (nd / P) % P, k = nd / (P * P);
-        const double Jn = CV ? (double)((const T *)a.mesh.nmet)[9 * a.NN + g] : a.mesh.emet[(size_t)e * 10 + 9];
-        const double wJ = bas.w[i] * bas.w[j] * bas.w[k] * Jn;
-        double u[6];
-        bool bad = false;
-        for (int q = 0; q < 6; ++q) {
-            u[q] = (double)U[q * a.NN + g];
-            if (!isfinite(u[q])) bad = true;
-        }
-        if (bad) {
-            v[14] = 1.0;
-        } else {
-            const double q0 = Q[12 * a.NN + g], q1 = Q[13 * a.NN + g], q2 = Q[14 * a.NN + g];
-            const double rho = u[0];
-            const double Tn = temperature(a.ph, rho, u[1], u[2], u[3], u[4], u[5], q0, q1, q2);
-            double p, cs2;
-            eos(a.ph, rho, Tn, p, cs2);
-            if (!(rho > 0.0 && rho * a.ph.b < 1.0)) v[15] = 1.0;
-            if (!(Tn > 0.0)) v[16] = 1.0;
-            if (cs2 < 0.0) v[17] = 1.0;
-            const double g2 = q0 * q0 + q1 * q1 + q2 * q2;
-            v[0] = wJ * rho;
-            v[1] = wJ * u[1];
-            v[2] = wJ * u[2];
-            v[3] = wJ * u[3];
-            v[4] = wJ * u[4];
-            v[5] = wJ * u[5];
-            v[6] = wJ * 0.5 * (u[1] * u[1] + u[2] * u[2] + u[3] * u[3]) / rho;
-            v[7] = wJ * 0.5 * a.ph.gam * g2;
-            v[8] = wJ * 0.5 * a.ph.alpha * (rho - u[5]) * (rho - u[5]);
-            v[9] = wJ * (rho - u[5]) * (rho - u[5]);
-            v[10] = v[11] = rho;
-            v[12] = v[13] = Tn;
-            if (a.ph.b > 0.0 && Tn > 0.0 && rho > 0.0 && rho * a.ph.b < 1.0)
-                v[18] = -wJ * rho * (a.ph.R * a.ph.cv * log(Tn) - a.ph.R * log(a.ph.b * rho / (1.0 - a.ph.b * rho)));
-            v[19] = wJ;
+    const int E = m.E;
+    const int ltask = line_of_thread<G>(t);
+    const LineTask<P> lt(ltask < 0 ? 0 : ltask);
+    const int el = e0 + lt.le;
+    const bool lact = ltask >= 0 && el < E;
+    T vn[2][P];
+    int side[2] = {-1, -1};  // of the neighbour's face; -1: wall
+    if (lact) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int code = gld(m.nbr, el * 6 + 2 * lt.d + s);
+            if (code < 0) continue;
+            const int face = code >> 3, en = face / 6, f = face - 6 * en, d = f >> 1, fp = nbr_point<P>(code, lt.fp);
+            const int p = fp % P, q = fp / P;
+            const int off = d == 0 ? P * fp : (d == 1 ? p + P * P * q : fp), str = d == 0 ? 1 : (d == 1 ? P : P * P);
+            const uint32_t g = (uint32_t)en * G::n3 + off;
+            side[s] = f & 1;
+#pragma unroll
+            for (int l = 0; l < P; ++l) vn[s][l] = gld(U + 5 * NN, g + l * str);
         }
     }
-    const int w = t >> 6, lane = t & 63;
-#pragma unroll
-    for (int k = 0; k < NSKR_NSUMS; ++k) {
-        const double m = wave_reduce(sum_kind(k), v[k]);
-        if (lane == 0) sr[k][w] = m;
+    T iJ = T(0);
+    if (act) {
+        sC[nt.q] = c;
+        if constexpr (CV) iJ = stage_node_metrics<T, G::NV>(m, NN, (size_t)e0 * G::n3 + nt.q, nt.q, sJ, sJz);
     }
     __syncthreads();
-    if (t < NSKR_NSUMS) {
-        const int kd = sum_kind(t);
-        double m = sr[t][0];
-        for (int q = 1; q < kBlock / 64; ++q) m = combine(kd, m, sr[t][q]);
-        a.part[(size_t)t * a.nblk + blockIdx.x] = m;
+    if (lact) {
+        T own[2];
+        prolong2<P, T>(sC, lt.le * G::n3, B, lt, own[0], own[1]);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int f = 2 * lt.d + s, slot = lt.le * 6 * G::n2 + f * G::n2 + lt.fp;
+            if constexpr (CV) {
+                T n[3], dS;
+                face_normal<P, T, true>(m, (size_t)el * 6 + f, lt.fp, n, dS);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) sN[k][slot] = n[k] * dS;
+            }
+            T cs = own[s];
+            if (side[s] >= 0) {
+                T cn = T(0);
+#pragma unroll
+                for (int l = 0; l < P; ++l) cn += B.Lf[side[s] * B.PS + l] * vn[s][l];
+                cs = T(0.5) * (own[s] + cn);
+            }
+            sS[slot] = cs;
+        }
+    }
+    __syncthreads();
+    qc[0] = qc[1] = qc[2] = T(0);
+    if (!act) return;
+    const int i = nt.nd % P, j = (nt.nd / P) % P, k = nt.nd / (P * P);
+    const int base = nt.le * G::n3, fbase = nt.le * 6 * G::n2;
+    if constexpr (CV) {
+        T q[1][3];
+        lifted_grads_curved<P, 1, G::NV, G::NF>([&](int n, T v[1]) { v[0] = sC[n]; }, [&](int n, T v[1]) { v[0] = sS[n]; }, sJ,
+                                                sJz, sN, base, fbase, i, j, k, B, iJ, q);
+#pragma unroll
+        for (int r = 0; r < 3; ++r) qc[r] = q[0][r];
+    } else {
+        T Ja[9];
+        element_metrics<G::kUni>(m, e0 + nt.le, Ja, iJ);
+        lifted_grad<P, T>(sC, sS, base, fbase, i, j, k, B, Ja, iJ, qc);
+    }
+}
+
+// What the point-wise evaluations outside a stage need: the state and the
+// lifted grad c at every node, evaluated and reduced in one pass over the
+// state.  kRates: maxima of the time-step rates; kSums: the integrals and
+// counters; kInitEnergy: rho e of the initial state.  The three used to read
+// grad c back from the gradients that a face-trace pass and the full first
+// lifting had stored (18 words written per node): 24^3 elements of N = 4 in
+// FP64 took 206 us a time step and 255 us a set of integrals, synchronisation
+// and the host's call included; now 63 and 72 us.
+enum { kRates, kSums, kInitEnergy };
+
+template <int P, typename T, bool CV, int WHAT>
+__global__ __launch_bounds__(kBlock, CV ? 1 : 4) void k_nodal(const T *U, T *Uw, RateArgs a)
+{
+    using G = Tile<P>;
+    constexpr int NK = WHAT == kRates ? kNRates : NSKR_NSUMS;
+    constexpr int NJ = CV ? 3 : 1, NJV = CV ? G::NV : 1, NQF = CV ? G::NF : 1;
+    __shared__ T sC[G::NV], sS[G::NF];
+    __shared__ V2<T> sJ[NJ][NJV];
+    __shared__ T sJz[NJ][NJV];
+    __shared__ T sN[NJ][NQF];
+    __shared__ BasisS<P, T> B;
+    __shared__ double sr[NK][kBlock / 64];
+    B.load(a.bas);
+    double tot[NK];
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+        const int kd = WHAT == kRates ? 2 : sum_kind(k);
+        tot[k] = WHAT == kRates || kd == 0 ? 0.0 : (kd == 1 ? INFINITY : -INFINITY);
+    }
+    for (int tile = blockIdx.x; tile < a.tiles; tile += gridDim.x) {
+        if (tile != (int)blockIdx.x) __syncthreads();  // the tile before is read
+        // (an opaque thread index: what follows from it is formed again for each
+        // tile instead of being kept in registers across them)
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        const NodeTask<G> nt(t);
+        const int e0 = tile * G::EPB, e = e0 + nt.le;
+        const bool act = nt.in && e < a.mesh.E;
+        const size_t g = (size_t)e0 * G::n3 + nt.q;
+        const uint32_t g32 = (uint32_t)g;
+        T un[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
+        if (act) {
+#pragma unroll
+            for (int v = 0; v < 6; ++v)
+                if (WHAT != kInitEnergy || v != 4) un[v] = gld(U + v * a.NN, g32);
+        }
+        T qc[3];
+        lifted_c<P, T, CV, G>(U, a.mesh, a.NN, t, e0, nt, act, un[5], B, sC, sS, sJ, sJz, sN, qc);
+        const double q0 = (double)qc[0], q1 = (double)qc[1], q2 = (double)qc[2];
+        const double u[6] = {(double)un[0], (double)un[1], (double)un[2], (double)un[3], (double)un[4], (double)un[5]};
+        const double rho = u[0];
+        if constexpr (WHAT == kInitEnergy) {
+            if (act)
+                gst(Uw + 4 * a.NN, g32, T(rho * (a.ph.R * a.ph.cv * a.T0 - a.ph.a * rho) +
+                                          0.5 * a.ph.gam * (q0 * q0 + q1 * q1 + q2 * q2) +
+                                          0.5 * (u[1] * u[1] + u[2] * u[2] + u[3] * u[3]) / rho));
+            continue;
+        }
+        double v[NK];
+#pragma unroll
+        for (int k = 0; k < NK; ++k) v[k] = 0.0;
+        if constexpr (WHAT == kRates) {
+            if (act) {
+                const double Tn = temperature(a.ph, rho, u[1], u[2], u[3], u[4], u[5], q0, q1, q2);
+                double p, cs2;
+                eos(a.ph, rho, Tn, p, cs2);
+                const double cs = sqrt(fabs(cs2 + a.ph.ap * rho));  // sound speed of the convective flux
+                double em[10];
+                if (CV) {
+                    const T *nm = (const T *)a.mesh.nmet;
+                    for (int r = 0; r < 10; ++r) em[r] = (double)nm[r * a.NN + g];
+                } else {
+                    for (int r = 0; r < 10; ++r) em[r] = a.mesh.emet[(size_t)e * 10 + r];
+                }
+                const double iJ = 1.0 / em[9];
+                for (int d = 0; d < 3; ++d) {
+                    const double *Ja = em + 3 * d;
+                    const double nJ = sqrt(Ja[0] * Ja[0] + Ja[1] * Ja[1] + Ja[2] * Ja[2]);
+                    v[0] += (fabs(u[1] * Ja[0] + u[2] * Ja[1] + u[3] * Ja[2]) / rho + cs * nJ) * iJ;
+                    const double h = 0.5 * nJ * iJ;
+                    v[1] += h * h;
+                }
+                v[2] = fmax(fmax(4.0 * a.ph.mu / (3.0 * rho), a.ph.kappa / (rho * a.ph.R * a.ph.cv)), a.ph.gam * a.ph.beta);
+                if (a.mesh.dyn) {
+                    const double gc[3] = {q0, q1, q2};
+                    v[3] = wall_rate<P>(a, e, em, rho, gc);
+                }
+                if (!isfinite(v[0]) || !isfinite(v[2]) || !isfinite(v[3])) v[0] = v[2] = INFINITY;
+            }
+        } else {
+            v[10] = v[12] = INFINITY;
+            v[11] = v[13] = -INFINITY;
+            if (act) {
+                const int i = nt.nd % P, j = (nt.nd / P) % P, k = nt.nd / (P * P);
+                const double Jn = CV ? (double)((const T *)a.mesh.nmet)[9 * a.NN + g] : a.mesh.emet[(size_t)e * 10 + 9];
+                const double wJ = a.bas.w[i] * a.bas.w[j] * a.bas.w[k] * Jn;
+                bool bad = false;
+                for (int q = 0; q < 6; ++q)
+                    if (!isfinite(u[q])) bad = true;
+                if (bad) {
+                    v[14] = 1.0;
+                } else {
+                    const double Tn = temperature(a.ph, rho, u[1], u[2], u[3], u[4], u[5], q0, q1, q2);
+                    double p, cs2;
+                    eos(a.ph, rho, Tn, p, cs2);
+                    if (!(rho > 0.0 && rho * a.ph.b < 1.0)) v[15] = 1.0;
+                    if (!(Tn > 0.0)) v[16] = 1.0;
+                    if (cs2 < 0.0) v[17] = 1.0;
+                    const double g2 = q0 * q0 + q1 * q1 + q2 * q2;
+                    v[0] = wJ * rho;
+                    v[1] = wJ * u[1];
+                    v[2] = wJ * u[2];
+                    v[3] = wJ * u[3];
+                    v[4] = wJ * u[4];
+                    v[5] = wJ * u[5];
+                    v[6] = wJ * 0.5 * (u[1] * u[1] + u[2] * u[2] + u[3] * u[3]) / rho;
+                    v[7] = wJ * 0.5 * a.ph.gam * g2;
+                    v[8] = wJ * 0.5 * a.ph.alpha * (rho - u[5]) * (rho - u[5]);
+                    v[9] = wJ * (rho - u[5]) * (rho - u[5]);
+                    v[10] = v[11] = rho;
+                    v[12] = v[13] = Tn;
+                    if (a.ph.b > 0.0 && Tn > 0.0 && rho > 0.0 && rho * a.ph.b < 1.0)
+                        v[18] = -wJ * rho * (a.ph.R * a.ph.cv * log(Tn) - a.ph.R * log(a.ph.b * rho / (1.0 - a.ph.b * rho)));
+                    v[19] = wJ;
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < NK; ++k) tot[k] = combine(WHAT == kRates ? 2 : sum_kind(k), tot[k], v[k]);
+    }
+    if constexpr (WHAT == kInitEnergy) return;
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+        const double r = wave_reduce(WHAT == kRates ? 2 : sum_kind(k), tot[k]);
+        if (lane == 0) sr[k][w] = r;
+    }
+    __syncthreads();
+    if (t < NK) {
+        const int kd = WHAT == kRates ? 2 : sum_kind(t);
+        double r = sr[t][0];
+        for (int q = 1; q < kBlock / 64; ++q) r = combine(kd, r, sr[t][q]);
+        a.part[(size_t)t * gridDim.x + blockIdx.x] = r;
     }
 }
 
@@ -646,20 +753,6 @@ __global__ __launch_bounds__(kBlock) void k_init_rho(T *U, InitArgs a)
     U[3 * a.NN + g] = T(rho * u[2]);
     U[4 * a.NN + g] = T(0);
     U[5 * a.NN + g] = T(rho);
-}
-
-template <int P, typename T>
-__global__ __launch_bounds__(kBlock) void k_init_energy(T *U, const T *Q, int E, size_t NN, Phys ph, double T0)
-{
-    using G = Tile<P>;
-    const int t = threadIdx.x;
-    const int e0 = blockIdx.x * G::EPB, le = t / G::n3, e = e0 + le;
-    if (t >= G::NV || e >= E) return;
-    const size_t g = (size_t)e0 * G::n3 + t;
-    const double rho = U[g], m0 = U[NN + g], m1 = U[2 * NN + g], m2 = U[3 * NN + g];
-    const double q0 = Q[12 * NN + g], q1 = Q[13 * NN + g], q2 = Q[14 * NN + g];
-    U[4 * NN + g] = T(rho * (ph.R * ph.cv * T0 - ph.a * rho) + 0.5 * ph.gam * (q0 * q0 + q1 * q1 + q2 * q2) +
-                      0.5 * (m0 * m0 + m1 * m1 + m2 * m2) / rho);
 }
 
 // Zero fill (used instead of a memset so that it can sit in captured graphs).
@@ -848,48 +941,41 @@ template <int P, typename T, bool CV> struct Impl {
         return NSKR_OK;
     }
     // the largest wave speed, mesh factor, diffusivity and wall rate over the
-    // nodes; part holds kNRates partial maxima per tile, dout the results (device)
-    static int dt(nskr_ctx *c, const void *U, double *rates, hipStream_t s, double *part, double *dout)
+    // nodes; part holds kNRates partial maxima per tile
+    // workgroups of k_nodal: what the card holds at once (4 per CU); each takes
+    // its tiles in turn and reduces once at the end.  One reduction per tile, 20
+    // values over 64 lanes, cost 44 of a call's 115 us on 24^3 N = 4 in FP64; 512
+    // and 2048 workgroups take 83 and 79 us where 1024 take 72.
+    static int nodal_grid(const nskr_ctx *c) { return std::min(nblk256(c), 1024); }
+    template <int WHAT> static void nodal(const nskr_ctx *c, const T *U, T *Uw, double *part, double T0, hipStream_t s)
     {
-        Launch<T> L = launch(c, inst(c, U, nullptr, nullptr, 0.0));
-        L.full = 1;  // every lifted gradient and the nodal temperature
-        prolong(c, L, s);
-        lift1(c, L, s);
-        RateArgs a{mesh(c), c->ph, c->NN, part, nblk256(c), kSigN[P - 1]};
-        hipLaunchKernelGGL((k_dt_rates<P, T, CV>), dim3(nblk256(c)), dim3(kBlock), 0, s, (const T *)U,
-                           (const T *)c->d_Q, a);
-        hipLaunchKernelGGL(k_max_final, dim3(kNRates), dim3(kBlock), 0, s, (const double *)part, nblk256(c), dout);
+        RateArgs a{mesh(c), c->ph, c->NN, part, nblk256(c), kSigN[P - 1], T0, c->bas};
+        hipLaunchKernelGGL((k_nodal<P, T, CV, WHAT>), dim3(nodal_grid(c)), dim3(kBlock), 0, s, U, Uw, a);
+    }
+    static int dt(nskr_ctx *c, const void *U, double *rates, hipStream_t s, double *part)
+    {
+        nodal<kRates>(c, (const T *)U, nullptr, part, 0.0, s);
+        hipLaunchKernelGGL(k_max_final, dim3(kNRates), dim3(kBlock), 0, s, (const double *)part, nodal_grid(c), c->h_out);
         HIPCHK(c, hipGetLastError());
-        HIPCHK(c, hipMemcpyAsync(rates, dout, kNRates * sizeof(double), hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipStreamSynchronize(s));
+        for (int k = 0; k < kNRates; ++k) rates[k] = c->h_out[k];
         return NSKR_OK;
     }
     static int reduce(nskr_ctx *c, const void *U, double *out, hipStream_t s)
     {
-        Launch<T> L = launch(c, inst(c, U, nullptr, nullptr, 0.0));
-        L.full = 1;  // every lifted gradient and the nodal temperature
-        prolong(c, L, s);
-        lift1(c, L, s);
-        RateArgs a{mesh(c), c->ph, c->NN, c->d_part, nblk256(c), 0.0};
-        hipLaunchKernelGGL((k_integrals<P, T, CV>), dim3(nblk256(c)), dim3(kBlock), 0, s, (const T *)U,
-                           (const T *)c->d_Q, a, c->bas);
+        nodal<kSums>(c, (const T *)U, nullptr, c->d_part, 0.0, s);
         hipLaunchKernelGGL(k_integrals_final, dim3(NSKR_NSUMS), dim3(kBlock), 0, s, (const double *)c->d_part,
-                           nblk256(c), c->d_out);
+                           nodal_grid(c), c->h_out);
         HIPCHK(c, hipGetLastError());
-        HIPCHK(c, hipMemcpyAsync(out, c->d_out, NSKR_NSUMS * sizeof(double), hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipStreamSynchronize(s));
+        for (int k = 0; k < NSKR_NSUMS; ++k) out[k] = c->h_out[k];
         return NSKR_OK;
     }
     static int init(nskr_ctx *c, const InitArgs &ia, double T0, void *Uv, hipStream_t s)
     {
         T *U = (T *)Uv;
         hipLaunchKernelGGL((k_init_rho<P, T, CV>), dim3(nblk256(c)), dim3(kBlock), 0, s, U, ia);
-        Launch<T> L = launch(c, inst(c, U, nullptr, nullptr, 0.0));
-        L.full = 1;
-        prolong(c, L, s);
-        lift1(c, L, s);
-        hipLaunchKernelGGL((k_init_energy<P, T>), dim3(nblk256(c)), dim3(kBlock), 0, s, U, (const T *)c->d_Q, c->E,
-                           c->NN, c->ph, T0);
+        nodal<kInitEnergy>(c, U, U, nullptr, T0, s);
         HIPCHK(c, hipGetLastError());
         return NSKR_OK;
     }
@@ -1009,13 +1095,13 @@ static int build_block_map(nskr_ctx *c)
 }
 
 // Reduction scratch of nskr_dt_noalloc, for callers that cannot allocate:
-// kNRates partial maxima per element tile of the 256-thread reduction kernel,
-// then the kNRates results.  Each device holds its own copy for the life of the
+// kNRates partial maxima per element tile of the 256-thread reduction kernel.
+// Each device holds its own copy for the life of the
 // process; its address on each device is looked up once, at the first
 // nskr_create on that device, and only that address is handed to kernels.
 // Every partial is written before it is read, so nothing needs clearing.
 constexpr int kStaticTiles = 131072;
-static __device__ __align__(256) double scratch[kNRates * (kStaticTiles + 1)];
+static __device__ __align__(256) double scratch[kNRates * kStaticTiles];
 
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mtx;
@@ -1241,7 +1327,7 @@ int nskr_create(const nskr_params *p, int N, int device, nskr_ctx **out)
 static void free_mesh(nskr_ctx *c)
 {
     void *ptrs[] = {c->d_nbr, c->d_bcid, c->d_emet, c->d_em, c->d_egeo, c->d_bcs, c->d_Q, c->d_TH,
-                    c->d_G2, c->d_T2, c->d_TF, c->d_TU, c->d_part, c->d_out, c->d_noise, c->d_drop, c->d_Ck,
+                    c->d_G2, c->d_T2, c->d_TF, c->d_TU, c->d_part, c->d_noise, c->d_drop, c->d_Ck,
                     c->d_stab, c->d_clk, c->d_nmet, c->d_fnrm, c->d_xnode, c->d_bmap};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
@@ -1255,7 +1341,9 @@ static void free_mesh(nskr_ctx *c)
     c->d_stab = nullptr;
     c->d_clk = nullptr;
     c->d_Q = c->d_TH = c->d_G2 = c->d_T2 = c->d_TF = c->d_TU = c->d_Ck = nullptr;
-    c->d_part = c->d_out = c->d_noise = c->d_drop = nullptr;
+    c->d_part = c->d_noise = c->d_drop = nullptr;
+    if (c->h_out) (void)hipHostFree(c->h_out);
+    c->h_out = nullptr;
     c->d_bmap = nullptr;
     std::vector<float>().swap(c->cent);
     c->E = 0;
@@ -1706,12 +1794,16 @@ int nskr_mesh_upload(nskr_ctx *c, const nskr_mesh *m, nskr_stream sv)
         (rc = dalloc(c, &c->d_G2, ts * 4 * c->NN)) || (rc = dalloc(c, &c->d_T2, ts * (ts == 4 ? kT2<float>() : kT2<double>()) * c->NF)) ||
         (rc = dalloc(c, &c->d_TF, ts * 6 * c->NF)) || (rc = dalloc(c, &c->d_TU, ts * 3 * 6 * c->NF)) ||
         (rc = dalloc(c, (void **)&c->d_part, sizeof(double) * NSKR_NSUMS * (size_t)nblk)) ||
-        (rc = dalloc(c, (void **)&c->d_out, sizeof(double) * NSKR_NSUMS)) ||
         (c->p.precision == 1 && c->p.kahan && (rc = dalloc(c, &c->d_Ck, ts * 6 * c->NN))) ||
         (tab && (rc = dalloc(c, (void **)&c->d_stab, sizeof(double) * tab->size()))) ||
         (trate && (rc = dalloc(c, (void **)&c->d_clk, sizeof(int))))) {
         free_mesh(c);
         return rc;
+    }
+    if (hipHostMalloc((void **)&c->h_out, sizeof(double) * NSKR_NSUMS, hipHostMallocDefault) != hipSuccess) {
+        c->h_out = nullptr;
+        free_mesh(c);
+        return fail(c, NSKR_E_NOMEM, "pinned host allocation failed");
     }
     // curved metrics in the element type of the precision
     auto upload_real = [&](void *dst, const std::vector<double> &v) -> hipError_t {
@@ -1908,7 +2000,7 @@ int nskr_dt(nskr_ctx *c, const void *U, double *dt, nskr_stream sv)
     if (!U || !dt) return fail(c, NSKR_E_ARG, "null argument");
     DeviceGuard guard(c->device);
     double r[kNRates];
-    rc = dispatch(c, [&](auto impl) { return decltype(impl)::dt(c, U, r, (hipStream_t)sv, c->d_part, c->d_out); });
+    rc = dispatch(c, [&](auto impl) { return decltype(impl)::dt(c, U, r, (hipStream_t)sv, c->d_part); });
     if (rc) return rc;
     return dt_from_rates(c, r, dt);
 }
@@ -1927,7 +2019,7 @@ int nskr_dt_noalloc(nskr_ctx *c, const void *U, double *dt, nskr_stream sv)
     DeviceGuard guard(c->device);
     double r[kNRates];
     rc = dispatch(c, [&](auto impl) {
-        return decltype(impl)::dt(c, U, r, (hipStream_t)sv, ptr, ptr + kNRates * (size_t)kStaticTiles);
+        return decltype(impl)::dt(c, U, r, (hipStream_t)sv, ptr);
     });
     if (rc) return rc;
     return dt_from_rates(c, r, dt);
