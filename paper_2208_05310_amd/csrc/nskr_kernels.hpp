@@ -192,9 +192,9 @@ template <int P, int EPB, bool FACES> struct Group {
     // workgroups of `tiles` tiles: the tiles of each XCD (tile mod 8, as the
     // hardware deals out workgroups) keep their XCD
     static int grid(int tiles) { return kSub == 1 ? tiles : (tiles + 7) / 8 * 8 * kSub; }
-    // this workgroup's tile and its place in it, in elements
-    static __device__ __forceinline__ int tile() { return kSub == 1 ? blockIdx.x : blockIdx.x / (8 * kSub) * 8 + blockIdx.x % 8; }
-    static __device__ __forceinline__ int part() { return kSub == 1 ? 0 : blockIdx.x / 8 % kSub * EPB; }
+    // the tile of workgroup b and its place in it, in elements
+    static __device__ __forceinline__ int tile(int b) { return kSub == 1 ? b : b / (8 * kSub) * 8 + b % 8; }
+    static __device__ __forceinline__ int part(int b) { return kSub == 1 ? 0 : b / 8 % kSub * EPB; }
 };
 
 // Node thread of a workgroup: local element, node of the element, and the
@@ -507,7 +507,7 @@ template <typename P> __device__ __forceinline__ P load_const(const P *p, int i)
 template <int P, typename W, bool BATCH, typename T>
 __device__ __forceinline__ bool instance_of(const Launch<T> &L, Inst<T> &a, int &e0, int tiles)
 {
-    const int b = W::tile();
+    const int b = W::tile(blockIdx.x);
     if (b >= tiles) return false;
     if (BATCH) {
         const int k = load_const(L.blk_inst, b);
@@ -517,7 +517,7 @@ __device__ __forceinline__ bool instance_of(const Launch<T> &L, Inst<T> &a, int 
         a = L.one;
         e0 = load_const(L.blk_map, b);
     }
-    e0 += W::part();
+    e0 += W::part(blockIdx.x);
     return true;
 }
 
@@ -582,6 +582,17 @@ template <int P> struct LineTask {
     }
 };
 
+// Bounds the loads that a sweep keeps in flight: what has been loaded is
+// summed into a[0..n) before anything that follows is loaded.  Without it the
+// compiler requests a whole line of every field at once and needs the
+// registers of one or two waves per SIMD for it.
+template <typename T> __device__ __forceinline__ void bound(T *a, int n)
+{
+#pragma unroll
+    for (int k = 0; k < n; ++k) asm volatile("" : "+v"(a[k]));
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // Prolongation of one LDS field of an element, or of a pair of fields, to
 // both faces of a line.
 template <int P, typename T>
@@ -600,24 +611,25 @@ __device__ __forceinline__ void prolong2(const T *s, int base, const BasisS<P, T
     vm = am;
     vp = ap;
 }
-template <int P, typename T>
+template <int P, typename T, bool LIM = false>
 __device__ __forceinline__ void prolong2(const V2<T> *s, int base, const BasisS<P, T> &B, const LineTask<P> &lt,
                                          T *vm, T *vp)
 {
-    T am0 = T(0), ap0 = T(0), am1 = T(0), ap1 = T(0);
+    T a[4] = {T(0), T(0), T(0), T(0)};
     const V2<T> *ln = s + base + lt.off;
 #pragma unroll
     for (int l = 0; l < P; ++l) {
         const V2<T> v = ln[l * lt.str], w = B.L[l];
-        am0 += w.x * v.x;
-        ap0 += w.y * v.x;
-        am1 += w.x * v.y;
-        ap1 += w.y * v.y;
+        a[0] += w.x * v.x;
+        a[1] += w.y * v.x;
+        a[2] += w.x * v.y;
+        a[3] += w.y * v.y;
+        if (LIM && l % 2 == 1) bound(a, 4);
     }
-    vm[0] = am0;
-    vm[1] = am1;
-    vp[0] = ap0;
-    vp[1] = ap1;
+    vm[0] = a[0];
+    vm[1] = a[2];
+    vp[0] = a[1];
+    vp[1] = a[3];
 }
 
 // Face task: face point fp of face f of local element le, with the line of
@@ -729,7 +741,7 @@ __device__ __forceinline__ WallPt wall_point(const MeshDev &m, const Basis &bas,
 // J q_m = sum_d Ja^d_m (Dhat w + lhat(+1) w*_+ - lhat(-1) w*_-), from the node
 // values fw (element starting at base) and face values fs (element's face
 // points starting at fbase) in LDS.
-template <int P, typename T>
+template <int P, typename T, bool LIM = false>
 __device__ __forceinline__ void lifted_grad(const T *fw, const T *fs, int base, int fbase, int i, int j, int k,
                                             const BasisS<P, T> &B, const T Ja[9], T iJ, T q[3])
 {
@@ -744,6 +756,7 @@ __device__ __forceinline__ void lifted_grad(const T *fw, const T *fs, int base, 
         B.row(B.Dh + idx[d] * B.PS, D);
 #pragma unroll
         for (int l = 0; l < P; ++l) acc += D[l] * fw[base + line_node<P>(d, l, p, r)];
+        if (LIM) bound(&acc, 1);
         const V2<T> lh = B.Lh[idx[d]];
         acc += lh.y * fs[fbase + (2 * d + 1) * n2 + fpd[d]];
         acc -= lh.x * fs[fbase + (2 * d) * n2 + fpd[d]];
@@ -751,17 +764,6 @@ __device__ __forceinline__ void lifted_grad(const T *fw, const T *fs, int base, 
     }
 #pragma unroll
     for (int m = 0; m < 3; ++m) q[m] = iJ * (Ja[m] * gd[0] + Ja[3 + m] * gd[1] + Ja[6 + m] * gd[2]);
-}
-
-// Bounds the loads that a sweep keeps in flight: what has been loaded is
-// summed into a[0..n) before anything that follows is loaded.  Without it the
-// compiler requests a whole line of every field at once and needs the
-// registers of one or two waves per SIMD for it.
-template <typename T> __device__ __forceinline__ void bound(T *a, int n)
-{
-#pragma unroll
-    for (int k = 0; k < n; ++k) asm volatile("" : "+v"(a[k]));
-    __builtin_amdgcn_sched_barrier(0);
 }
 
 // Five fields of a tile: two rows of pairs and one single row.
@@ -951,20 +953,24 @@ __global__ __launch_bounds__(ProlongGroup<P>::NT) void k_prolong(Launch<T> L, in
 // Lifted grad c, and the own-face traces of grad c and of the face
 // temperature.  FULL: also every lifted gradient and the nodal temperature
 // (Q, TH) for the API outputs.
-// The per-stage instances on affine elements in 256-thread workgroups are
-// latency-bound and keep as many waves per SIMD as their LDS allows without
-// register spills: 7 in FP32 (8 spills; so does 7 in 448-thread
-// workgroups), and in FP64 8 at N = 5 (63 registers instead of 79) and 6 at
-// N = 3 (80 instead of 83).
-template <int P, typename T, bool FULL, bool CV> constexpr int lift1_waves()
+// The per-stage instances are bound by the latency of their short phases and
+// keep as many waves per SIMD as their registers allow without spills.
+// PIPE (meshes of many groups per resident workgroup): the workgroup takes
+// every gridDim-th group of elements and has the next group's c, connectivity
+// and neighbour traces in flight while it works on one.  One group per
+// workgroup / pipelined: 32^3 N = 5 112 / 97 us in FP64, 85 / 70 in FP32-mixed;
+// 50^3 N = 3 FP64 116 / 103; where the groups are few the loop only costs
+// (16^3 N = 4 FP64 8.6 / 9.3, 4^3 N = 3 4.2 / 5.4).
+template <int P, typename T, bool FULL, bool CV, bool PIPE> constexpr int lift1_waves()
 {
     if (FULL || CV) return 1;
+    if (PIPE) return sizeof(T) == 4 || P == 4 ? 8 : 6;  // (P == 6 FP64 at 7: 13 spills, 126 us against 97)
     return sizeof(T) == 4 ? 7 : (P == 6 ? 8 : (P == 4 ? 6 : 1));
 }
 template <int P> using Lift1Group = Group<P, StageTile<P>::kLift1, false>;
 
-template <int P, typename T, bool BATCH, bool FULL = false, bool CV = false>
-__global__ __launch_bounds__(Lift1Group<P>::NT, (lift1_waves<P, T, FULL, CV>())) void k_lift1(Launch<T> L, int tiles)
+template <int P, typename T, bool BATCH, bool FULL = false, bool CV = false, bool PIPE = false>
+__global__ __launch_bounds__(Lift1Group<P>::NT, (lift1_waves<P, T, FULL, CV, PIPE>())) void k_lift1(Launch<T> L, int tiles)
 {
     using W = Lift1Group<P>;
     using G = typename W::G;
@@ -972,6 +978,7 @@ __global__ __launch_bounds__(Lift1Group<P>::NT, (lift1_waves<P, T, FULL, CV>()))
     Inst<T> a;
     int e0;
     if (!instance_of<P, W, BATCH>(L, a, e0, tiles)) return;
+    static_assert(!PIPE || (!BATCH && !FULL && !CV), "one instance, affine elements");
     static_assert(n_lines<G>() <= BS, "one line per thread");
     // state (c only, or with FULL all of it) and primitives (FULL), BR1 face
     // values of c or of all primitives
@@ -989,192 +996,244 @@ __global__ __launch_bounds__(Lift1Group<P>::NT, (lift1_waves<P, T, FULL, CV>()))
     __shared__ BasisS<P, T> B;
     B.load(L.bas);
     const int E = a.mesh.E;
-    const int t = threadIdx.x;
-    const NodeTask<G> nt(t);
-    const int le = nt.le, nd = nt.nd, tq = nt.q;
-    const int e = e0 + le;
-    const bool act = nt.in && e < E;
-    const size_t g = (size_t)e0 * G::n3 + tq;
-    const uint32_t g32 = (uint32_t)g;
     const size_t NF = (size_t)E * 6 * G::n2;
     constexpr bool full = FULL;
     const T *TU = a.TU + (size_t)L.tb * 6 * NF;
 
     // early loads: own nodes, and the neighbour traces of this thread's line
-    const int ltask = line_of_thread<G>(t);
-    const LineTask<P> lt(ltask < 0 ? 0 : ltask);
-    const int el = e0 + lt.le;
-    const bool lact = ltask >= 0 && el < E;
     int nbm = -1, nbp = -1;
-    T wn[2][6];
-    if (lact) {
-        nbm = gld(a.mesh.nbr, el * 6 + 2 * lt.d);
-        nbp = gld(a.mesh.nbr, el * 6 + 2 * lt.d + 1);
+    T wn[2][6], c0 = T(0);
+    auto load_codes = [&](int t, int first, int &cm, int &cp) {
+        cm = cp = -1;
+        const int ltask = line_of_thread<G>(t);
+        const LineTask<P> lt(ltask < 0 ? 0 : ltask);
+        const int el = first + lt.le;
+        if (ltask < 0 || el >= E) return;
+        cm = gld(a.mesh.nbr, el * 6 + 2 * lt.d);
+        cp = gld(a.mesh.nbr, el * 6 + 2 * lt.d + 1);
+    };
+    auto load_traces = [&](int t, int cm, int cp, T w[2][6]) {
+        const int ltask = line_of_thread<G>(t);
+        const LineTask<P> lt(ltask < 0 ? 0 : ltask);
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            const int nb = s ? nbp : nbm;
+            const int nb = s ? cp : cm;
             if (nb >= 0) {
                 const FaceIx<G::n2> o(nbr_face<P>(nb), nbr_point<P>(nb, lt.fp));
                 if (full) {
 #pragma unroll
                     for (int v = 0; v < 6; ++v)
-                        if (v != 4) wn[s][v] = TU[o.at(6, v)];
+                        if (v != 4) w[s][v] = TU[o.at(6, v)];
                 } else {
-                    wn[s][5] = TU[o.at(6, 5)];
+                    w[s][5] = TU[o.at(6, 5)];
                 }
             }
         }
+    };
+    auto load_c = [&](int t, int first) -> T {
+        const NodeTask<G> nt(t);
+        const int le = nt.le, tq = nt.q;
+        return nt.in && first + le < E ? gld(a.U + 5 * a.NN, (uint32_t)first * G::n3 + tq) : T(0);
+    };
+    load_codes(threadIdx.x, e0, nbm, nbp);
+    if (!FULL) c0 = load_c(threadIdx.x, e0);
+    load_traces(threadIdx.x, nbm, nbp, wn);
+    // the group after this one: its first element (-1: none) and codes
+    int vb = blockIdx.x, en = -1, cnm = -1, cnp = -1;
+    auto next_group = [&]() {
+        vb += gridDim.x;
+        const int tile = W::tile(vb);
+        return tile < tiles ? load_const(L.blk_map, tile) + W::part(vb) : -1;
+    };
+    if constexpr (PIPE) {
+        en = next_group();
+        if (en >= 0) load_codes(threadIdx.x, en, cnm, cnp);
     }
-    T iJn = T(0);
-    if (act) {
-        if constexpr (FULL) {
-            T u6[6], w[5];
+    for (;;) {
+        // (an opaque thread index: what follows from it is formed again for each
+        // group instead of being kept in registers across them)
+        int t = threadIdx.x;
+        if constexpr (PIPE) asm volatile("" : "+v"(t));
+        const NodeTask<G> nt(t);
+        const int le = nt.le, nd = nt.nd, tq = nt.q;
+        const int ltask = line_of_thread<G>(t);
+        const LineTask<P> lt(ltask < 0 ? 0 : ltask);
+        const int e = e0 + le, el = e0 + lt.le;
+        const bool act = nt.in && e < E, lact = ltask >= 0 && el < E;
+        const size_t g = (size_t)e0 * G::n3 + tq;
+        const uint32_t g32 = (uint32_t)g;
+        T iJn = T(0);
+        if (act) {
+            if constexpr (FULL) {
+                T u6[6], w[5];
 #pragma unroll
-            for (int v = 0; v < 6; ++v) { u6[v] = gld(a.U + (v) * a.NN, g32); sU[v][tq] = u6[v]; }
-            primitives(u6, w);
+                for (int v = 0; v < 6; ++v) { u6[v] = gld(a.U + (v) * a.NN, g32); sU[v][tq] = u6[v]; }
+                primitives(u6, w);
 #pragma unroll
-            for (int k = 0; k < 5; ++k) sW[k][tq] = w[k];
-        } else {
-            sU[kC][tq] = gld(a.U + 5 * a.NN, g32);
-        }
-        if constexpr (CV) iJn = stage_node_metrics<T, NJV>(a.mesh, a.NN, g, tq, sJ, sJz);
-    }
-    __syncthreads();
-    // BR1 face values w* on both faces of the line
-    if (lact) {
-        const int base = lt.le * G::n3;
-        T uf[2][6];
-        if constexpr (FULL) {
-#pragma unroll
-            for (int v = 0; v < 6; ++v) prolong2<P, T>(sU[v], base, B, lt, uf[0][v], uf[1][v]);
-        } else {
-            prolong2<P, T>(sU[kC], base, B, lt, uf[0][5], uf[1][5]);
-        }
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int f = 2 * lt.d + s;
-            const int nb = s ? nbp : nbm;
-            const int slot = lt.le * 6 * G::n2 + f * G::n2 + lt.fp;
-            if constexpr (CV) {
-                T n[3], dS;
-                face_normal<P, T, true>(a.mesh, (size_t)el * 6 + f, lt.fp, n, dS);
-#pragma unroll
-                for (int m = 0; m < 3; ++m) sN[m][slot] = n[m] * dS;
-            }
-            if (full) {
-                T w[5];
-                primitives(uf[s], w);
-                if (nb >= 0) {
-                    T v5[5];
-                    primitives(wn[s], v5);
-#pragma unroll
-                    for (int k = 0; k < 5; ++k) w[k] = T(0.5) * (w[k] + v5[k]);
-                } else {
-                    T n[3], dS;
-                    face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + f, lt.fp, n, dS);
-                    wall_primitives(a.mesh, el, f, n, w);
-                }
-#pragma unroll
-                for (int k = 0; k < NS; ++k) sS[k][slot] = w[k];
+                for (int k = 0; k < 5; ++k) sW[k][tq] = w[k];
             } else {
-                sS[NS - 1][slot] = nb >= 0 ? T(0.5) * (uf[s][5] + wn[s][5]) : uf[s][5];
+                sU[kC][tq] = c0;
+            }
+            if constexpr (CV) iJn = stage_node_metrics<T, NJV>(a.mesh, a.NN, g, tq, sJ, sJz);
+        }
+        T w1[2][6];
+        T c1 = T(0);
+        int e2 = -1, c2m = -1, c2p = -1;
+        if constexpr (PIPE) {
+            if (en >= 0) {
+                load_traces(t, cnm, cnp, w1);
+                c1 = load_c(t, en);
+                e2 = next_group();
+                if (e2 >= 0) load_codes(t, e2, c2m, c2p);
             }
         }
-    }
-    __syncthreads();
-    T qc[3] = {T(0), T(0), T(0)};
-    if (act) {
-        const int i = nd % P, j = (nd / P) % P, k = nd / (P * P);
-        const int base = le * G::n3, fbase = le * 6 * G::n2;
-        if constexpr (CV) {
-            constexpr int NG = FULL ? 5 : 1;
-            auto node = [&](int n, T v[NG]) {
-#pragma unroll
-                for (int f = 0; f < NG; ++f) v[f] = FULL ? sW[f][FULL ? n : 0] : sU[kC][n];
-            };
-            auto face = [&](int n, T v[NG]) {
-#pragma unroll
-                for (int f = 0; f < NG; ++f) v[f] = sS[f][n];
-            };
-            T q[NG][3];
-            lifted_grads_curved<P, NG, G::NV, G::NF>(node, face, sJ, sJz, sN, base, fbase, i, j, k, B, iJn, q);
+        __syncthreads();
+        // BR1 face values w* on both faces of the line
+        if (lact) {
+            const int base = lt.le * G::n3;
+            T uf[2][6];
             if constexpr (FULL) {
 #pragma unroll
-                for (int w = 0; w < 4; ++w)
-#pragma unroll
-                    for (int m = 0; m < 3; ++m) gst(a.Q + ((3 * w + m)) * a.NN, g32, T(q[w][m]));
+                for (int v = 0; v < 6; ++v) prolong2<P, T>(sU[v], base, B, lt, uf[0][v], uf[1][v]);
+            } else {
+                prolong2<P, T>(sU[kC], base, B, lt, uf[0][5], uf[1][5]);
             }
-#pragma unroll
-            for (int m = 0; m < 3; ++m) qc[m] = q[NG - 1][m];
-        } else {
-            T Ja[9], iJ;
-            element_metrics<G::kUni>(a.mesh, e, Ja, iJ);
-            if (full) {
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    T q[3];
-                    lifted_grad<P, T>(sW[w], sS[w], base, fbase, i, j, k, B, Ja, iJ, q);
-#pragma unroll
-                    for (int m = 0; m < 3; ++m) gst(a.Q + ((3 * w + m)) * a.NN, g32, T(q[m]));
-                }
-            }
-            lifted_grad<P, T>(sU[kC], sS[NS - 1], base, fbase, i, j, k, B, Ja, iJ, qc);
-        }
-        if constexpr (FULL) {
-#pragma unroll
-            for (int m = 0; m < 3; ++m) gst(a.Q + ((12 + m)) * a.NN, g32, T(qc[m]));
-            const double Tn = temperature<fast_fp64<T>()>(a.ph, (double)sU[0][tq], (double)sU[1][tq], (double)sU[2][tq], (double)sU[3][tq],
-                                          (double)sU[4][tq], (double)sU[5][tq], (double)qc[0], (double)qc[1],
-                                          (double)qc[2]);
-            gst(a.TH, g32, T(Tn));
-        }
-    }
-    if (act) {
-        sG[tq] = V2<T>{qc[0], qc[1]};
-        sGz[tq] = qc[2];
-    }
-    __syncthreads();
-    if (lact) {
-        const int base = lt.le * G::n3;
-        T qf[2][3];
-        prolong2<P, T>(sG, base, B, lt, qf[0], qf[1]);
-        prolong2<P, T>(sGz, base, B, lt, qf[0][2], qf[1][2]);
-        // outward normal of each face of this line: on affine elements the -
-        // face's is the exact negative of the + face's, as the mesh upload
-        // forms them
-        T nf[2][3];
-        if constexpr (CV) {
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
+                const int f = 2 * lt.d + s;
+                const int nb = s ? nbp : nbm;
+                const int slot = lt.le * 6 * G::n2 + f * G::n2 + lt.fp;
+                if constexpr (CV) {
+                    T n[3], dS;
+                    face_normal<P, T, true>(a.mesh, (size_t)el * 6 + f, lt.fp, n, dS);
+#pragma unroll
+                    for (int m = 0; m < 3; ++m) sN[m][slot] = n[m] * dS;
+                }
+                if (full) {
+                    T w[5];
+                    primitives(uf[s], w);
+                    if (nb >= 0) {
+                        T v5[5];
+                        primitives(wn[s], v5);
+#pragma unroll
+                        for (int k = 0; k < 5; ++k) w[k] = T(0.5) * (w[k] + v5[k]);
+                    } else {
+                        T n[3], dS;
+                        face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + f, lt.fp, n, dS);
+                        wall_primitives(a.mesh, el, f, n, w);
+                    }
+#pragma unroll
+                    for (int k = 0; k < NS; ++k) sS[k][slot] = w[k];
+                } else {
+                    sS[NS - 1][slot] = nb >= 0 ? T(0.5) * (uf[s][5] + wn[s][5]) : uf[s][5];
+                }
+            }
+        }
+        __syncthreads();
+        T qc[3] = {T(0), T(0), T(0)};
+        if (act) {
+            const int i = nd % P, j = (nd / P) % P, k = nd / (P * P);
+            const int base = le * G::n3, fbase = le * 6 * G::n2;
+            if constexpr (CV) {
+                constexpr int NG = FULL ? 5 : 1;
+                auto node = [&](int n, T v[NG]) {
+#pragma unroll
+                    for (int f = 0; f < NG; ++f) v[f] = FULL ? sW[f][FULL ? n : 0] : sU[kC][n];
+                };
+                auto face = [&](int n, T v[NG]) {
+#pragma unroll
+                    for (int f = 0; f < NG; ++f) v[f] = sS[f][n];
+                };
+                T q[NG][3];
+                lifted_grads_curved<P, NG, G::NV, G::NF>(node, face, sJ, sJz, sN, base, fbase, i, j, k, B, iJn, q);
+                if constexpr (FULL) {
+#pragma unroll
+                    for (int w = 0; w < 4; ++w)
+#pragma unroll
+                        for (int m = 0; m < 3; ++m) gst(a.Q + ((3 * w + m)) * a.NN, g32, T(q[w][m]));
+                }
+#pragma unroll
+                for (int m = 0; m < 3; ++m) qc[m] = q[NG - 1][m];
+            } else {
+                T Ja[9], iJ;
+                element_metrics<G::kUni>(a.mesh, e, Ja, iJ);
+                if (full) {
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        T q[3];
+                        lifted_grad<P, T>(sW[w], sS[w], base, fbase, i, j, k, B, Ja, iJ, q);
+#pragma unroll
+                        for (int m = 0; m < 3; ++m) gst(a.Q + ((3 * w + m)) * a.NN, g32, T(q[m]));
+                    }
+                }
+                lifted_grad<P, T, PIPE>(sU[kC], sS[NS - 1], base, fbase, i, j, k, B, Ja, iJ, qc);
+            }
+            if constexpr (FULL) {
+#pragma unroll
+                for (int m = 0; m < 3; ++m) gst(a.Q + ((12 + m)) * a.NN, g32, T(qc[m]));
+                const double Tn = temperature<fast_fp64<T>()>(a.ph, (double)sU[0][tq], (double)sU[1][tq], (double)sU[2][tq], (double)sU[3][tq],
+                                              (double)sU[4][tq], (double)sU[5][tq], (double)qc[0], (double)qc[1],
+                                              (double)qc[2]);
+                gst(a.TH, g32, T(Tn));
+            }
+        }
+        if (act) {
+            sG[tq] = V2<T>{qc[0], qc[1]};
+            sGz[tq] = qc[2];
+        }
+        __syncthreads();
+        if (lact) {
+            const int base = lt.le * G::n3;
+            T qf[2][3];
+            prolong2<P, T, PIPE>(sG, base, B, lt, qf[0], qf[1]);
+            prolong2<P, T>(sGz, base, B, lt, qf[0][2], qf[1][2]);
+            // outward normal of each face of this line: on affine elements the -
+            // face's is the exact negative of the + face's, as the mesh upload
+            // forms them
+            T nf[2][3];
+            if constexpr (CV) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    T dS;
+                    face_normal<P, T, true>(a.mesh, (size_t)el * 6 + 2 * lt.d + s, lt.fp, nf[s], dS);
+                }
+            } else {
                 T dS;
-                face_normal<P, T, true>(a.mesh, (size_t)el * 6 + 2 * lt.d + s, lt.fp, nf[s], dS);
+                face_normal<P, T, false>(a.mesh, (size_t)el * 6 + 2 * lt.d + 1, lt.fp, nf[1], dS);
+#pragma unroll
+                for (int m = 0; m < 3; ++m) nf[0][m] = -nf[1][m];
             }
-        } else {
-            T dS;
-            face_normal<P, T, false>(a.mesh, (size_t)el * 6 + 2 * lt.d + 1, lt.fp, nf[1], dS);
 #pragma unroll
-            for (int m = 0; m < 3; ++m) nf[0][m] = -nf[1][m];
-        }
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const FaceIx<G::n2> o((size_t)el * 6 + 2 * lt.d + s, lt.fp);
-            a.T2[o.at(kT2<T>(), 0)] = qf[s][0] * nf[s][0] + qf[s][1] * nf[s][1] + qf[s][2] * nf[s][2];
-            const double q0 = (double)qf[s][0], q1 = (double)qf[s][1], q2 = (double)qf[s][2];
-            const double g2 = q0 * q0 + q1 * q1 + q2 * q2;
-            const T gh = T(g2);
-            a.T2[o.at(kT2<T>(), 1)] = gh;
-            if constexpr (sizeof(T) == 4) a.T2[o.at(kT2<T>(), 2)] = T(g2 - (double)gh);
-        }
-        // wall faces also keep the vector grad c (Navier-slip traction), in
-        // a loop of its own: inside the one above the branch costs ~40 VGPRs
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-            if ((s ? nbp : nbm) < 0) {
+            for (int s = 0; s < 2; ++s) {
                 const FaceIx<G::n2> o((size_t)el * 6 + 2 * lt.d + s, lt.fp);
-                a.T2[o.at(kT2<T>(), kT2gc<T>())] = qf[s][0];
-                a.T2[o.at(kT2<T>(), kT2gc<T>() + 1)] = qf[s][1];
-                a.T2[o.at(kT2<T>(), kT2gc<T>() + 2)] = qf[s][2];
+                a.T2[o.at(kT2<T>(), 0)] = qf[s][0] * nf[s][0] + qf[s][1] * nf[s][1] + qf[s][2] * nf[s][2];
+                const double q0 = (double)qf[s][0], q1 = (double)qf[s][1], q2 = (double)qf[s][2];
+                const double g2 = q0 * q0 + q1 * q1 + q2 * q2;
+                const T gh = T(g2);
+                a.T2[o.at(kT2<T>(), 1)] = gh;
+                if constexpr (sizeof(T) == 4) a.T2[o.at(kT2<T>(), 2)] = T(g2 - (double)gh);
             }
+            // wall faces also keep the vector grad c (Navier-slip traction), in
+            // a loop of its own: inside the one above the branch costs ~40 VGPRs
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+                if ((s ? nbp : nbm) < 0) {
+                    const FaceIx<G::n2> o((size_t)el * 6 + 2 * lt.d + s, lt.fp);
+                    a.T2[o.at(kT2<T>(), kT2gc<T>())] = qf[s][0];
+                    a.T2[o.at(kT2<T>(), kT2gc<T>() + 1)] = qf[s][1];
+                    a.T2[o.at(kT2<T>(), kT2gc<T>() + 2)] = qf[s][2];
+                }
+        }
+        if (!PIPE || en < 0) return;
+        e0 = en;
+        en = e2;
+        nbm = cnm;
+        nbp = cnp;
+        cnm = c2m;
+        cnp = c2p;
+        c0 = c1;
+        wn[0][5] = w1[0][5];
+        wn[1][5] = w1[1][5];
     }
 }
 

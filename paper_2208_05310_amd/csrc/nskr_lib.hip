@@ -20,6 +20,7 @@
 #include "../../include/nskr.h"
 #include "nskr_kernels.hpp"
 
+
 using namespace nskr;
 
 // ------------------------------------------------------------------ context
@@ -826,6 +827,16 @@ template <int P, typename T, bool CV> struct Impl {
     {
         using W = Lift1Group<P>;
         const int n = tiles(c);
+        if constexpr (!CV) {
+            // workgroups the card holds at once (a multiple of the 8 XCDs, so that
+            // a workgroup's groups stay on its XCD); from four groups each on
+            // the pipelined instance runs
+            const int held = 256 * 4 * lift1_waves<P, T, false, false, true>() / (W::NT / 64) / 8 * 8;
+            if (!L.full && W::grid(n) >= 4 * held) {
+                stage_launch(c, 1, &k_lift1<P, T, false, false, false, true>, held, W::NT, s, L, n);
+                return;
+            }
+        }
         stage_launch(c, 1, L.full ? &k_lift1<P, T, false, true, CV> : &k_lift1<P, T, false, false, CV>, W::grid(n), W::NT,
                      s, L, n);
     }
