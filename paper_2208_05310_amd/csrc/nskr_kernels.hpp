@@ -1246,9 +1246,11 @@ __global__ __launch_bounds__(Lift1Group<P>::NT, (lift1_waves<P, T, FULL, CV, PIP
 // face points cost a workgroup the latency of a whole one.
 template <int P> using Lift2Group = Group<P, StageTile<P>::kLift2, true>;
 
-// FP64 instances on affine elements keep 4 waves per SIMD (128 registers)
-// where their LDS lets them.
-template <int P, typename T, bool CV> constexpr int lift2_waves() { return sizeof(T) == 8 && !CV && P > 3 ? 4 : 1; }
+// Registers: affine FP64 instances fit in the 128 of 4 waves per SIMD and affine
+// FP32 ones in the 80 of 6 (the walls' would take 96: 48 against 52 us on a
+// sliding 51x25x13 mesh at N = 3; at 7 waves the spills cost more, 55 us).
+// Curved ones take what they need.
+template <int P, typename T, bool CV> constexpr int lift2_waves() { return CV ? 1 : (sizeof(T) == 8 ? 4 : 6); }
 
 // WALL: the mesh (or a batch's) has wall faces; without them the wall pass and
 // its registers are left out.  DIAG: every element is a box along the axes, so
@@ -1793,7 +1795,14 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
         const Pro pro{B.Lf + (f & 1) * B.PS, ft.le * G::n3 + ft.off, ft.str};
         const FaceIx<G::n2> o((size_t)el * 6 + f, ft.fp);
         T K[6], n[3], dS;
-        face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp, n, dS);
+        // the prolongations before the traces are loaded, and before the normal
+        // where they do without it: in the other order the pass needs more
+        // registers than the kernel has, and spills
+        if constexpr (CV) face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp, n, dS);
+        T tn[3], dv, gTn, lapc;
+        viscous(pro, f, n, tn, dv, gTn, lapc);
+        bound(tn, 3);
+        if constexpr (!CV) face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp, n, dS);
         T u6[6], q[3];
 #pragma unroll
         for (int v = 0; v < 6; ++v) u6[v] = TU[o.at(6, v)];
@@ -1805,8 +1814,6 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
         const T rho = u6[0], c = u6[5], ir = T(1) / rho;
         const T u0 = u6[1] * ir, u1 = u6[2] * ir, u2 = u6[3] * ir;
         const T mn = u6[1] * n[0] + u6[2] * n[1] + u6[3] * n[2], vn = mn * ir, lam = fabs(vn) + cw;
-        T tn[3], dv, gTn, lapc;
-        viscous(pro, f, n, tn, dv, gTn, lapc);
         const T w0 = T(bc.uw[0]), w1 = T(bc.uw[1]), w2 = T(bc.uw[2]);
         K[0] = K[4] = K[5] = T(0);
         if (kind == 1) {
