@@ -94,7 +94,15 @@ struct Phys {
     double inv_Rcv;   // 1 / (R c_v)
     double cs_fac;    // (1 + 1/c_v) R
     double ap;        // alpha for relaxation model 2 (p_alpha = p + ap/2 rho^2), 0 for model 1
+    double alpha_2, gam_2, ap_2, a2;  // alpha/2, gamma/2, ap/2, 2 a
     int model;        // 1 or 2
+};
+
+// The constants that the fluxes and the source use, in the element type: a
+// conversion or product of wave-uniform values is a vector instruction in every
+// wave that does it.
+template <typename T> struct PhysT {
+    T mu, kappa, gam, alpha, beta, gb;  // gb = gamma beta
 };
 
 struct BcDev {
@@ -294,6 +302,10 @@ template <bool FAST> __device__ __forceinline__ double recip(double x)
     return 1.0 / x;
 }
 
+// 1/x in the element type: of FP32 instances the refined reciprocal, rounded,
+// which the temperature and the equation of state form anyway.
+template <typename T> __device__ __forceinline__ T recip_to(T x) { return T(recip<sizeof(T) == 4>((double)x)); }
+
 // Temperature recovery of eq. totalenergyalpha with eps = R c_v T - a rho
 // (always FP64 arithmetic: it cancels large terms near the spinodal).
 template <bool FAST = false>
@@ -302,8 +314,8 @@ __device__ __forceinline__ double temperature_g2(const Phys &ph, double rho, dou
 {
     const double ir = recip<FAST>(rho);
     double kin = 0.5 * (m0 * m0 + m1 * m1 + m2 * m2) * ir;
-    double rel = 0.5 * ph.alpha * (rho - c) * (rho - c);
-    double grd = 0.5 * ph.gam * g2;
+    double rel = ph.alpha_2 * (rho - c) * (rho - c);
+    double grd = ph.gam_2 * g2;
     return ((E - kin - rel - grd) * ir + ph.a * rho) * ph.inv_Rcv;
 }
 template <bool FAST = false>
@@ -320,7 +332,7 @@ __device__ __forceinline__ void eos(const Phys &ph, double rho, double T, double
 {
     double q = recip<FAST>(1.0 - ph.b * rho);
     p = rho * ph.R * T * q - ph.a * rho * rho;
-    cs2 = ph.cs_fac * T * q * q - 2.0 * ph.a * rho;
+    cs2 = ph.cs_fac * T * q * q - ph.a2 * rho;
 }
 
 // The FP32-mixed instances take the refined reciprocals above.
@@ -379,12 +391,11 @@ __device__ __forceinline__ void hllc(const T uL[6], T pL, T aL, const T uR[6], T
 // Relaxation model 2 (eq. navierstokeskorteweg_palpha) drops the alpha rho
 // grad rho and alpha/2 rho^2 div u parts, which its pressure p_alpha carries.
 template <typename T>
-__device__ __forceinline__ void source(const Phys &ph, T rho, T c, const T u[3], const T grho[3], const T gu[3][3],
+__device__ __forceinline__ void source(const PhysT<T> &pt, bool m2, T rho, T c, const T u[3], const T grho[3], const T gu[3][3],
                                        const T gc[3], T S[6])
 {
     const T div = gu[0][0] + gu[1][1] + gu[2][2];
-    const T al = T(ph.alpha);
-    const bool m2 = ph.model == 2;
+    const T al = pt.alpha;
     T d[3], gg = T(0), cc = T(0), du = T(0);
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
@@ -404,8 +415,8 @@ __device__ __forceinline__ void source(const Phys &ph, T rho, T c, const T u[3],
     S[2] = al * rho * d[1];
     S[3] = al * rho * d[2];
     S[4] = al * rho * du + T(0.5) * al * (m2 ? c * c : c * c - rho * rho) * div +
-           T(ph.gam) * (T(0.5) * gg * div - cc);
-    S[5] = al * T(ph.beta) * (rho - c);
+           pt.gam * (T(0.5) * gg * div - cc);
+    S[5] = al * pt.beta * (rho - c);
 }
 
 // ------------------------------------------------------------ kernel args
@@ -422,6 +433,7 @@ template <typename T> struct Inst {
                                // (a buffer) face-major: [face][field][point]
     MeshDev mesh;
     Phys ph;
+    PhysT<T> pt;
     size_t NN;                 // nodes of the instance
     double dt;
     const int *clk;            // batch: steps taken since admission, for walls whose
@@ -661,10 +673,11 @@ template <typename G> __device__ __forceinline__ int line_of_thread(int t)
 }
 
 // ------------------------------------------------------------ shared pieces
-// Primitive variables (rho, u, v, w, c) of a conserved state.
-template <typename T> __device__ __forceinline__ void primitives(const T u6[6], T w[5])
+// Primitive variables (rho, u, v, w, c) of a conserved state.  SHARED: with the
+// reciprocal that the temperature of the same state forms.
+template <typename T, bool SHARED = false> __device__ __forceinline__ void primitives(const T u6[6], T w[5])
 {
-    const T ir = T(1) / u6[0];
+    const T ir = SHARED ? recip_to(u6[0]) : T(1) / u6[0];
     w[0] = u6[0];
     w[1] = u6[1] * ir;
     w[2] = u6[2] * ir;
@@ -891,7 +904,7 @@ __device__ __forceinline__ void to_physical(const T Ja[9], T iJ, const T gd[3], 
 {
     if constexpr (DIAG) {  // Ja^d along axis d
 #pragma unroll
-        for (int m = 0; m < 3; ++m) q[m] = iJ * (Ja[4 * m] * gd[m]);
+        for (int m = 0; m < 3; ++m) q[m] = (iJ * Ja[4 * m]) * gd[m];  // one uniform factor for every field
         return;
     }
 #pragma unroll
@@ -1357,7 +1370,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
     auto face_eos = [&](T rho, double Tf, T &p, T &cw) {
         double pd, cs2;
         eos<fast_fp64<T>()>(a.ph, (double)rho, Tf, pd, cs2);
-        p = T(pd + 0.5 * a.ph.ap * (double)rho * (double)rho);
+        p = T(pd + a.ph.ap_2 * (double)rho * (double)rho);
         cw = sqrt_to<T>(fabs(cs2 + a.ph.ap * (double)rho));
     };
     Tr tr;
@@ -1370,7 +1383,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
         T w[5];
 #pragma unroll
         for (int v = 0; v < 6; ++v) un[v] = gld(a.U + (v) * a.NN, g32);
-        primitives(un, w);
+        primitives<T, true>(un, w);
         sM[tq] = V2<T>{un[1], un[2]};
         sM[G::NV + tq] = V2<T>{un[3], un[4]};
         sR[0][tq] = V2<T>{w[0], w[1]};
@@ -1403,12 +1416,12 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
         const int slot = ft.le * 6 * G::n2 + f * G::n2 + ft.fp;
         const T *uf = tr.uo;
         T w[5];
-        primitives(uf, w);
+        primitives<T, true>(uf, w);
         const double To = face_T(uf, tr.own);
         T Ts, Fs;
         if (!WALL || tr.nb >= 0) {
             T v5[5];
-            primitives(tr.wn, v5);
+            primitives<T, true>(tr.wn, v5);
             T po, co, pn, cn;
             face_eos(uf[0], To, po, co);
             __builtin_amdgcn_sched_barrier(0);  // one side after the other: registers
@@ -1421,8 +1434,8 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
             } else {
                 const T mn = uf[1] * n[0] + uf[2] * n[1] + uf[3] * n[2];
                 const T mo = tr.wn[1] * n[0] + tr.wn[2] * n[1] + tr.wn[3] * n[2];
-                const T ir = T(1) / uf[0], vn = mn * ir;
-                const T lo = fabs(vn) + co, ln = fabs(mo * (T(1) / tr.wn[0])) + cn;
+                const T vn = mn * recip_to(uf[0]);
+                const T lo = fabs(vn) + co, ln = fabs(mo * recip_to(tr.wn[0])) + cn;
                 const T hl = T(0.5) * (lo > ln ? lo : ln);
                 K[0] = mn + hl * (uf[0] - tr.wn[0]);
                 K[1] = uf[1] * vn + po * n[0] + hl * (uf[1] - tr.wn[1]);
@@ -1502,7 +1515,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
     const int i = nd % P, j = (nd / P) % P, k = nd / (P * P);
     const int base = le * G::n3, fbase = le * 6 * G::n2;
     T gc[3] = {T(0), T(0), T(0)}, S[6];
-    T iJ = T(0), div = T(0), p = T(0);
+    T iJ = T(0), div = T(0), p = T(0), irn = T(0);
     double Tn = 0.0;
     T gu[3][3];
     if (act) {
@@ -1543,10 +1556,10 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
         div = gu[0][0] + gu[1][1] + gu[2][2];
         double pd, cs2;
         eos<fast_fp64<T>()>(a.ph, (double)un[0], Tn, pd, cs2);
-        p = T(pd + 0.5 * a.ph.ap * (double)un[0] * (double)un[0]);  // p_alpha for model 2
-        const T ir = T(1) / un[0];
-        const T u[3] = {un[1] * ir, un[2] * ir, un[3] * ir};
-        source(a.ph, un[0], un[5], u, grho, gu, gc, S);
+        p = T(pd + a.ph.ap_2 * (double)un[0] * (double)un[0]);  // p_alpha for model 2
+        irn = recip_to(un[0]);
+        const T u[3] = {un[1] * irn, un[2] * irn, un[3] * irn};
+        source(a.pt, a.ph.model == 2, un[0], un[5], u, grho, gu, gc, S);
     }
     __syncthreads();
     if (act) {
@@ -1566,7 +1579,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
             // values (n_d is constant on the face), so a face task prolongs
             // 6 fields instead of 13
             // (gc: the contravariant components from here on)
-            const T mu = T(a.ph.mu), td = T(2.0 / 3.0) * div, g0 = gc[0], g1 = gc[1], g2 = gc[2];
+            const T mu = a.pt.mu, td = T(2.0 / 3.0) * div, g0 = gc[0], g1 = gc[1], g2 = gc[2];
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
                 const int jr = kEmJa + 3 * d, fr = (2 * d + 1) * 4;
@@ -1657,10 +1670,11 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
         }
     }
     if (L.mode == 2) return;
-    // j_e = k grad T + (gamma zeta - gamma c div u) grad c
-    const T zc = T(a.ph.gam) * (T(a.ph.beta) * (T(a.ph.gam) * lap + T(a.ph.alpha) * (un[0] - un[5])) - un[5] * div);
+    T zc;
     __syncthreads();
     if (act) {
+        // j_e = k grad T + (gamma zeta - gamma c div u) grad c
+        zc = a.pt.gam * (a.pt.beta * (a.pt.gam * lap + a.pt.alpha * (un[0] - un[5])) - un[5] * div);
         if constexpr (CV) {
             sR[kT][tq] = V2<T>{gT[0], gT[1]};
             sR[kT + 1][tq] = V2<T>{gT[2], lap};
@@ -1714,7 +1728,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
                 gf[2 * r + 1] = v.y;
             }
             dv = gf[0] + gf[4] + gf[8];
-            const T td = T(2.0 / 3.0) * dv, mu = T(a.ph.mu);
+            const T td = T(2.0 / 3.0) * dv, mu = a.pt.mu;
             tn[0] = mu * ((gf[0] + gf[0]) * n[0] + (gf[1] + gf[3]) * n[1] + (gf[2] + gf[6]) * n[2] - td * n[0]);
             tn[1] = mu * ((gf[3] + gf[1]) * n[0] + (gf[4] + gf[4]) * n[1] + (gf[5] + gf[7]) * n[2] - td * n[1]);
             tn[2] = mu * ((gf[6] + gf[2]) * n[0] + (gf[7] + gf[5]) * n[1] + (gf[8] + gf[8]) * n[2] - td * n[2]);
@@ -1775,11 +1789,11 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
         K[2] -= tn[1];
         K[3] -= tn[2];
         K[4] -= tn[0] * u0 + tn[1] * u1 + tn[2] * u2;
-        K[4] -= T(a.ph.kappa) * gTn;
+        K[4] -= a.pt.kappa * gTn;
         // order-parameter terms of j_e and F^V_c
-        const T zeta = T(a.ph.beta) * (T(a.ph.gam) * lapc + T(a.ph.alpha) * rc);
-        K[4] -= -T(a.ph.gam) * c * gcn * dv + T(a.ph.gam) * gcn * zeta;
-        K[5] -= T(a.ph.gam * a.ph.beta) * gcn;
+        const T zeta = a.pt.beta * (a.pt.gam * lapc + a.pt.alpha * rc);
+        K[4] -= -a.pt.gam * c * gcn * dv + a.pt.gam * gcn * zeta;
+        K[5] -= a.pt.gb * gcn;
         dS *= T(0.5);
 #pragma unroll
         for (int v = 0; v < 6; ++v) a.TF[o.at(6, v)] = K[v] * dS;
@@ -1852,7 +1866,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
         }
         if (kind != 2) {
             if (bc.iso) {
-                K[4] -= T(a.ph.kappa) * gTn;
+                K[4] -= a.pt.kappa * gTn;
             } else {  // heat transfer, eq. bc_energy_alpha
                 const double itw = bc.var ? (double)a.TF[o.at(6, 0)] : bc.inv_tw;
                 K[4] -= T(-bc.g3 * (itw - 1.0 / Tf));
@@ -1862,8 +1876,8 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
             // the wall value zeta_c = -gamma_1 gamma_4 div u
             const T gw = sTF[ft.le * 6 * G::n2 + f * G::n2 + ft.fp].y / dS;
             const T zeta = -T(bc.g1 * bc.g4) * dv;
-            K[4] -= -T(a.ph.gam) * c * gw * dv + T(a.ph.gam) * gw * zeta;
-            K[5] -= T(a.ph.gam * a.ph.beta) * gw;
+            K[4] -= -a.pt.gam * c * gw * dv + a.pt.gam * gw * zeta;
+            K[5] -= a.pt.gb * gw;
         }
 #pragma unroll
         for (int v = 0; v < 6; ++v) a.TF[o.at(6, v)] = K[v] * dS;
@@ -1879,7 +1893,6 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
     // direction d+1 are written while direction d is read, one barrier per
     // direction
     T acc[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
-    const T irn = T(1) / un[0];
     // row q of the fluxes of direction 1 (odd) or 0 and 2
     auto frow = [&](bool odd, int q) { return odd ? (CV ? 8 + q : (q == 0 ? 0 : (q == 1 ? 3 : 1))) : kT + q; };
     auto put_flux = [&](int d) {
@@ -1899,7 +1912,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
                 gg[2 * r] = v.x;
                 gg[2 * r + 1] = v.y;
             }
-            const T mu = T(a.ph.mu), td = T(2.0 / 3.0) * div;
+            const T mu = a.pt.mu, td = T(2.0 / 3.0) * div;
 #pragma unroll
             for (int m = 0; m < 3; ++m)
                 tj[m] = mu * ((gg[3 * m] + gg[m]) * J[0] + (gg[3 * m + 1] + gg[3 + m]) * J[1] +
@@ -1930,8 +1943,8 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
         for (int m = 0; m < 3; ++m) mf[m] = (DIAG && m != d ? un[1 + m] * uJ : un[1 + m] * uJ + p * J[m]) - tj[m];
         sR[frow(d & 1, 0)][tq] = V2<T>{mJ, mf[0]};
         sR[frow(d & 1, 1)][tq] = V2<T>{mf[1], mf[2]};
-        sR[frow(d & 1, 2)][tq] = V2<T>{(un[4] + p) * uJ - tw - (T(a.ph.kappa) * qj + zc * gj),
-                                       un[5] * uJ - T(a.ph.gam * a.ph.beta) * gj};
+        sR[frow(d & 1, 2)][tq] = V2<T>{(un[4] + p) * uJ - tw - (a.pt.kappa * qj + zc * gj),
+                                       un[5] * uJ - a.pt.gb * gj};
     };
     __syncthreads();
     if (act) put_flux(0);

@@ -795,6 +795,7 @@ template <int P, typename T, bool CV> struct Impl {
         I.Q = (T *)c->d_Q; I.TH = (T *)c->d_TH; I.G2 = (T *)c->d_G2;
         I.T2 = (T *)c->d_T2; I.TF = (T *)c->d_TF; I.TU = (T *)c->d_TU;
         I.mesh = mesh(c); I.ph = c->ph; I.NN = c->NN; I.dt = dt;
+        I.pt = PhysT<T>{T(I.ph.mu), T(I.ph.kappa), T(I.ph.gam), T(I.ph.alpha), T(I.ph.beta), T(I.ph.gam * I.ph.beta)};
         I.clk = nullptr; I.t0 = 0.0;
         return I;
     }
@@ -1331,6 +1332,10 @@ int nskr_create(const nskr_params *p, int N, int device, nskr_ctx **out)
     c->ph.cs_fac = (1.0 + 1.0 / p->cv) * p->R;
     c->ph.model = p->model == 2 ? 2 : 1;
     c->ph.ap = p->model == 2 ? p->alpha : 0.0;
+    c->ph.alpha_2 = 0.5 * p->alpha;
+    c->ph.gam_2 = 0.5 * c->ph.gam;
+    c->ph.ap_2 = 0.5 * c->ph.ap;
+    c->ph.a2 = 2.0 * p->a;
     *out = c;
     return NSKR_OK;
 }
