@@ -899,16 +899,20 @@ __device__ __forceinline__ T stage_node_metrics(const MeshDev &m, size_t NN, siz
     return T(1) / gld(nm + 9 * NN, (uint32_t)g);
 }
 
+// Gradient from its contravariant components, Ja^d / J of the element times the
+// reference derivatives: the factors are the same for every field, and on a box
+// along the axes (DIAG) bitwise those of the general form, whose other products
+// are zero there.
 template <bool DIAG, typename T>
 __device__ __forceinline__ void to_physical(const T Ja[9], T iJ, const T gd[3], T q[3])
 {
     if constexpr (DIAG) {  // Ja^d along axis d
 #pragma unroll
-        for (int m = 0; m < 3; ++m) q[m] = (iJ * Ja[4 * m]) * gd[m];  // one uniform factor for every field
+        for (int m = 0; m < 3; ++m) q[m] = (iJ * Ja[4 * m]) * gd[m];
         return;
     }
 #pragma unroll
-    for (int m = 0; m < 3; ++m) q[m] = iJ * (Ja[m] * gd[0] + Ja[3 + m] * gd[1] + Ja[6 + m] * gd[2]);
+    for (int m = 0; m < 3; ++m) q[m] = (iJ * Ja[m]) * gd[0] + (iJ * Ja[3 + m]) * gd[1] + (iJ * Ja[6 + m]) * gd[2];
 }
 
 template <bool UNI, typename T> __device__ __forceinline__ void element_metrics(const MeshDev &m, int e, T Ja[9], T &iJ)
