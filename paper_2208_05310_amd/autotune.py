@@ -1,11 +1,11 @@
-"""Tile-shape autotuner: picks the stage kernels' workgroup size per (degree,
-precision), i.e. how many elements share a workgroup and how tightly they fill
-its waves, among the sizes the library builds for that degree (256, 512 and a
-tight size: N = 2 192, N = 3 and 4 128, N = 5 448).  Each candidate runs a few
-RK steps of a droplet workload at the mesh sizes the request stream draws,
-from the same initial state; the fastest total wins.  The tuner also records
-whether every candidate ended in bitwise the same state (an element's
-arithmetic does not depend on its tile).  The table can be kept in a JSON
+"""Tile-shape autotuner: times the nominal workgroup sizes that the library
+accepts for a (degree, precision) (256, 512 and a tight size: N = 2 192, N = 3
+and 4 128, N = 5 448).  The stage kernels have workgroup sizes of their own, so
+the sizes do not differ in speed any more and the choice is free; the table and
+the calls stay for programs that keep them.  Each candidate runs a few RK steps
+of a droplet workload at the mesh sizes the request stream draws, from the same
+initial state; the fastest total wins.  The tuner also records whether every
+candidate ended in bitwise the same state.  The table can be kept in a JSON
 file."""
 from __future__ import annotations
 
@@ -22,7 +22,7 @@ DEFAULT_SIZES = ((8, 8, 8), (16, 16, 16))
 
 
 def block_sizes(N):
-    """Workgroup sizes the library builds for degree N."""
+    """Nominal workgroup sizes of degree N."""
     tight = {2: 192, 3: 128, 4: 128, 5: 448}[N]
     return tuple(sorted({256, 512, tight}))
 

@@ -4,10 +4,10 @@
 // 3).
 //
 // Execution model
-//   One workgroup of 256 (or 512) threads owns EPB = threads / (N+1)^3
-//   elements; each thread owns one volume node.  Element tiles are staged in
-//   LDS for the 1D derivative sweeps along xi, eta, zeta; face work runs as
-//   line tasks (one thread per grid line normal to a face pair).  State is
+//   One workgroup owns a few elements (StageTile: each kernel of a stage has
+//   its own number), one thread a volume node.  Element tiles are staged in
+//   LDS for the 1D derivative sweeps along xi, eta, zeta; face work runs one
+//   face point, or one grid line normal to a face pair, per thread.  State is
 //   structure-of-arrays [var][element][node]; face traces are face-major
 //   [element][face][var][point] so that each element writes its own six faces
 //   contiguously and reads all fields of a neighbour's face as one contiguous
@@ -30,9 +30,9 @@
 // Everything that needs the gradients is done in the one kernel that lifts
 // them.  Where the update kernel lifted them again for the volume integral,
 // the three kernels took 132, 412 and 570 us on 32^3 elements of N = 5 in
-// FP64 (71, 232 and 317 us on 48x48x24 of N = 3); this split takes 105, 475
-// and 402 us (55, 291 and 212), moves 11 % fewer bytes and evaluates half as
-// many sweeps.
+// FP64 (71, 232 and 317 us on 48x48x24 of N = 3); this split takes 97, 460
+// and 363 us (49, 281 and 212) with the workgroups below, moves 11 % fewer
+// bytes and evaluates half as many sweeps.
 // The conserved traces rotate over three buffers: stage s reads buffer b(s)
 // and writes b(s+1), b = 0 1 0 1 2 (0), so no kernel overwrites traces that
 // a neighbouring workgroup may still read.
@@ -863,17 +863,19 @@ __device__ __forceinline__ void lifted_grads_curved(FN node, FS face, const V2<T
             }
         }
         const V2<T> lh = B.Lh[idx[d]];
+        // the two faces' terms enter as one correction: they all but cancel, and
+        // added one after the other their round-off moves an FP32 U_t by 1.5e-5
+        // (2-norm, 6x6x5 elements of N = 5; 58.1 against 57.0 us in FP64 on 16^3
+        // elements of N = 4)
+        const int pp = fbase + (2 * d + 1) * n2 + fpd[d], pm = fbase + (2 * d) * n2 + fpd[d];
+        T vm[NFLD];
+        face(pp, v);
+        face(pm, vm);
 #pragma unroll
-        for (int sd = 0; sd < 2; ++sd) {
-            const int pt = fbase + (2 * d + 1 - sd) * n2 + fpd[d];
-            const T lw = sd ? lh.x : lh.y;
-            face(pt, v);
+        for (int m = 0; m < 3; ++m) {
+            const T np = lh.y * sN[m][pp], nm = lh.x * sN[m][pm];
 #pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                const T nl = lw * sN[m][pt];
-#pragma unroll
-                for (int f = 0; f < NFLD; ++f) q[f][m] += nl * v[f];
-            }
+            for (int f = 0; f < NFLD; ++f) q[f][m] += np * v[f] + nm * vm[f];
         }
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -1258,9 +1260,14 @@ __global__ __launch_bounds__(Lift1Group<P>::NT, (lift1_waves<P, T, FULL, CV, PIP
 // Tile of k_lift2: its own, since its workgroups are bound by the registers
 // and the LDS of the node phases and by the rounds of the face phases, not by
 // what the streaming kernels of the stage like.  One element per workgroup at
-// N = 4 and 5, two at N = 3, three at N = 2 and as many threads as the face points need, in whole
-// waves, so that the face phases take one round: the second round of a few
-// face points cost a workgroup the latency of a whole one.
+// N = 4 and 5, two at N = 3, three at N = 2 and as many threads as the face
+// points need, in whole waves, so that the face phases take one round: the
+// second round of a few face points cost a workgroup the latency of a whole one
+// (N = 3 on 48x48x24: 387 us with two rounds, 291 with one; with one element
+// 325, with four 378; N = 5 on 32^3 with two elements 604 against 460).
+// FP64 instances are bound by memory latency at 4 waves per SIMD, LDS and
+// vector unit each busy for 60 % of the time (32^3 N = 5: 460 us, 3.8 TB/s of
+// algorithmic bytes); FP32 ones by instruction issue, 88 % busy (271 us).
 template <int P> using Lift2Group = Group<P, StageTile<P>::kLift2, true>;
 
 // Registers: affine FP64 instances fit in the 128 of 4 waves per SIMD and affine
@@ -1990,6 +1997,12 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
 }
 
 // ------------------------------------------------------------ k_update
+// Bound by memory: 32^3 N = 5 in FP64 363 us, 5.4 TB/s of algorithmic bytes, where
+// a large copy takes 5.07; with the gradients lifted again and the volume
+// integral in this kernel it took 570 us.  The flux traces come as differences
+// to take, so no normals, states or wave speeds are read, and the register
+// already holds the volume part.  A thread per face point where the faces
+// outnumber the nodes (N = 3, two elements: 513 -> 505 us on 50^3).
 template <int P> using UpdateGroup = Group<P, StageTile<P>::kUpdate, P == 4>;
 
 template <int P, typename T, bool BATCH, bool CV = false, bool NT = false>
