@@ -188,7 +188,8 @@ template <int P> struct StageTile {
     static constexpr int kLift2 = P >= 5 ? 1 : (P == 4 ? 2 : 3);
     static constexpr int kUpdate = P == 3 ? 9 : (P == 4 ? 2 : 4);
     static constexpr int kTile = P == 3 ? 9 : (P == 4 ? 2 : 4);
-    static_assert(kTile % kLift1 == 0 && kTile % kLift2 == 0 && kTile % kUpdate == 0, "tile");
+    static constexpr int kFew = P >= 5 ? 1 : kUpdate;  // k_update on meshes of few tiles
+    static_assert(kTile % kFew == 0 && kTile % kLift1 == 0 && kTile % kLift2 == 0 && kTile % kUpdate == 0, "tile");
 };
 // Workgroup of EPB elements in whole waves, with a thread for every node and
 // (FACES) for every face point.
@@ -2003,12 +2004,13 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
 // to take, so no normals, states or wave speeds are read, and the register
 // already holds the volume part.  A thread per face point where the faces
 // outnumber the nodes (N = 3, two elements: 513 -> 505 us on 50^3).
-template <int P> using UpdateGroup = Group<P, StageTile<P>::kUpdate, P == 4>;
+template <int P, bool FEW> using UpdateGroup = Group<P, FEW ? StageTile<P>::kFew : StageTile<P>::kUpdate, P == 4 || FEW>;
 
-template <int P, typename T, bool BATCH, bool CV = false, bool NT = false>
-__global__ __launch_bounds__(UpdateGroup<P>::NT) void k_update(Launch<T> L, int tiles)
+
+template <int P, typename T, bool BATCH, bool CV = false, bool NT = false, bool FEW = false>
+__global__ __launch_bounds__((UpdateGroup<P, FEW>::NT)) void k_update(Launch<T> L, int tiles)
 {
-    using W = UpdateGroup<P>;
+    using W = UpdateGroup<P, FEW>;
     using G = typename W::G;
     constexpr int BS = W::NT;
     Inst<T> a;

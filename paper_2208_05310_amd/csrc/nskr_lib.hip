@@ -809,6 +809,14 @@ template <int P, typename T, bool CV> struct Impl {
         L.blk_map = c->d_bmap;
         return L;
     }
+    // Up to this many tiles (three for each CU) the update of N = 4 and 5 runs one
+    // element per workgroup instead of a tile of four: a tile each leaves CUs idle.
+    // Tile / element, us of k_update in FP64: N = 5 3^3 7.7 / 5.3, 8^3 8.9 / 7.0,
+    // 13^3 (550 tiles) 27.3 / 22.2, 32^3 363 / 402; N = 4 3^3 6.9 / 5.1, 8^3 7.8 /
+    // 6.3, 13^3 15.9 / 14.5 (FP32 11.0 / 9.8), 16^3 (1024) 25.6 / 25.6 (FP32 16.3 /
+    // 19.2).  At N = 2 and 3 smaller groups gain nothing (N = 3 with one element 8^3
+    // 4.8 / 5.8, N = 2 with three 10^3 6.1 / 6.6).
+    static constexpr int kFewTiles = 768;
     // the second lifting's instance for a mesh with or without walls, of
     // boxes along the axes or not
     template <bool BATCH> static auto lift2_kernel(bool wall, bool diag)
@@ -849,8 +857,14 @@ template <int P, typename T, bool CV> struct Impl {
     }
     static void update(nskr_ctx *c, const Launch<T> &L, hipStream_t s)
     {
-        using W = UpdateGroup<P>;
+        using W = UpdateGroup<P, false>;
+        using F = UpdateGroup<P, true>;
         const int n = tiles(c);
+        if constexpr (P >= 5)
+            if (n <= kFewTiles) {
+                stage_launch(c, 3, &k_update<P, T, false, CV, false, true>, F::grid(n), F::NT, s, L, n);
+                return;
+            }
         stage_launch(c, 3, c->stream_nodes ? &k_update<P, T, false, CV, true> : &k_update<P, T, false, CV, false>,
                      W::grid(n), W::NT, s, L, n);
     }
@@ -861,7 +875,8 @@ template <int P, typename T, bool CV> struct Impl {
     {
         using W1 = Lift1Group<P>;
         using W2 = Lift2Group<P>;
-        using W3 = UpdateGroup<P>;
+        using W3 = UpdateGroup<P, false>;
+        using F3 = UpdateGroup<P, true>;
         const auto lift2 = lift2_kernel<true>(wall, diag);
         Launch<T> L = L0;
         for (int st = 0; st < 5; ++st) {
@@ -875,7 +890,9 @@ template <int P, typename T, bool CV> struct Impl {
             L.cs = kRkC[st];
             hipLaunchKernelGGL((k_lift1<P, T, true, false, CV>), dim3(W1::grid(n)), dim3(W1::NT), 0, s, L, n);
             hipLaunchKernelGGL(lift2, dim3(W2::grid(n)), dim3(W2::NT), 0, s, L, n);
-            hipLaunchKernelGGL((k_update<P, T, true, CV>), dim3(W3::grid(n)), dim3(W3::NT), 0, s, L, n);
+            if (P >= 5 && n <= kFewTiles)
+                hipLaunchKernelGGL((k_update<P, T, true, CV, false, P >= 5>), dim3(F3::grid(n)), dim3(F3::NT), 0, s, L, n);
+            else hipLaunchKernelGGL((k_update<P, T, true, CV>), dim3(W3::grid(n)), dim3(W3::NT), 0, s, L, n);
         }
     }
 

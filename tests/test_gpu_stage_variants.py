@@ -141,3 +141,21 @@ def test_reductions_over_many_tiles(torch_cuda, N, n, wall):  # noqa: F811
     for k in range(20):
         scale = max(abs(ro[0]), 1.0) if k in (1, 2, 3) else abs(ro[k])
         assert abs(rg[k] - ro[k]) <= 1e-12 * scale + 1e-300, (k, rg[k], ro[k])
+
+
+@pytest.mark.parametrize("N", (4, 5))
+@pytest.mark.parametrize("prec", ("fp64", "fp32_mixed"))
+@pytest.mark.parametrize("curve", (0.0, 0.02))
+def test_few_tiles_equal_many_bitwise(torch_cuda, N, prec, curve):  # noqa: F811
+    """A small mesh updates one element per workgroup alone, and a tile of four
+    in a batch whose group has more than 768 tiles (1024 + 7 + 16)."""
+    torch = torch_cuda
+    from paper_2208_05310_amd.nskr import init_workload
+    solvers = []
+    for n in ((3, 3, 3), (16, 16, 16), (8, 8, 1)):
+        w = wl.c1().with_(N=N, n=n, curve_amp=curve)
+        s = gpu_solver(w, prec)
+        solvers.append((s, init_workload(s, w)))
+    alone, held = alone_and_batched(torch, solvers, 2)
+    for a, h in zip(alone, held):
+        assert torch.equal(a, h)
