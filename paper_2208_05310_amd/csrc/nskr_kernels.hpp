@@ -442,6 +442,20 @@ template <typename T> struct Inst {
     double t0;                 // batch: the instance's time at admission
 };
 
+// What the stage kernels write.
+// kUtParts: U_t in FP32 for model 2, where the divergence of p_alpha (p + alpha/2
+// rho^2) and the source alpha rho grad c all but cancel, so that each rounding of
+// a value of the size of p_alpha shows.  Of the momenta and the energy (v = 1..4)
+// the volume sum and the source go through memory apart (Ut and Q) and meet the
+// surface sum unrounded, and so do the convective flux and the own side's
+// viscous one (TF, and the traces' second buffer, which only a step uses): U_t
+// then differs by 1e-6 (2-norm) from an evaluation with one accumulator, by up to
+// 1.3e-4 where they are summed first (33x27x28 elements of N = 4; round-off against
+// FP64 6.6e-4 in both).  Its price, on 41x33x35 elements of N = 3: 283 -> 339 us.
+// A step keeps the sums: its state does not resolve the difference.  Model 1's U_t
+// moves by 3e-6 at most.
+enum { kUt, kRk, kG2, kUtParts };
+
 // Kernel argument: a single instance by value, or (BATCH) a device table of
 // instances with a block map (instance and first element of every block),
 // plus what is common to the launch.
@@ -451,7 +465,8 @@ template <typename T> struct Launch {
     const int *blk_inst, *blk_e0;
     const int *blk_map;  // single instance: first element of every tile
     Basis bas;
-    int mode;        // 0 write U_t; 1 RK stage (update U, R, write traces); 2 write grad T and lap c (k_lift2)
+    int mode;        // kUt write U_t; kRk RK stage (update U, R, write traces); kG2 write grad T and lap c
+                     // (k_lift2); kUtParts write U_t from its parts
     int first;       // RK: assign R at the first stage
     int last;        // RK: the step's last stage, which does not store R (the next
                      // stage to read it is a first stage, which assigns it)
@@ -902,20 +917,22 @@ __device__ __forceinline__ T stage_node_metrics(const MeshDev &m, size_t NN, siz
     return T(1) / gld(nm + 9 * NN, (uint32_t)g);
 }
 
-// Gradient from its contravariant components, Ja^d / J of the element times the
-// reference derivatives: the factors are the same for every field, and on a box
-// along the axes (DIAG) bitwise those of the general form, whose other products
-// are zero there.
+// Physical gradient from the reference derivatives: 1/J times the sum of Ja^d
+// times derivative d; on a box along the axes (DIAG) bitwise the general form,
+// whose other products are zero there.  The sum is scaled and not Ja^d by 1/J
+// beforehand: that factor's rounding is the same at every node of an element,
+// and one in grad c or grad rho does not cancel in the source (FP32, 7x6x5
+// elements of N = 3: 1.75e-6 of U_t in the 2-norm, of 2.3e-5 in all).
 template <bool DIAG, typename T>
 __device__ __forceinline__ void to_physical(const T Ja[9], T iJ, const T gd[3], T q[3])
 {
     if constexpr (DIAG) {  // Ja^d along axis d
 #pragma unroll
-        for (int m = 0; m < 3; ++m) q[m] = (iJ * Ja[4 * m]) * gd[m];
+        for (int m = 0; m < 3; ++m) q[m] = iJ * (Ja[4 * m] * gd[m]);
         return;
     }
 #pragma unroll
-    for (int m = 0; m < 3; ++m) q[m] = (iJ * Ja[m]) * gd[0] + (iJ * Ja[3 + m]) * gd[1] + (iJ * Ja[6 + m]) * gd[2];
+    for (int m = 0; m < 3; ++m) q[m] = iJ * (Ja[m] * gd[0] + Ja[3 + m] * gd[1] + Ja[6 + m] * gd[2]);
 }
 
 template <bool UNI, typename T> __device__ __forceinline__ void element_metrics(const MeshDev &m, int e, T Ja[9], T &iJ)
@@ -1296,7 +1313,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
     // and their BR1 face values while they are lifted; then
     //   rows 0..2  (tau . n_d)_0, (tau . n_d)_1 of direction d
     //   rows 3..5  (tau . n_d)_2, div u
-    //   rows 6..8  T, contravariant grad c_d; then grad T . n_d, lap c
+    //   rows 6..8  T, grad c . n_d; then grad T . n_d, lap c
     // so that a face task reads three pairs; and the contravariant fluxes of
     // the volume integral over rows 6..8 (directions 0 and 2) and rows 0, 3, 1
     // (direction 1, whose values every thread has read by then).
@@ -1345,6 +1362,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
     // surface element are loaded with its traces too (in FP32 the registers
     // would cost a wave per SIMD)
     constexpr bool kOne = G::NF <= NT && sizeof(T) == 8;
+    const bool parts = sizeof(T) == 4 && !BATCH && L.mode == kUtParts;
     struct Tr {
         int nb;
         T own[3], oth[3], wn[6], uo[6];
@@ -1443,6 +1461,14 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
             T K[6];
             if (a.ph.model == 2) {
                 hllc(uf, po, co, tr.wn, pn, cn, n, K);
+                if (parts) {
+                    const FaceIx<G::n2> o((size_t)el * 6 + f, ft.fp);
+#pragma unroll
+                    for (int v = 1; v < 5; ++v) {
+                        a.TF[o.at(6, v)] = K[v];
+                        K[v] = T(0);
+                    }
+                }
             } else {
                 const T mn = uf[1] * n[0] + uf[2] * n[1] + uf[3] * n[2];
                 const T mo = tr.wn[1] * n[0] + tr.wn[2] * n[1] + tr.wn[3] * n[2];
@@ -1474,7 +1500,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
             }
 #pragma unroll
             for (int k = 0; k < 5; ++k) w[k] = T(0.5) * (w[k] + v5[k]);
-            Ts = T(0.5 * (To + Tn));
+            Ts = T(0.5) * (T(To) + T(Tn));
             Fs = T(0.5) * (tr.own[0] - tr.oth[0]) * dS;
         } else {
             wall_primitives(a.mesh, el, f, n, w);
@@ -1590,21 +1616,21 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
             // elements); its face values are the prolongations of these nodal
             // values (n_d is constant on the face), so a face task prolongs
             // 6 fields instead of 13
-            // (gc: the contravariant components from here on)
+            // (gc: the components along the n_d from here on.  They and the fluxes
+            // below are scaled by the surface element after they are summed: scaled
+            // node by node in FP32, each node's rounding is differentiated)
             const T mu = a.pt.mu, td = T(2.0 / 3.0) * div, g0 = gc[0], g1 = gc[1], g2 = gc[2];
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-                const int jr = kEmJa + 3 * d, fr = (2 * d + 1) * 4;
+                const int fr = (2 * d + 1) * 4;
                 T tn[3];
                 if constexpr (DIAG) {  // n_d is the unit vector of axis d
-                    gc[d] = em_at<G::kUni, T>(a.mesh, e, jr + d) * gc[d];
 #pragma unroll
                     for (int m = 0; m < 3; ++m) tn[m] = mu * ((gu[m][d] + gu[d][m]) - (m == d ? td : T(0)));
                 } else {
-                    gc[d] = em_at<G::kUni, T>(a.mesh, e, jr) * g0 + em_at<G::kUni, T>(a.mesh, e, jr + 1) * g1 +
-                            em_at<G::kUni, T>(a.mesh, e, jr + 2) * g2;
                     const T n0 = em_at<G::kUni, T>(a.mesh, e, fr), n1 = em_at<G::kUni, T>(a.mesh, e, fr + 1),
                             n2 = em_at<G::kUni, T>(a.mesh, e, fr + 2);
+                    gc[d] = n0 * g0 + n1 * g1 + n2 * g2;
 #pragma unroll
                     for (int m = 0; m < 3; ++m)
                         tn[m] = mu * ((gu[m][0] + gu[0][m]) * n0 + (gu[m][1] + gu[1][m]) * n1 +
@@ -1641,7 +1667,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
         __syncthreads();
     }
     // grad T (BR1 with T*) and lap c (divergence lifting of grad c from its
-    // contravariant components)
+    // components along the normals; curved: its contravariant components)
     T gT[3] = {T(0), T(0), T(0)}, lap = T(0);
     if (act) {
         const int idx[3] = {i, j, k};
@@ -1660,6 +1686,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
             }
             const V2<T> lh = B.Lh[idx[d]], vp = sTF[fbase + (2 * d + 1) * G::n2 + fpd[d]], vm = sTF[fbase + (2 * d) * G::n2 + fpd[d]];
             if constexpr (!CV) gd[d] = accT + (lh.y * vp.x - lh.x * vm.x);
+            if constexpr (!CV) ad = em_at<G::kUni, T>(a.mesh, e, (2 * d + 1) * 4 + 3) * ad;
             dl += ad + lh.y * vp.y + lh.x * vm.y;
         }
         if constexpr (CV) {
@@ -1674,14 +1701,14 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
             to_physical<DIAG>(Ja, iJ, gd, gT);
         }
         lap = iJ * dl;
-        if (L.mode == 2) {  // the second lifting's output alone
+        if (L.mode == kG2) {  // the second lifting's output alone
             gst(a.G2 + (0) * a.NN, g32, T(gT[0]));
             gst(a.G2 + (1) * a.NN, g32, T(gT[1]));
             gst(a.G2 + (2) * a.NN, g32, T(gT[2]));
             gst(a.G2 + (3) * a.NN, g32, T(lap));
         }
     }
-    if (L.mode == 2) return;
+    if (L.mode == kG2) return;
     T zc;
     __syncthreads();
     if (act) {
@@ -1807,8 +1834,16 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
         K[4] -= -a.pt.gam * c * gcn * dv + a.pt.gam * gcn * zeta;
         K[5] -= a.pt.gb * gcn;
         dS *= T(0.5);
+        T *TV = a.TU + 6 * NF;
+        if (parts) {
 #pragma unroll
-        for (int v = 0; v < 6; ++v) a.TF[o.at(6, v)] = K[v] * dS;
+            for (int v = 1; v < 5; ++v) TV[o.at(4, v - 1)] = K[v];
+            a.TF[o.at(6, 0)] = K[0] * dS;
+            a.TF[o.at(6, 5)] = K[5] * dS;
+        } else {
+#pragma unroll
+            for (int v = 0; v < 6; ++v) a.TF[o.at(6, v)] = K[v] * dS;
+        }
     }
     if (WALL && a.mesh.wall)
     for (int task = t; task < G::NF; task += NT) {
@@ -1897,7 +1932,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
     // the RK register of this node, requested now so that the loads complete
     // during the volume integral
     T Rn[6];
-    if (L.mode == 1 && act && !L.first) {
+    if (L.mode == kRk && act && !L.first) {
 #pragma unroll
         for (int v = 0; v < 6; ++v) Rn[v] = gld(a.R + (v) * a.NN, g32);
     }
@@ -1907,16 +1942,12 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
     T acc[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
     // row q of the fluxes of direction 1 (odd) or 0 and 2
     auto frow = [&](bool odd, int q) { return odd ? (CV ? 8 + q : (q == 0 ? 0 : (q == 1 ? 3 : 1))) : kT + q; };
-    auto put_flux = [&](int d) {
-        // contravariant fluxes Ja^d . F of (F^C - F^V), F^V = (0, tau, tau u +
-        // j_e, gamma beta grad c): on affine elements Ja^d . tau is dS_d times
-        // tau . n_d
-        T J[3], tj[3], gj, qj, mJ;
-        if constexpr (CV) {
-            const V2<T> jj = sJ[d][tq];
-            J[0] = jj.x;
-            J[1] = jj.y;
-            J[2] = sJz[d][tq];
+    // (F^C - F^V), F^V = (0, tau, tau u + j_e, gamma beta grad c): curved elements
+    // form the tensor, whose rows Ja^d takes at each node; affine ones the flux
+    // along n_d, times dS_d
+    T Fx[CV ? 6 : 1][3];
+    if constexpr (CV) {
+        if (act) {
             T gg[10];
 #pragma unroll
             for (int r = 0; r < 5; ++r) {
@@ -1924,39 +1955,57 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
                 gg[2 * r] = v.x;
                 gg[2 * r + 1] = v.y;
             }
+            const T u[3] = {un[1] * irn, un[2] * irn, un[3] * irn};
             const T mu = a.pt.mu, td = T(2.0 / 3.0) * div;
 #pragma unroll
-            for (int m = 0; m < 3; ++m)
-                tj[m] = mu * ((gg[3 * m] + gg[m]) * J[0] + (gg[3 * m + 1] + gg[3 + m]) * J[1] +
-                              (gg[3 * m + 2] + gg[6 + m]) * J[2] - td * J[m]);
-            gj = J[0] * gc[0] + J[1] * gc[1] + J[2] * gc[2];
-        } else {
+            for (int r = 0; r < 3; ++r) {
+                T tau[3];
 #pragma unroll
-            for (int m = 0; m < 3; ++m)
-                J[m] = !DIAG || m == d ? em_at<G::kUni, T>(a.mesh, e, kEmJa + 3 * d + m) : T(0);
-            const T dS = em_at<G::kUni, T>(a.mesh, e, (2 * d + 1) * 4 + 3);
+                for (int m = 0; m < 3; ++m) tau[m] = mu * (gg[3 * m + r] + gg[3 * r + m] - (m == r ? td : T(0)));
+                Fx[0][r] = un[1 + r];
+#pragma unroll
+                for (int m = 0; m < 3; ++m) Fx[1 + m][r] = un[1 + m] * u[r] + (m == r ? p : T(0)) - tau[m];
+                Fx[4][r] = (un[4] + p) * u[r] - (tau[0] * u[0] + tau[1] * u[1] + tau[2] * u[2]) -
+                           (a.pt.kappa * gT[r] + zc * gc[r]);
+                Fx[5][r] = un[5] * u[r] - a.pt.gb * gc[r];
+            }
+        }
+    }
+    auto put_flux = [&](int d) {
+        T f[6];
+        if constexpr (CV) {
+            const V2<T> jj = sJ[d][tq];
+            const T jz = sJz[d][tq];
+#pragma unroll
+            for (int v = 0; v < 6; ++v) f[v] = jj.x * Fx[v][0] + jj.y * Fx[v][1] + jz * Fx[v][2];
+        } else {
+            const int fr = (2 * d + 1) * 4;
+            const T gn = d == 0 ? gc[0] : (d == 1 ? gc[1] : gc[2]);
+            T n[3], mn, qn;
+            if constexpr (DIAG) {
+                mn = un[1 + d];
+                qn = gT[d];
+            } else {
+#pragma unroll
+                for (int m = 0; m < 3; ++m) n[m] = em_at<G::kUni, T>(a.mesh, e, fr + m);
+                mn = n[0] * un[1] + n[1] * un[2] + n[2] * un[3];
+                qn = n[0] * gT[0] + n[1] * gT[1] + n[2] * gT[2];
+            }
             const V2<T> x = sR[d][tq], y = sR[3 + d][tq];
-            tj[0] = dS * x.x;
-            tj[1] = dS * x.y;
-            tj[2] = dS * y.x;
-            gj = d == 0 ? gc[0] : (d == 1 ? gc[1] : gc[2]);
-        }
-        if constexpr (DIAG) {
-            qj = J[d] * gT[d];
-            mJ = J[d] * un[1 + d];
-        } else {
-            qj = J[0] * gT[0] + J[1] * gT[1] + J[2] * gT[2];
-            mJ = J[0] * un[1] + J[1] * un[2] + J[2] * un[3];
-        }
-        const T uJ = mJ * irn;
-        const T tw = (tj[0] * un[1] + tj[1] * un[2] + tj[2] * un[3]) * irn;
-        T mf[3];
+            const T tn[3] = {x.x, x.y, y.x}, vn = mn * irn, dS = em_at<G::kUni, T>(a.mesh, e, fr + 3);
+            f[0] = mn;
 #pragma unroll
-        for (int m = 0; m < 3; ++m) mf[m] = (DIAG && m != d ? un[1 + m] * uJ : un[1 + m] * uJ + p * J[m]) - tj[m];
-        sR[frow(d & 1, 0)][tq] = V2<T>{mJ, mf[0]};
-        sR[frow(d & 1, 1)][tq] = V2<T>{mf[1], mf[2]};
-        sR[frow(d & 1, 2)][tq] = V2<T>{(un[4] + p) * uJ - tw - (a.pt.kappa * qj + zc * gj),
-                                       un[5] * uJ - a.pt.gb * gj};
+            for (int m = 0; m < 3; ++m) {
+                if constexpr (DIAG) f[1 + m] = un[1 + m] * vn + (m == d ? p : T(0)) - tn[m];
+                else f[1 + m] = un[1 + m] * vn + p * n[m] - tn[m];
+            }
+            f[4] = (un[4] + p) * vn - (tn[0] * un[1] + tn[1] * un[2] + tn[2] * un[3]) * irn - (a.pt.kappa * qn + zc * gn);
+            f[5] = un[5] * vn - a.pt.gb * gn;
+#pragma unroll
+            for (int v = 0; v < 6; ++v) f[v] *= dS;
+        }
+#pragma unroll
+        for (int r = 0; r < 3; ++r) sR[frow(d & 1, r)][tq] = V2<T>{f[2 * r], f[2 * r + 1]};
     };
     __syncthreads();
     if (act) put_flux(0);
@@ -1986,13 +2035,17 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
         }
     }
     // the volume part W = S - iJ acc of U_t, into the register (RK) or the
-    // output (U_t alone); k_update adds the surface part
+    // output (U_t alone); k_update adds the surface part (kUtParts: the sum and
+    // the source)
     if (!act) return;
     const T A = T(L.A), dt = T(a.dt);
 #pragma unroll
     for (int v = 0; v < 6; ++v) {
         const T W = -acc[v] * iJ + S[v];
-        if (L.mode == 0) gst(a.Ut + (v) * a.NN, g32, W);
+        if (parts && v % 5) {
+            gst(a.Ut + (v) * a.NN, g32, acc[v]);
+            gst(a.Q + (v) * a.NN, g32, S[v]);
+        } else if (L.mode != kRk) gst(a.Ut + (v) * a.NN, g32, W);
         else gst(a.R + (v) * a.NN, g32, L.first ? dt * W : A * Rn[v] + dt * W);
     }
 }
@@ -2031,7 +2084,10 @@ __global__ __launch_bounds__((UpdateGroup<P, FEW>::NT)) void k_update(Launch<T> 
     const size_t NF = (size_t)E * 6 * G::n2;
 
     // per face point: (F* . n) dS, the difference of the two sides' flux
-    // traces (the wall flux on walls)
+    // traces (the wall flux on walls; kUtParts: the own side's convective flux
+    // plus half the difference of the viscous ones, both still times dS)
+    const bool parts = sizeof(T) == 4 && !BATCH && L.mode == kUtParts;
+    const T *TV = a.TU + 6 * NF;
     for (int task = t; task < G::NF; task += BS) {
         const FaceTask<P> ft(task);
         const int el = e0 + ft.le;
@@ -2044,7 +2100,16 @@ __global__ __launch_bounds__((UpdateGroup<P, FEW>::NT)) void k_update(Launch<T> 
         if (nb >= 0) {
             const FaceIx<G::n2> on(nbr_face<P>(nb), nbr_point<P>(nb, ft.fp));
 #pragma unroll
-            for (int v = 0; v < 6; ++v) Kn[v] = a.TF[on.at(6, v)];
+            for (int v = 0; v < 6; ++v) Kn[v] = parts && v % 5 ? TV[on.at(4, v - 1)] : a.TF[on.at(6, v)];
+            if (parts) {
+                const T dS = face_dS<P, T, CV>(a.mesh, (size_t)el * 6 + ft.f, ft.fp);
+#pragma unroll
+                for (int v = 1; v < 5; ++v) {
+                    const T vis = T(0.5) * (TV[o.at(4, v - 1)] - Kn[v]) * dS;
+                    K[v] = vis + K[v] * dS;
+                    Kn[v] = T(0);
+                }
+            }
 #pragma unroll
             for (int v = 0; v < 6; ++v) K[v] -= Kn[v];
         }
@@ -2054,9 +2119,9 @@ __global__ __launch_bounds__((UpdateGroup<P, FEW>::NT)) void k_update(Launch<T> 
     }
     // this node's state and register (and compensation of an FP32 instance)
     T u6[6], Rn[6], Cn[6], iJ = T(0);
-    const bool rk = L.mode == 1;
+    const bool rk = L.mode == kRk;
     if (act) {
-        T *R = rk ? a.R : a.Ut;  // holds the volume part
+        T *R = rk ? a.R : a.Ut;  // holds the volume part (kUtParts: its sum)
 #pragma unroll
         for (int v = 0; v < 6; ++v) Rn[v] = gldn<NT>(R + (v) * a.NN, g32);
         if (rk) {
@@ -2076,6 +2141,10 @@ __global__ __launch_bounds__((UpdateGroup<P, FEW>::NT)) void k_update(Launch<T> 
         const int idx[3] = {i, j, k};
         const int fpd[3] = {j + P * k, i + P * k, i + P * j};
         const int fbase = le * 6 * G::n2;
+        if (parts) {
+#pragma unroll
+            for (int v = 1; v < 5; ++v) acc[v] = Rn[v];
+        }
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             const V2<T> lh = B.Lh[idx[d]];
@@ -2088,7 +2157,10 @@ __global__ __launch_bounds__((UpdateGroup<P, FEW>::NT)) void k_update(Launch<T> 
         }
         if (!rk) {
 #pragma unroll
-            for (int v = 0; v < 6; ++v) gst(a.Ut + (v) * a.NN, g32, Rn[v] - acc[v] * iJ);
+            for (int v = 0; v < 6; ++v) {
+                const T W = parts && v % 5 ? gld(a.Q + v * a.NN, g32) : Rn[v];
+                gst(a.Ut + (v) * a.NN, g32, W - acc[v] * iJ);
+            }
         }
     }
     if (!rk) return;

@@ -880,7 +880,7 @@ template <int P, typename T, bool CV> struct Impl {
         const auto lift2 = lift2_kernel<true>(wall, diag);
         Launch<T> L = L0;
         for (int st = 0; st < 5; ++st) {
-            L.mode = 1;
+            L.mode = kRk;
             L.first = st == 0;
             L.last = st == 4;
             L.A = kRkA[st];
@@ -906,7 +906,7 @@ template <int P, typename T, bool CV> struct Impl {
     static int rhs(nskr_ctx *c, const void *U, void *Ut, hipStream_t s)
     {
         Launch<T> L = launch(c, inst(c, U, nullptr, Ut, 0.0));
-        L.mode = 0;
+        L.mode = sizeof(T) == 4 && c->ph.model == 2 ? kUtParts : kUt;
         prolong(c, L, s);
         lift1(c, L, s);
         lift2(c, L, s);
@@ -930,7 +930,7 @@ template <int P, typename T, bool CV> struct Impl {
         const double t0 = c->time;
         for (int n = 0; n < nsteps; ++n)
             for (int st = 0; st < 5; ++st) {
-                L.mode = 1;
+                L.mode = kRk;
                 L.first = st == 0;
                 L.last = st == 4;
                 L.A = kRkA[st];
@@ -960,7 +960,7 @@ template <int P, typename T, bool CV> struct Impl {
     {
         Launch<T> L = launch(c, inst(c, U, nullptr, nullptr, 0.0));
         L.full = 1;  // every lifted gradient and the nodal temperature
-        L.mode = 2;
+        L.mode = kG2;
         prolong(c, L, s);
         lift1(c, L, s);
         lift2(c, L, s);
