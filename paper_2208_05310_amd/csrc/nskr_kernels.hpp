@@ -1295,10 +1295,11 @@ template <int P> using Lift2Group = Group<P, StageTile<P>::kLift2, true>;
 template <int P, typename T, bool CV> constexpr int lift2_waves() { return CV ? 1 : (sizeof(T) == 8 ? 4 : 6); }
 
 // WALL: the mesh (or a batch's) has wall faces; without them the wall pass and
-// its registers are left out.  DIAG: every element is a box along the axes, so
-// Ja^d has the component d alone (the others are exactly zero, and leaving them
-// out changes no finite result): three products for a gradient instead of
-// twelve, and no normal components of the stress to form.
+// its registers are left out.  DIAG: every element is a box along the axes, Ja^d
+// a positive multiple of e_d (the other components are exactly zero, and leaving
+// them out changes no finite result) and the normal of face 2d+1 e_d: three
+// products for a gradient instead of twelve, and no normal components of the
+// stress to form.
 template <int P, typename T, bool BATCH, bool CV, bool WALL, bool DIAG>
 __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void k_lift2(Launch<T> L, int tiles)
 {

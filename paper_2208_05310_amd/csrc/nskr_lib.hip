@@ -41,7 +41,7 @@ struct nskr_ctx {
     double *d_xnode = nullptr;   // curved: node coordinates
     BcDev *d_bcs = nullptr;
     int wall = 0;                // some face is a wall
-    bool diag = false;           // every element is a box along the axes (Ja^d has component d alone)
+    bool diag = false;           // every element is a box along the axes (Ja^d is a positive multiple of e_d)
     int dyn = 0;                 // a Navier-slip wall with gamma_1 != 0
     double *d_stab = nullptr;    // wall-temperature table (walls with a temperature gradient)
     int var = 0;                 // some wall has a temperature gradient or rate
@@ -1670,10 +1670,12 @@ int nskr_mesh_upload(nskr_ctx *c, const nskr_mesh *m, nskr_stream sv)
             }
         }
     }
+    // (an element with two axes reversed has a diagonal Ja too, with negative
+    // entries: n_d is -e_d there)
     bool diag = !curved;
     for (size_t e = 0; diag && e < (size_t)E; ++e)
         for (int q = 0; q < 9; ++q)
-            if (q % 4 != 0 && emet[e * 10 + q] != 0.0) diag = false;
+            if (q % 4 != 0 ? emet[e * 10 + q] != 0.0 : !(emet[e * 10 + q] > 0.0)) diag = false;
     // the two sides of an interior face use exactly opposite normals and the
     // same surface element (conservation): one side (the master: the face on
     // the element's + side, else the lower element and face) keeps its own,
