@@ -1349,20 +1349,17 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
     const size_t NF = (size_t)E * 6 * G::n2;
     const T *TU = a.TU + (size_t)L.tb * 6 * NF;
 
-    // face work runs as face tasks (one face point per thread, a second round
-    // where the block has more face points than threads); the first round's
-    // traces are loaded before the node loads: both sides' conserved state
-    // (the own side's is the prolongation of the state, written by the
-    // previous stage), (grad c) . n and |grad c|^2
-    // Of the first round's face point, the convective part of the flux and
-    // the face values that its viscous part needs stay in registers until
-    // that part is known; the second round's wait in the flux trace and are
-    // formed again from the own trace.
-    constexpr bool kKeep = G::NF <= NT;
-    // FP64, where one round covers the block: the face point's normal and
-    // surface element are loaded with its traces too (in FP32 the registers
-    // would cost a wave per SIMD)
-    constexpr bool kOne = G::NF <= NT && sizeof(T) == 8;
+    // face work: one face point per thread, as loops of at most one turn (as
+    // plain conditions the compiler keeps what the phases share in registers and
+    // spills 5 to 8 of them in the FP32 instances with walls).  The traces are
+    // loaded before the node loads: both sides' conserved state (the own side's
+    // is the prolongation of the state, written by the previous stage), (grad
+    // c) . n and |grad c|^2.  The convective part of the flux and the face values
+    // that its viscous part needs stay in registers until that part is known.
+    static_assert(G::NF <= NT, "one face point per thread");
+    // FP64: the face point's normal and surface element are loaded with its
+    // traces too (in FP32 the registers would cost a wave per SIMD)
+    constexpr bool kOne = sizeof(T) == 8;
     const bool parts = sizeof(T) == 4 && !BATCH && L.mode == kUtParts;
     struct Tr {
         int nb;
@@ -1422,7 +1419,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
         sWc[tq] = w[4];
         if constexpr (CV) iJn = stage_node_metrics<T, NJV>(a.mesh, a.NN, g, tq, sJ, sJz);
     }
-    // what the flux pass needs of the first round's face point
+    // what the flux pass needs of this face point
     T Kc[6], fu[3], fc = T(0), frc = T(0), fgn = T(0), fdS = T(0);
     bool fwall = true;
     // face values: BR1 w* of the primitives; T* and (grad c)* . n dS of the
@@ -1483,22 +1480,16 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
                 K[4] = (uf[4] + po) * vn + hl * (uf[4] - tr.wn[4]);
                 K[5] = uf[5] * vn + hl * (uf[5] - tr.wn[5]);
             }
-            if (kKeep && task == t) {
 #pragma unroll
-                for (int v = 0; v < 6; ++v) Kc[v] = K[v];
-                fu[0] = w[1];
-                fu[1] = w[2];
-                fu[2] = w[3];
-                fc = uf[5];
-                frc = uf[0] - uf[5];
-                fgn = tr.own[0];
-                fdS = dS;
-                fwall = false;
-            } else {
-                const FaceIx<G::n2> o((size_t)el * 6 + f, ft.fp);
-#pragma unroll
-                for (int v = 0; v < 6; ++v) a.TF[o.at(6, v)] = K[v];
-            }
+            for (int v = 0; v < 6; ++v) Kc[v] = K[v];
+            fu[0] = w[1];
+            fu[1] = w[2];
+            fu[2] = w[3];
+            fc = uf[5];
+            frc = uf[0] - uf[5];
+            fgn = tr.own[0];
+            fdS = dS;
+            fwall = false;
 #pragma unroll
             for (int k = 0; k < 5; ++k) w[k] = T(0.5) * (w[k] + v5[k]);
             Ts = T(0.5) * (T(To) + T(Tn));
@@ -1525,12 +1516,11 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
 #pragma unroll
             for (int m = 0; m < 3; ++m) sN[m][slot] = n[m] * dS;
         }
-        if (task + NT < G::NF) load_tr(task + NT, tr);
     }
     if (WALL && a.mesh.var) {
         // walls whose temperature varies along them: T* and the static
         // contact-angle flux at the local wall temperature, through the table
-        // (each thread rewrites only the face points it wrote above)
+        // (each thread rewrites only the face point it wrote above)
         double tb = 0.0;  // a batch instance's stage time
         if (BATCH && a.clk) tb = stage_time(a.t0, *a.clk, a.dt, L.cs);
         for (int task = t; task < G::NF; task += NT) {
@@ -1791,34 +1781,13 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
         const FaceTask<P> ft(task);
         const int el = e0 + ft.le, f = ft.f;
         if (el >= E) break;
-        const bool keep = kKeep && task == t;
-        if (WALL && (keep ? fwall : gld(a.mesh.nbr, el * 6 + f) < 0)) continue;
+        if (WALL && fwall) continue;
         const Pro pro{B.Lf + (f & 1) * B.PS, ft.le * G::n3 + ft.off, ft.str};
         const FaceIx<G::n2> o((size_t)el * 6 + f, ft.fp);
-        T K[6], dS;
-        T u0, u1, u2, c, rc, gcn, n[3] = {T(0), T(0), T(0)};
-        if (keep) {
+        T K[6], dS = fdS, n[3] = {T(0), T(0), T(0)};
 #pragma unroll
-            for (int v = 0; v < 6; ++v) K[v] = Kc[v];
-            u0 = fu[0]; u1 = fu[1]; u2 = fu[2];
-            c = fc;
-            rc = frc;
-            gcn = fgn;
-            dS = fdS;
-            if constexpr (CV) face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp, n, dS);
-        } else {
-#pragma unroll
-            for (int v = 0; v < 6; ++v) K[v] = a.TF[o.at(6, v)];
-            const T uo[6] = {TU[o.at(6, 0)], TU[o.at(6, 1)], TU[o.at(6, 2)], TU[o.at(6, 3)], T(0), TU[o.at(6, 5)]};
-            T w[5];
-            primitives(uo, w);
-            u0 = w[1]; u1 = w[2]; u2 = w[3];
-            c = uo[5];
-            rc = uo[0] - uo[5];
-            gcn = a.T2[o.at(kT2<T>(), 0)];
-            if constexpr (CV) face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp, n, dS);
-            else dS = face_dS<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp);
-        }
+        for (int v = 0; v < 6; ++v) K[v] = Kc[v];
+        if constexpr (CV) face_normal<P, T, CV>(a.mesh, (size_t)el * 6 + f, ft.fp, n, dS);
         // scheduling barriers keep each field group's LDS loads next to the
         // arithmetic that consumes them (otherwise all of them are hoisted
         // and the register demand limits occupancy)
@@ -1828,12 +1797,12 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
         K[1] -= tn[0];
         K[2] -= tn[1];
         K[3] -= tn[2];
-        K[4] -= tn[0] * u0 + tn[1] * u1 + tn[2] * u2;
+        K[4] -= tn[0] * fu[0] + tn[1] * fu[1] + tn[2] * fu[2];
         K[4] -= a.pt.kappa * gTn;
         // order-parameter terms of j_e and F^V_c
-        const T zeta = a.pt.beta * (a.pt.gam * lapc + a.pt.alpha * rc);
-        K[4] -= -a.pt.gam * c * gcn * dv + a.pt.gam * gcn * zeta;
-        K[5] -= a.pt.gb * gcn;
+        const T zeta = a.pt.beta * (a.pt.gam * lapc + a.pt.alpha * frc);
+        K[4] -= -a.pt.gam * fc * fgn * dv + a.pt.gam * fgn * zeta;
+        K[5] -= a.pt.gb * fgn;
         dS *= T(0.5);
         T *TV = a.TU + 6 * NF;
         if (parts) {
@@ -1846,8 +1815,7 @@ __global__ __launch_bounds__(Lift2Group<P>::NT, (lift2_waves<P, T, CV>())) void 
             for (int v = 0; v < 6; ++v) a.TF[o.at(6, v)] = K[v] * dS;
         }
     }
-    if (WALL && a.mesh.wall)
-    for (int task = t; task < G::NF; task += NT) {
+    for (int task = t; WALL && a.mesh.wall && task < G::NF; task += NT) {
         const FaceTask<P> ft(task);
         const int el = e0 + ft.le, f = ft.f;
         if (el >= E) break;
