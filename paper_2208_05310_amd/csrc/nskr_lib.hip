@@ -53,7 +53,7 @@ struct nskr_ctx {
     void *d_Ck = nullptr;        // Kahan compensation of the FP32 state update
     int *d_clk = nullptr;        // batch: steps since admission (walls whose temperature changes in time)
     double *d_part = nullptr;    // reduction partials
-    double *h_out = nullptr;     // final reduction values (pinned host memory that the kernels write)
+    double *h_out = nullptr;     // final reduction values (a slot of pinned host memory that the kernels write)
     double *d_noise = nullptr;   // init noise
     double *d_drop = nullptr;    // init droplets
     std::vector<float> cent;     // element centroids (host), for the block order
@@ -1155,6 +1155,40 @@ static double *static_scratch(int device)
     return g_scratch[device];
 }
 
+// Results of the reductions, in pinned host memory that their final kernels
+// write.  One block serves the process: a context holds a slot of it from the
+// upload of its mesh until it lets the mesh go (every call that writes a slot
+// waits for it), and contexts beyond kOutSlots allocate their own.  An allocation
+// for each upload costs 40 us (create and upload of 4x4x4 elements of N = 3: 357
+// against 318 us).  Plain arrays: contexts may be destroyed after the statics.
+constexpr int kOutSlots = 256, kOutStride = 32;
+static_assert(kNRates <= kOutStride && NSKR_NSUMS <= kOutStride, "slot");
+static std::mutex g_out_mtx;
+static double *g_out;
+static bool g_out_used[kOutSlots];
+
+static double *take_out()
+{
+    std::lock_guard<std::mutex> lock(g_out_mtx);
+    if (!g_out && hipHostMalloc((void **)&g_out, sizeof(double) * kOutSlots * kOutStride, hipHostMallocPortable) != hipSuccess)
+        g_out = nullptr;
+    for (int k = 0; g_out && k < kOutSlots; ++k)
+        if (!g_out_used[k]) {
+            g_out_used[k] = true;
+            return g_out + k * kOutStride;
+        }
+    double *p = nullptr;
+    return hipHostMalloc((void **)&p, sizeof(double) * kOutStride, hipHostMallocPortable) == hipSuccess ? p : nullptr;
+}
+
+static void give_out(double *p)
+{
+    if (!p) return;
+    std::lock_guard<std::mutex> lock(g_out_mtx);
+    if (g_out && p >= g_out && p < g_out + kOutSlots * kOutStride) g_out_used[(p - g_out) / kOutStride] = false;
+    else (void)hipHostFree(p);
+}
+
 // ------------------------------------------------------------ mesh geometry
 // Elements are given by their geometry nodes on the Gauss-Lobatto points of
 // degree ngeo <= N (Sec. 3.1: curved elements of geometry degree N_geo); the
@@ -1375,7 +1409,7 @@ static void free_mesh(nskr_ctx *c)
     c->d_clk = nullptr;
     c->d_Q = c->d_TH = c->d_G2 = c->d_T2 = c->d_TF = c->d_TU = c->d_Ck = nullptr;
     c->d_part = c->d_noise = c->d_drop = nullptr;
-    if (c->h_out) (void)hipHostFree(c->h_out);
+    give_out(c->h_out);
     c->h_out = nullptr;
     c->d_bmap = nullptr;
     std::vector<float>().swap(c->cent);
@@ -1835,8 +1869,8 @@ int nskr_mesh_upload(nskr_ctx *c, const nskr_mesh *m, nskr_stream sv)
         free_mesh(c);
         return rc;
     }
-    if (hipHostMalloc((void **)&c->h_out, sizeof(double) * NSKR_NSUMS, hipHostMallocDefault) != hipSuccess) {
-        c->h_out = nullptr;
+    c->h_out = take_out();
+    if (!c->h_out) {
         free_mesh(c);
         return fail(c, NSKR_E_NOMEM, "pinned host allocation failed");
     }
