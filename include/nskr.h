@@ -290,11 +290,10 @@ int nskr_dt(nskr_ctx *ctx, const void *U, double *dt, nskr_stream s);
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same time step, bit for bit, with the reduction's partial maxima in a
  * static device array of 4 MiB instead of the context's memory.  It calls no
- * allocating routine; its result goes through the context's pinned host
- * memory, allocated at mesh upload.  Limit: a
- * mesh of at most 131072 element tiles of the 256-thread reduction kernel
- * (tiles = nelems / floor(256 / (N+1)^3), rounded up; the 32^3 N = 5 mesh
- * has 32768), else NSKR_E_ARG with nothing enqueued.  Every call on one GPU
+ * allocating routine; its result goes through pinned host memory that the
+ * context holds since mesh upload.  Limit: a mesh of at most 131072 element
+ * tiles of 256 threads (tiles = nelems / floor(256 / (N+1)^3), rounded up; the
+ * 32^3 N = 5 mesh has 32768), else NSKR_E_ARG with nothing enqueued.  Every call on one GPU
  * shares that GPU's array: calls that overlap in time on one GPU (other host
  * threads, other streams) race and must be serialised by the caller.
  * Synchronises s.  Errors as nskr_dt; NSKR_E_STATE if the array's address
@@ -305,8 +304,8 @@ int nskr_dt_noalloc(nskr_ctx *ctx, const void *U, double *dt, nskr_stream s);
  * (the low-storage fourth-order scheme family cited in Sec. 3.1): per stage
  * R <- A_s R + dt L(U) (assigned at stage 1, so R needs no initialisation),
  * U <- U + B_s R.  R is the scheme's scratch register: its content after
- * the call is unspecified (the last stage of a step does not store it, as
- * the next stage to read it assigns it).  Asynchronous.  Errors: NSKR_E_ARG
+ * the call is unspecified (the last stage of a step leaves a part of its sum
+ * there, as the next stage to read it assigns it).  Asynchronous.  Errors: NSKR_E_ARG
  * (dt not positive and finite, nsteps < 0, null or aliasing buffers),
  * NSKR_E_STATE, NSKR_E_HIP. */
 int nskr_rk_steps(nskr_ctx *ctx, void *U, void *R, double dt, int nsteps, nskr_stream s);

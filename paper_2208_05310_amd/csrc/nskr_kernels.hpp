@@ -468,8 +468,8 @@ template <typename T> struct Launch {
     int mode;        // kUt write U_t; kRk RK stage (update U, R, write traces); kG2 write grad T and lap c
                      // (k_lift2); kUtParts write U_t from its parts
     int first;       // RK: assign R at the first stage
-    int last;        // RK: the step's last stage, which does not store R (the next
-                     // stage to read it is a first stage, which assigns it)
+    int last;        // RK: the step's last stage, whose update does not store R (the
+                     // next stage to read it is a first stage, which assigns it)
     int tb, tw;      // conserved-trace buffer read by this stage, written for the next
     int full;        // host side: launch the k_lift1 variant that also writes Q and TH
     double A, B;     // RK coefficients of this stage

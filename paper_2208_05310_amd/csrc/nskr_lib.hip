@@ -565,6 +565,12 @@ __device__ __forceinline__ void lifted_c(const T *U, const MeshDev &m, size_t NN
 // FP64 took 206 us a time step and 255 us a set of integrals, synchronisation
 // and the host's call included; now 63 and 72 us.
 enum { kRates, kSums, kInitEnergy };
+// Workgroups of k_nodal: what the card holds at once (4 per CU); each takes its
+// tiles in turn, reduces once at the end and writes one partial of each value,
+// which a second kernel (k_max_final, k_integrals_final) reduces.  One reduction
+// per tile, 20 values over 64 lanes, cost 44 of a call's 115 us on 24^3 N = 4 in
+// FP64; 512 and 2048 workgroups take 83 and 79 us where 1024 take 72.
+constexpr int kNodalGroups = 1024;
 
 template <int P, typename T, bool CV, int WHAT>
 __global__ __launch_bounds__(kBlock, CV ? 1 : 4) void k_nodal(const T *U, T *Uw, RateArgs a)
@@ -969,18 +975,14 @@ template <int P, typename T, bool CV> struct Impl {
         HIPCHK(c, hipMemcpyAsync((T *)o + c->NN, c->d_G2, sizeof(T) * 4 * c->NN, hipMemcpyDeviceToDevice, s));
         return NSKR_OK;
     }
-    // the largest wave speed, mesh factor, diffusivity and wall rate over the
-    // nodes; part holds kNRates partial maxima per tile
-    // workgroups of k_nodal: what the card holds at once (4 per CU); each takes
-    // its tiles in turn and reduces once at the end.  One reduction per tile, 20
-    // values over 64 lanes, cost 44 of a call's 115 us on 24^3 N = 4 in FP64; 512
-    // and 2048 workgroups take 83 and 79 us where 1024 take 72.
-    static int nodal_grid(const nskr_ctx *c) { return std::min(nblk256(c), 1024); }
+    static int nodal_grid(const nskr_ctx *c) { return std::min(nblk256(c), kNodalGroups); }
     template <int WHAT> static void nodal(const nskr_ctx *c, const T *U, T *Uw, double *part, double T0, hipStream_t s)
     {
         RateArgs a{mesh(c), c->ph, c->NN, part, nblk256(c), kSigN[P - 1], T0, c->bas};
         hipLaunchKernelGGL((k_nodal<P, T, CV, WHAT>), dim3(nodal_grid(c)), dim3(kBlock), 0, s, U, Uw, a);
     }
+    // the largest wave speed, mesh factor, diffusivity and wall rate over the
+    // nodes; part has room for kNRates partial maxima of each workgroup
     static int dt(nskr_ctx *c, const void *U, double *rates, hipStream_t s, double *part)
     {
         nodal<kRates>(c, (const T *)U, nullptr, part, 0.0, s);
@@ -1067,11 +1069,13 @@ static int elem_per_block(int N)
 // nearby addresses (neighbouring slabs at the same position in their own
 // order).
 constexpr int kXcds = 8;
-// Node data of a stage (U, R and the API arrays: 16 values per
-// node) beyond which its node accesses carry the non-temporal hint: half the
-// 256 MiB last-level cache.  Measured: 0.5-1.3 % faster in FP64 on the
-// 32^3 N = 5, 48x48x24 N = 3 and 50^3 N = 3 meshes, 3-5 % in FP32-mixed on the
-// N = 3 meshes; 1-8 % slower on the 16^3 N = 4 mesh, whose arrays stay cached.
+// Node data of a stage (U, R and the FP32 compensation, 12 or 18 values per
+// node, counted as 16) beyond which the update's node accesses carry the
+// non-temporal hint: half the 256 MiB last-level cache.  Without / with the hint,
+// us of two steps in FP64: N = 4 16^3 (66 MB) 754 / 865, 20^3 (128 MB) 1451 / 1530,
+// 24^3 (221 MB) 2720 / 2633; 48x48x24 N = 3 (453 MB) 5624 / 5486; 32^3 N = 5 (906 MB)
+// 9788 / 9457.  FP32-mixed: 51x25x13 N = 3 (68 MB) 1011 / 1151, 26^3 N = 4 (141 MB)
+// 2237 / 2169, 32^3 N = 5 (453 MB) 6199 / 5886.
 constexpr double kStreamBytes = 134217728.0;
 
 static int build_block_map(nskr_ctx *c)
@@ -1124,12 +1128,15 @@ static int build_block_map(nskr_ctx *c)
 }
 
 // Reduction scratch of nskr_dt_noalloc, for callers that cannot allocate:
-// kNRates partial maxima per element tile of the 256-thread reduction kernel.
+// kNRates partial maxima for each workgroup of k_nodal.  They are kNodalGroups
+// at most; the array is larger, and its size in element tiles of 256 threads
+// stays the limit of the mesh that the call takes.
 // Each device holds its own copy for the life of the
 // process; its address on each device is looked up once, at the first
 // nskr_create on that device, and only that address is handed to kernels.
 // Every partial is written before it is read, so nothing needs clearing.
 constexpr int kStaticTiles = 131072;
+static_assert(kNodalGroups <= kStaticTiles, "scratch");
 static __device__ __align__(256) double scratch[kNRates * kStaticTiles];
 
 constexpr int kMaxDevices = 64;
