@@ -2135,10 +2135,12 @@ __global__ __launch_bounds__((UpdateGroup<P, FEW>::NT)) void k_update(Launch<T> 
     if (!rk) return;
     // low-storage RK stage
     if (act) {
-        const T B = T(L.B), dJ = T(a.dt) * iJ;
+        const T B = T(L.B), dt = T(a.dt);
 #pragma unroll
         for (int v = 0; v < 6; ++v) {
-            const T r = Rn[v] - dJ * acc[v];
+            // (1/J first, as in the volume part: dt / J would round for the surface
+            // part alone, the same way in every step)
+            const T r = Rn[v] - dt * (acc[v] * iJ);
             if (!L.last) gstn<NT>(a.R + (v) * a.NN, g32, T(r));
             T u;
             if (sizeof(T) == 4 && a.Ck) {
