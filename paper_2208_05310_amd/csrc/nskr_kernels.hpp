@@ -1284,8 +1284,8 @@ __global__ __launch_bounds__(Lift1Group<P>::NT, (lift1_waves<P, T, FULL, CV, PIP
 // (N = 3 on 48x48x24: 387 us with two rounds, 291 with one; with one element
 // 325, with four 378; N = 5 on 32^3 with two elements 604 against 460).
 // FP64 instances are bound by memory latency at 4 waves per SIMD, LDS and
-// vector unit each busy for 60 % of the time (32^3 N = 5: 460 us, 3.8 TB/s of
-// algorithmic bytes); FP32 ones by instruction issue, 88 % busy (271 us).
+// vector unit each busy for 60 % of the time (32^3 N = 5: 465 us, 3.7 TB/s of
+// algorithmic bytes); FP32 ones by instruction issue, 88 % busy (274 us).
 template <int P> using Lift2Group = Group<P, StageTile<P>::kLift2, true>;
 
 // Registers: affine FP64 instances fit in the 128 of 4 waves per SIMD and affine
