@@ -426,7 +426,7 @@ __device__ __forceinline__ void source(const PhysT<T> &pt, bool m2, T rho, T c, 
 template <typename T> struct Inst {
     T *U, *R, *Ut;             // state, RK register, U_t output (rhs)
     T *Ck;                     // compensation of the state update (FP32 Kahan), or null
-    T *Q, *TH;                 // grad(rho,u,c) [15] and T, for the API outputs only
+    T *Q, *TH;                 // grad(rho,u,c) [15] and T, for the API outputs (kUtParts: Q holds the source)
     T *G2;                     // grad T + lap c [4], for the API output only
     T *T2, *TF, *TU;           // face traces: grad c . n, |grad c|^2 (+ grad c on walls) [kT2<T>()],
                                // flux [6],
